@@ -66,9 +66,9 @@ struct fgs_context {
     int ev_next = 0;
     fgs_timings acc{};
     unsigned long long *work_dev = nullptr;
-    // backward: per-Gaussian sums of the blend adjoint, 9 planes of gacc_stride
+    // backward: per-Gaussian sums of the blend adjoint, kAccStride floats each
     float *gacc = nullptr;
-    size_t gacc_stride = 0;
+    size_t gacc_cap = 0;
     std::vector<fgs_prepared *> prepared;
     // multi-camera batches: the buffers of each camera of a batch
     struct BatchCam {
@@ -290,7 +290,7 @@ fgs_status fgs_reserve(fgs_context *ctx, int64_t max_gaussians, int64_t max_pair
 size_t fgs_scratch_bytes(const fgs_context *ctx) {
     if (!ctx) return 0;
     size_t b = ctx->fb.bytes() + sizeof(FrameCounters) + ctx->ch.bytes() + (ctx->ss.rhist ? SortScratch::bytes() : 0);
-    b += 9 * ctx->gacc_stride * sizeof(float);
+    b += kAccStride * ctx->gacc_cap * sizeof(float);
     for (const fgs_prepared *p : ctx->prepared) b += p->pb.bytes();
     for (const FrameBuffers &p : ctx->pool) b += p.bytes();
     for (const fgs_frame *f : ctx->frames) b += f->fb.bytes();
@@ -1137,29 +1137,27 @@ fgs_status fgs_render_backward(fgs_context *ctx, const fgs_frame *frame, const f
     if (s != frame->stream) HIP_TRY(ctx, hipStreamWaitEvent(s, frame->done, 0));
     if (P == 0) return FGS_OK;
 
-    const size_t stride = (size_t)P;
-    if (ctx->gacc_stride < stride || !ctx->gacc) {
-        const size_t cap = stride + stride / 8 + 1024;
+    if (ctx->gacc_cap < (size_t)P || !ctx->gacc) {
+        const size_t cap = (size_t)P + (size_t)P / 8 + 1024;
         if (ctx->gacc) {
             HIP_TRY(ctx, hipDeviceSynchronize());
             (void)hipFree(ctx->gacc);
             ctx->gacc = nullptr;
-            ctx->gacc_stride = 0;
+            ctx->gacc_cap = 0;
         }
-        HIP_TRY(ctx, hipMalloc((void **)&ctx->gacc, 9 * cap * sizeof(float)));
-        ctx->gacc_stride = cap;
+        HIP_TRY(ctx, hipMalloc((void **)&ctx->gacc, kAccStride * cap * sizeof(float)));
+        ctx->gacc_cap = cap;
     }
-    const int64_t as = (int64_t)ctx->gacc_stride;
     // cleared with a fill kernel (no memset node if the caller captures a graph)
-    launch_fill_u32(reinterpret_cast<uint32_t *>(ctx->gacc), 0u, 9 * (size_t)as, s);
+    launch_fill_u32(reinterpret_cast<uint32_t *>(ctx->gacc), 0u, kAccStride * (size_t)P, s);
 
     const DevOptions dop = to_dev(frame->opt);
     const DevCamera dcam = to_dev(frame->cam);
     const FrameBuffers &fb = frame->fb;
     launch_blend_backward(fb.gs, frame->tiles_in_a ? fb.tv_a : fb.tv_b, fb.ranges, fb.T, fb.last, dL_drgb,
-                          frame->W, frame->H, dop, ctx->gacc, as, s);
+                          frame->W, frame->H, dop, ctx->gacc, s);
     const DevScene dsc = to_dev(*scene);
-    launch_preprocess_backward(dsc, dcam, dop, frame->W, frame->H, fb.gs, ctx->gacc, as, grad->means,
+    launch_preprocess_backward(dsc, dcam, dop, frame->W, frame->H, fb.gs, ctx->gacc, grad->means,
                                grad->log_scales, grad->quats, grad->opacity_logits, grad->sh, grad->plane_stride, s);
     HIP_TRY(ctx, hipGetLastError());
     return FGS_OK;
