@@ -15,30 +15,48 @@ constexpr float kHalfLog2e = 0.72134752044448170f;  // log2(e) / 2
 // rectangle [X0, X1] x [Y0, Y1] in pixel-sample coordinates (Alg. 3 with the
 // chord-overlap condition of Eq. 7).  Callers inflate k2 slightly so that no
 // contributor is ever skipped.
+// (Straight-line, and with its roundings written out: the tests of a tile's
+// regions share their lines' terms, and every form of the blend takes the same
+// decisions.)
 __device__ __forceinline__ bool rect_hit(float u, float v, float A, float B, float C, float k2, float X0, float X1,
                                          float Y0, float Y1) {
+#pragma clang fp contract(off)
     const float x0 = X0 - u, x1 = X1 - u, y0 = Y0 - v, y1 = Y1 - v;
-    if (x0 <= 0.0f && 0.0f <= x1 && y0 <= 0.0f && 0.0f <= y1) return true;
-    bool hit = false;
+    bool hit = (x0 <= 0.0f) & (0.0f <= x1) & (y0 <= 0.0f) & (0.0f <= y1);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        const float ye_ = e ? y1 : y0;
-        const float bq = 2.0f * B * ye_;
-        const float cq = C * ye_ * ye_ - k2;
-        const float delta = bq * bq - 4.0f * A * cq;
+        const float y = e ? y1 : y0;
+        const float bq = 2.0f * B * y;
+        const float cq = fmaf(y, C * y, -k2);
+        const float delta = fmaf(bq, bq, -(4.0f * A * cq));
         const float e1 = 2.0f * A * x0 + bq, e2 = 2.0f * A * x1 + bq;
-        hit |= (delta >= 0.0f) && (e1 <= 0.0f || e1 * e1 <= delta) && (e2 >= 0.0f || e2 * e2 <= delta);
+        hit |= (delta >= 0.0f) & ((e1 <= 0.0f) | (e1 * e1 <= delta)) & ((e2 >= 0.0f) | (e2 * e2 <= delta));
     }
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        const float xe_ = e ? x1 : x0;
-        const float bq = 2.0f * B * xe_;
-        const float cq = A * xe_ * xe_ - k2;
-        const float delta = bq * bq - 4.0f * C * cq;
+        const float x = e ? x1 : x0;
+        const float bq = 2.0f * B * x;
+        const float cq = fmaf(x, A * x, -k2);
+        const float delta = fmaf(bq, bq, -(4.0f * C * cq));
         const float e1 = 2.0f * C * y0 + bq, e2 = 2.0f * C * y1 + bq;
-        hit |= (delta >= 0.0f) && (e1 <= 0.0f || e1 * e1 <= delta) && (e2 >= 0.0f || e2 * e2 <= delta);
+        hit |= (delta >= 0.0f) & ((e1 <= 0.0f) | (e1 * e1 <= delta)) & ((e2 >= 0.0f) | (e2 * e2 <= delta));
     }
     return hit;
+}
+
+// The inflated extent of that test for the halves of a tile.
+__device__ __forceinline__ float test_extent(const GaussState &s) { return fmaf(s.f1.y, 1.00002f, 1e-5f); }
+
+// And for parts of a half, where it must drop nothing that the half's test
+// kept.  The discriminant cancels for long thin footprints: over the
+// ellipse's height (y^2 <= k^2 A / det) its terms reach 4 A k^2 (A C / det),
+// so a few roundings of them move it as a change of about 5e-7 (A C / det) in
+// k^2 would.  Twice that, and 2e-5 for the rest; a conic too thin to tell
+// always hits.
+__device__ __forceinline__ float test_extent_thin(const GaussState &s) {
+    const float ac = s.f0.z * s.f1.x, det = fmaf(-s.f0.w, s.f0.w, ac);
+    const float k2i = fmaf(s.f1.y, fmaf(1e-6f * ac, __builtin_amdgcn_rcpf(det), 1.00002f), 1e-5f);
+    return det > 1e-6f * ac ? k2i : INFINITY;
 }
 
 // Staged form of a Gaussian for the pixel loop.  With c = log2(e) / 2 the

@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(const GaussState *__restri
             if (j < nb) {
                 const uint32_t g = values[start + (uint32_t)lo + (uint32_t)j];
                 const GaussState s = gs[g];
-                const float k2i = s.f1.y * 1.00002f + 1e-5f;
+                const float k2i = test_extent(s);
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     const int X0i = tx * kTile + q * 8, Y0i = ty * kTile + h * 8;

@@ -2,16 +2,27 @@
 // rendering stage; Sec. 5.2 early stop on saturated transmittance, opacity
 // checks moved out of the per-pixel loop; Sec. 5.3.2 exponent in log form).
 //
-// One 128-thread workgroup per 16 x 16 tile: each wavefront owns a 16 x 8
-// half, each lane two horizontally adjacent pixels, so the row terms of the
+// One workgroup per 16 x 16 tile, in two forms (launch_blend picks one by the
+// number of tiles): two wavefronts, each owning a 16 x 8 half with two
+// horizontally adjacent pixels per lane, so that the row terms of the
 // quadratic form, the LDS reads and the loop control are shared by two
-// pixels.  The tile's sorted list is walked in batches of 128 Gaussians
-// (6.4 KB of LDS per workgroup: eight wavefronts per SIMD fit):
+// pixels; or four, each owning an 8 x 8 quadrant with one pixel per lane,
+// which walk shorter lists and fill the device when the tiles are few.  The
+// tile's sorted list is walked in batches of one Gaussian per thread (eight
+// wavefronts per SIMD fit):
 // every thread stages one Gaussian (the coefficients of the exponent,
-// opacity threshold and colour) in LDS and tests each ellipse against the two
-// halves (the exact tile test with a slightly inflated extent, so it never
-// drops a contributor); a wavefront walks only the set bits of its half's
-// masks, in scalar code.  Per pixel and Gaussian:
+// opacity threshold and colour) in LDS and tests each ellipse against the
+// regions (the exact tile test with a slightly inflated extent, so it never
+// drops a contributor); a wavefront walks only the entries that meet its
+// region, two at a time: their evaluations overlap, and the saturation check
+// of both is one (T only falls; when a pixel saturates within the pair, the
+// pair is resolved entry by entry).  Bound by FP32 issue when the tiles are
+// many (4K city 10M: 24 slots per step and two pixels) and by the serial chain
+// of a wavefront when they are few.  One entry at a time in halves took 346 us
+// at 4K and 97 / 106 / 149 us at 256 / 3600 / 8160 tiles; now 324 and 46 / 71 /
+// 115 us.  (The colour accumulated by v_mfma_f32_4x4x1_f32, which leaves 18
+// slots, was slower: 380 us at 4K.)
+// Per pixel and Gaussian:
 //   E = log2 o - q log2(e) / 2; contributes iff E >= log2 o - k^2 log2(e) / 2;
 //   alpha = min(alpha_max, 2^E);
 //   T' = T (1 - alpha); if T' < T_stop the pixel stops before blending it;
@@ -25,12 +36,287 @@ namespace fgs {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kThreads = 128;        // two wavefronts per tile
-constexpr int kBatch = 128;          // Gaussians staged per batch
-constexpr int kWords = kBatch / kWave;
+constexpr int kThreads = 128;        // two wavefronts per tile (the prefetch variant)
 constexpr float kFar = 1e30f;
 
 struct Pixel {
+    float x;        // sample x, or kFar once stopped
+    float T, c0, c1, c2;
+    uint32_t last;
+    uint32_t examined;
+    bool done;
+};
+
+// Alpha of one pixel for one Gaussian, and whether it contributes.
+struct Alpha {
+    float a;
+    bool in;
+};
+
+__device__ __forceinline__ Alpha alpha_at(float e, float thr, float amax) {
+    Alpha r;
+    r.in = e >= thr;
+    // min(2^E, amax), 0 outside the extent: the clamp's upper end is selected
+    // beside the exponential (2^E >= 0), one v_med3_f32 with no per-iteration
+    // canonicalisation of amax that a minimum would bring
+    r.a = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(e), 0.0f, r.in ? amax : 0.0f);
+    return r;
+}
+
+// kPx: horizontally adjacent pixels per lane (2: two wavefronts per tile, a
+// 16 x 8 half each; 1: four, an 8 x 8 quadrant each).
+template <int kPx, bool kCountWork, bool kLast>
+__global__ __launch_bounds__(256 / kPx) __attribute__((amdgpu_waves_per_eu(8))) void k_blend(const GaussState *__restrict__ gs,
+                                                     const uint32_t *__restrict__ values,
+                                                     const uint2 *__restrict__ ranges, int W, int H, int tiles_x,
+                                                     DevOptions op, float *__restrict__ rgb, float *__restrict__ Tout,
+                                                     uint32_t *__restrict__ last_out, unsigned long long *work) {
+    constexpr int kThreads = 256 / kPx, kBatch = kThreads;  // each thread stages one Gaussian of a batch
+    constexpr int kRegions = kThreads / kWave, kWords = kBatch / kWave;
+    // one float4 stride for all three arrays: a single LDS address per
+    // Gaussian.  Entry kBatch contributes nowhere (its threshold is +inf).
+    __shared__ float4 s_f0[kBatch + 1], s_f1[kBatch + 1], s_f2[kBatch + 1];
+    // kPx == 1: bit h of s_hit: the entry meets region h; s_list: the entries
+    // that meet region h, in list order, as byte offsets into s_f0 (padded to
+    // whole pairs with entry kBatch).  kPx == 2: s_rel[h][w]: bit i set iff
+    // entry 64 w + i meets region h; its set bits are walked in scalar code.
+    constexpr bool kList = kPx == 1;
+    __shared__ uint8_t s_hit[kList ? kBatch : 1];
+    __shared__ alignas(4) uint16_t s_list[kList ? kRegions : 1][kList ? kBatch + 2 : 2];
+    __shared__ uint32_t s_rel[kList ? 1 : kRegions][kWords][2];
+    static_assert((kBatch + 1) * sizeof(float4) <= 65536, "16-bit offsets");
+
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform
+    const int tile = blockIdx.x;
+    const int tx = tile % tiles_x, ty = tile / tiles_x;
+    const int rx = kPx == 2 ? 0 : wave & 1, ry = kPx == 2 ? wave : wave >> 1;
+    const int pi0 = tx * kTile + rx * 8 + kPx * (lane & 7);
+    const int pj = ty * kTile + ry * 8 + (lane >> 3);
+    const float py = (float)pj + 0.5f;
+
+    const uint2 rg = ranges[tile];
+    const uint32_t start = rg.x, end = rg.y > rg.x ? rg.y : rg.x;  // an empty tile may hold start > end
+    Pixel p[kPx];
+    auto all_done = [&]() {
+        bool d = p[0].done;
+        if constexpr (kPx == 2) d = d && p[1].done;
+        return d;
+    };
+#pragma unroll
+    for (int i = 0; i < kPx; ++i) {
+        const bool in = pi0 + i < W && pj < H;
+        p[i] = Pixel{in ? (float)(pi0 + i) + 0.5f : kFar, 1.0f, 0.0f, 0.0f, 0.0f, 0u, in ? end - start : 0u, !in};
+    }
+    bool wave_done = __ballot(!all_done()) == 0;
+    // loop-invariant clamp as the result of an arithmetic op (a canonical
+    // value, so the minimum needs no per-iteration canonicalisation)
+    const float amax = op.alpha_max + 0.0f;
+    const float tstop = op.T_stop;
+    uint32_t wsteps = 0;  // kCountWork: entries this wavefront evaluates (uniform)
+    if (tid == 0) {
+        s_f0[kBatch] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        s_f1[kBatch] = make_float4(0.0f, INFINITY, 0.0f, 0.0f);
+        s_f2[kBatch] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    // kPx == 1 (few tiles, so little else hides it): the next batch's state is
+    // loaded while this one is blended
+    constexpr bool kAhead = kPx == 1;
+    GaussState ahead;
+    if (kAhead && start + tid < end) ahead = gs[values[start + tid]];
+
+    for (uint32_t b0 = start; b0 < end; b0 += kBatch) {
+        const uint32_t nb = (end - b0) < (uint32_t)kBatch ? (end - b0) : (uint32_t)kBatch;
+        {
+            uint32_t hm = 0;
+            if ((uint32_t)tid < nb) {
+                const GaussState s = kAhead ? ahead : gs[values[b0 + tid]];
+                const float k2i = test_extent(s);
+                // region [x, x + w) x [y, y + 8), cut by the image
+                auto meets = [&](int X0i, int w, int Y0i, float k2) {
+                    int X1i = X0i + w, Y1i = Y0i + 8;
+                    X1i = X1i > W ? W : X1i;
+                    Y1i = Y1i > H ? H : Y1i;
+                    const bool in = (X0i < X1i) & (Y0i < Y1i);
+                    return in & rect_hit(s.f0.x, s.f0.y, s.f0.z, s.f0.w, s.f1.x, k2, (float)X0i + 0.5f,
+                                         (float)X1i - 0.5f, (float)Y0i + 0.5f, (float)Y1i - 0.5f);
+                };
+                // (a quadrant counts only where its half is met, so that both
+                // forms blend the same entries)
+                const float k2t = kPx == 1 ? test_extent_thin(s) : 0.0f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bool half = meets(tx * kTile, kTile, ty * kTile + 8 * h, k2i);
+                    if constexpr (kPx == 2) {
+                        hm |= (uint32_t)half << h;
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)
+                            hm |= (uint32_t)(half & meets(tx * kTile + 8 * q, 8, ty * kTile + 8 * h, k2t))
+                                  << (2 * h + q);
+                    }
+                }
+                float4 f0, f1;
+                float2 f2;
+                stage_gauss(s, f0, f1, f2);
+                s_f0[tid] = f0;
+                s_f1[tid] = f1;
+                s_f2[tid] = make_float4(f2.x, f2.y, 0.0f, 0.0f);
+            }
+            if constexpr (kList) {
+                s_hit[tid] = (uint8_t)hm;
+            } else {
+#pragma unroll
+                for (int h = 0; h < kRegions; ++h) {
+                    const uint64_t bq = __ballot((hm >> h) & 1u);
+                    if (lane == 0) {
+                        s_rel[h][wave][0] = (uint32_t)bq;
+                        s_rel[h][wave][1] = (uint32_t)(bq >> 32);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (kAhead && b0 + kBatch + tid < end) ahead = gs[values[b0 + kBatch + tid]];
+        if (!wave_done) {
+            const uint32_t pos1 = b0 - start + 1u;
+            // two staged Gaussians (byte offsets into s_f0) for the lane's
+            // pixels: their chains overlap, and one termination check covers
+            // both; true once every pixel of the wavefront has stopped
+            auto blend_two = [&](uint32_t offa, uint32_t offb) {
+                const uint32_t off[2] = {offa, offb};
+                float4 f0[2], f1[2];
+                float2 f2[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    f0[k] = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_f0) + off[k]);
+                    f1[k] = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_f1) + off[k]);
+                    f2[k] = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(s_f2) + off[k]);
+                }
+                Alpha a[2][kPx];
+                float T[3][kPx];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const RowTerms rt = row_terms(f0[k], f1[k], py);
+#pragma unroll
+                    for (int i = 0; i < kPx; ++i) a[k][i] = alpha_at(exponent_at(f0[k], rt, p[i].x), f1[k].y, amax);
+                }
+                bool low = false;
+#pragma unroll
+                for (int i = 0; i < kPx; ++i) {
+                    T[0][i] = p[i].T;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) T[k + 1][i] = fmaf(-a[k][i].a, T[k][i], T[k][i]);
+                    low = low || T[2][i] < tstop;
+                }
+                // (T only falls, so the first of them cannot pass the
+                // threshold unseen)
+                if (__ballot(low) != 0) {
+#pragma unroll
+                    for (int i = 0; i < kPx; ++i) {
+                        // the pixel saturates: it stops before the first
+                        // Gaussian that would pass the threshold (rare path)
+                        bool stopped = false;
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            if (!stopped && T[k + 1][i] < tstop) {
+                                stopped = true;
+                                if (kCountWork) p[i].examined = pos1 + off[k] / (uint32_t)sizeof(float4);
+                                p[i].x = kFar;
+                                p[i].done = true;
+                            }
+                            if (stopped) {
+                                a[k][i].a = 0.0f;
+                                a[k][i].in = false;
+                                T[k + 1][i] = T[k][i];
+                            }
+                        }
+                    }
+                    wave_done = __ballot(!all_done()) == 0;
+                }
+#pragma unroll
+                for (int i = 0; i < kPx; ++i) {
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const float w = a[k][i].a * T[k][i];
+                        p[i].c0 = fmaf(w, f1[k].w, p[i].c0);
+                        p[i].c1 = fmaf(w, f2[k].x, p[i].c1);
+                        p[i].c2 = fmaf(w, f2[k].y, p[i].c2);
+                        if (kLast) p[i].last = a[k][i].in ? pos1 + off[k] / (uint32_t)sizeof(float4) : p[i].last;
+                    }
+                    p[i].T = T[2][i];
+                }
+                return wave_done;
+            };
+            constexpr uint32_t kNone = kBatch * sizeof(float4);
+            if constexpr (kList) {
+                uint32_t n = 0;  // uniform
+                uint16_t *const list = s_list[wave];
+#pragma unroll
+                for (int w = 0; w < kWords; ++w) {
+                    const uint64_t bal = __ballot(((s_hit[w * kWave + lane] >> wave) & 1u) != 0u);
+                    const uint32_t at = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                    if ((bal >> lane) & 1u) list[at] = (uint16_t)((w * kWave + lane) * (int)sizeof(float4));
+                    n += (uint32_t)__popcll(bal);
+                }
+                if (lane == 0) list[n] = (uint16_t)kNone;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                for (uint32_t q = 0; q < n; q += 2) {
+                    const uint32_t pair = *reinterpret_cast<const uint32_t *>(list + q);
+                    if (kCountWork) wsteps += q + 1 < n ? 2u : 1u;
+                    if (blend_two(pair & 0xffffu, pair >> 16)) break;
+                }
+            } else {
+                for (int w = 0; w < kWords && !wave_done; ++w) {
+                    uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)s_rel[wave][w][0]) |
+                                 ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)s_rel[wave][w][1]) << 32);
+                    while (m) {
+                        const uint32_t ja = (uint32_t)(w * kWave + __builtin_ctzll(m));
+                        m &= m - 1;
+                        const uint32_t jb = m ? (uint32_t)(w * kWave + __builtin_ctzll(m)) : (uint32_t)kBatch;
+                        m &= m - 1;  // (0 stays 0)
+                        if (kCountWork) wsteps += jb < (uint32_t)kBatch ? 2u : 1u;
+                        if (blend_two(ja * (uint32_t)sizeof(float4), jb * (uint32_t)sizeof(float4))) break;
+                    }
+                }
+            }
+        }
+        // all 256 pixels finished: stop walking the list (also the barrier
+        // that protects the staging buffers)
+        if (__syncthreads_count(all_done() ? 1 : 0) == kThreads) break;
+    }
+
+    if (kCountWork) {
+        // a wave that skipped a Gaussian whose ellipse misses its region still
+        // counts it: the count is the method's, not this kernel's
+        unsigned long long v = 0;
+#pragma unroll
+        for (int i = 0; i < kPx; ++i) v += p[i].examined;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) v += __shfl_xor(v, d, kWave);
+        if (lane == 0) {
+            atomicAdd(work, v);
+            atomicAdd(work + 1, (unsigned long long)wsteps);
+        }
+    }
+    const size_t hw = (size_t)W * H;
+    const size_t q = (size_t)pj * W + pi0;
+#pragma unroll
+    for (int i = 0; i < kPx; ++i)
+        if (pi0 + i < W && pj < H) {
+            rgb[q + i] = p[i].c0 + p[i].T * op.bg[0];
+            rgb[hw + q + i] = p[i].c1 + p[i].T * op.bg[1];
+            rgb[2 * hw + q + i] = p[i].c2 + p[i].T * op.bg[2];
+            if (Tout) Tout[q + i] = p[i].T;
+            if (kLast && last_out) last_out[q + i] = p[i].last;
+        }
+}
+
+// ---- the variant's pixel: colour in plain registers ------------------------
+struct PixelV {
     float x;        // sample x, or kFar once stopped
     float T, c0, c1, c2;
     uint32_t last;
@@ -45,7 +331,7 @@ struct Step {
     bool in, stop;
 };
 
-__device__ __forceinline__ Step step(const Pixel &p, float e, float thr, float amax, float tstop) {
+__device__ __forceinline__ Step step(const PixelV &p, float e, float thr, float amax, float tstop) {
     Step st;
     st.in = e >= thr;
     // min(2^E, amax) as a clamp to [0, amax] (2^E >= 0): one v_med3_f32, with
@@ -58,7 +344,7 @@ __device__ __forceinline__ Step step(const Pixel &p, float e, float thr, float a
 
 // The pixel saturates: it stops before this Gaussian (rare path).
 template <bool kCountWork>
-__device__ __forceinline__ void stop_before(Pixel &p, Step &st, uint32_t pos) {
+__device__ __forceinline__ void stop_before(PixelV &p, Step &st, uint32_t pos) {
     st.a = 0.0f;
     st.Tn = p.T;
     st.in = false;
@@ -68,152 +354,13 @@ __device__ __forceinline__ void stop_before(Pixel &p, Step &st, uint32_t pos) {
 }
 
 template <bool kLast>
-__device__ __forceinline__ void apply(Pixel &p, const Step &st, const float4 &f1, const float2 &f2, uint32_t pos) {
+__device__ __forceinline__ void apply(PixelV &p, const Step &st, const float4 &f1, const float2 &f2, uint32_t pos) {
     const float w = st.a * p.T;
     p.c0 = fmaf(w, f1.w, p.c0);
     p.c1 = fmaf(w, f2.x, p.c1);
     p.c2 = fmaf(w, f2.y, p.c2);
     p.T = st.Tn;
     if (kLast) p.last = st.in ? pos + 1u : p.last;
-}
-
-template <bool kCountWork, bool kLast>
-__global__ __launch_bounds__(kThreads) void k_blend(const GaussState *__restrict__ gs,
-                                                    const uint32_t *__restrict__ values,
-                                                    const uint2 *__restrict__ ranges, int W, int H, int tiles_x,
-                                                    DevOptions op, float *__restrict__ rgb, float *__restrict__ Tout,
-                                                    uint32_t *__restrict__ last_out, unsigned long long *work) {
-    // one float4 stride for all three arrays: a single LDS address per Gaussian
-    __shared__ float4 s_f0[kBatch], s_f1[kBatch], s_f2[kBatch];
-    // s_rel[h][w]: bit i set iff entry 64 w + i of the batch meets half h
-    __shared__ uint32_t s_rel[2][kWords][2];
-
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform
-    const int tile = blockIdx.x;
-    const int tx = tile % tiles_x, ty = tile / tiles_x;
-    const int pi0 = tx * kTile + 2 * (lane & 7);
-    const int pj = ty * kTile + wave * 8 + (lane >> 3);
-    const bool in0 = pi0 < W && pj < H, in1 = pi0 + 1 < W && pj < H;
-    const float py = (float)pj + 0.5f;
-
-    const uint2 rg = ranges[tile];
-    const uint32_t start = rg.x, end = rg.y > rg.x ? rg.y : rg.x;  // an empty tile may hold start > end
-    Pixel p0{in0 ? (float)pi0 + 0.5f : kFar, 1.0f, 0.0f, 0.0f, 0.0f, 0u, in0 ? end - start : 0u, !in0};
-    Pixel p1{in1 ? (float)pi0 + 1.5f : kFar, 1.0f, 0.0f, 0.0f, 0.0f, 0u, in1 ? end - start : 0u, !in1};
-    bool wave_done = __ballot(!(p0.done && p1.done)) == 0;
-    // loop-invariant clamp as the result of an arithmetic op (a canonical
-    // value, so the minimum needs no per-iteration canonicalisation)
-    const float amax = op.alpha_max + 0.0f;
-    const float tstop = op.T_stop;
-    uint32_t wsteps = 0;  // kCountWork: entries this wavefront evaluates (uniform)
-
-    for (uint32_t b0 = start; b0 < end; b0 += kBatch) {
-        const uint32_t nb = (end - b0) < (uint32_t)kBatch ? (end - b0) : (uint32_t)kBatch;
-#pragma unroll
-        for (int r = 0; r < kBatch / kThreads; ++r) {
-            const uint32_t i = (uint32_t)(r * kThreads + tid);
-            uint32_t hm = 0;
-            if (i < nb) {
-                const GaussState s = gs[values[b0 + i]];
-                const float k2i = s.f1.y * 1.00002f + 1e-5f;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int X0i = tx * kTile, Y0i = ty * kTile + h * 8;
-                    int X1i = X0i + kTile, Y1i = Y0i + 8;
-                    X1i = X1i > W ? W : X1i;
-                    Y1i = Y1i > H ? H : Y1i;
-                    if (Y0i < Y1i && rect_hit(s.f0.x, s.f0.y, s.f0.z, s.f0.w, s.f1.x, k2i, (float)X0i + 0.5f,
-                                              (float)X1i - 0.5f, (float)Y0i + 0.5f, (float)Y1i - 0.5f))
-                        hm |= 1u << h;
-                }
-                float4 f0, f1;
-                float2 f2;
-                stage_gauss(s, f0, f1, f2);
-                s_f0[i] = f0;
-                s_f1[i] = f1;
-                s_f2[i] = make_float4(f2.x, f2.y, 0.0f, 0.0f);
-            }
-            // entry i = 128 r + 64 wave + lane: word 2 r + wave, bit lane
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint64_t bq = __ballot((hm >> h) & 1u);
-                if (lane == 0) {
-                    s_rel[h][2 * r + wave][0] = (uint32_t)bq;
-                    s_rel[h][2 * r + wave][1] = (uint32_t)(bq >> 32);
-                }
-            }
-        }
-        __syncthreads();
-        if (!wave_done) {
-            for (int wd = 0; wd < kWords && !wave_done; ++wd) {
-                uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)s_rel[wave][wd][0]) |
-                             ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)s_rel[wave][wd][1]) << 32);
-                // one staged Gaussian for both pixels of the lane; true once
-                // every pixel of the wavefront has stopped
-                auto blend_one = [&](int j) {
-                    if (kCountWork) ++wsteps;
-                    const float4 f0 = s_f0[j], f1 = s_f1[j];
-                    const float2 f2 = *reinterpret_cast<const float2 *>(&s_f2[j]);
-                    const RowTerms rt = row_terms(f0, f1, py);
-                    const float e0 = exponent_at(f0, rt, p0.x);
-                    const float e1 = exponent_at(f0, rt, p1.x);
-                    const uint32_t pos = b0 - start + (uint32_t)j;
-                    Step s0 = step(p0, e0, f1.y, amax, tstop);
-                    Step s1 = step(p1, e1, f1.y, amax, tstop);
-                    if (__ballot(s0.stop || s1.stop) != 0) {
-                        if (s0.stop) stop_before<kCountWork>(p0, s0, pos);
-                        if (s1.stop) stop_before<kCountWork>(p1, s1, pos);
-                        wave_done = __ballot(!(p0.done && p1.done)) == 0;
-                    }
-                    apply<kLast>(p0, s0, f1, f2, pos);
-                    apply<kLast>(p1, s1, f1, f2, pos);
-                    return wave_done;
-                };
-                // two Gaussians per trip (the loop-carried state alternates
-                // between register sets instead of being copied back)
-                while (m) {
-                    const int ja = wd * kWave + __builtin_ctzll(m);
-                    m &= m - 1;
-                    if (blend_one(ja) || !m) break;
-                    const int jb = wd * kWave + __builtin_ctzll(m);
-                    m &= m - 1;
-                    if (blend_one(jb)) break;
-                }
-            }
-        }
-        // all 256 pixels finished: stop walking the list (also the barrier
-        // that protects the staging buffers)
-        if (__syncthreads_count((p0.done && p1.done) ? 1 : 0) == kThreads) break;
-    }
-
-    if (kCountWork) {
-        // a wave that skipped a Gaussian whose ellipse misses its half still
-        // counts it: the count is the method's, not this kernel's
-        unsigned long long v = (unsigned long long)p0.examined + p1.examined;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) v += __shfl_xor(v, d, kWave);
-        if (lane == 0) {
-            atomicAdd(work, v);
-            atomicAdd(work + 1, (unsigned long long)wsteps);
-        }
-    }
-    const size_t hw = (size_t)W * H;
-    const size_t q = (size_t)pj * W + pi0;
-    if (in0) {
-        rgb[q] = p0.c0 + p0.T * op.bg[0];
-        rgb[hw + q] = p0.c1 + p0.T * op.bg[1];
-        rgb[2 * hw + q] = p0.c2 + p0.T * op.bg[2];
-        if (Tout) Tout[q] = p0.T;
-        if (kLast && last_out) last_out[q] = p0.last;
-    }
-    if (in1) {
-        rgb[q + 1] = p1.c0 + p1.T * op.bg[0];
-        rgb[hw + q + 1] = p1.c1 + p1.T * op.bg[1];
-        rgb[2 * hw + q + 1] = p1.c2 + p1.T * op.bg[2];
-        if (Tout) Tout[q + 1] = p1.T;
-        if (kLast && last_out) last_out[q + 1] = p1.last;
-    }
 }
 
 // Variant of the blend (selected per context): each wavefront walks its
@@ -244,8 +391,8 @@ __global__ __launch_bounds__(kThreads) void k_blend_prefetch(const GaussState *_
 
     const uint2 rg = ranges[tile];
     const uint32_t start = rg.x, end = rg.y > rg.x ? rg.y : rg.x;  // an empty tile may hold start > end
-    Pixel p0{in0 ? (float)pi0 + 0.5f : kFar, 1.0f, 0.0f, 0.0f, 0.0f, 0u, 0u, !in0};
-    Pixel p1{in1 ? (float)pi0 + 1.5f : kFar, 1.0f, 0.0f, 0.0f, 0.0f, 0u, 0u, !in1};
+    PixelV p0{in0 ? (float)pi0 + 0.5f : kFar, 1.0f, 0.0f, 0.0f, 0.0f, 0u, 0u, !in0};
+    PixelV p1{in1 ? (float)pi0 + 1.5f : kFar, 1.0f, 0.0f, 0.0f, 0.0f, 0u, 0u, !in1};
     bool wave_done = __ballot(!(p0.done && p1.done)) == 0;
     const float amax = op.alpha_max + 0.0f;
     const float tstop = op.T_stop;
@@ -343,15 +490,23 @@ void launch_blend(const GaussState *gs, const uint32_t *values, const uint2 *ran
                                nvalues, ngs, op, rgb, T, last);
         return;
     }
-    if (work)
-        hipLaunchKernelGGL((k_blend<true, true>), grid, block, 0, s, gs, values, ranges, W, H, tiles_x, op, rgb, T,
-                           last, work);
-    else if (last)
-        hipLaunchKernelGGL((k_blend<false, true>), grid, block, 0, s, gs, values, ranges, W, H, tiles_x, op, rgb, T,
-                           last, work);
-    else
-        hipLaunchKernelGGL((k_blend<false, false>), grid, block, 0, s, gs, values, ranges, W, H, tiles_x, op, rgb,
-                           T, last, work);
+    // One pixel per lane (four wavefronts per tile) while the tiles leave the
+    // device short of wavefronts or with a long tail, two per lane (about 15 %
+    // fewer instructions per pixel) above.  Blend, us, one / two per lane, 1M
+    // Gaussians in a box and 10M city: 920 tiles 96 / 123 and 136 / 244, 3600
+    // tiles 101 / 130 and 93 / 144, 8160 tiles 114 / 136 and 138 / 133, 14400
+    // tiles 173 / 179 and 202 / 183, 32400 tiles 273 / 235 and 381 / 311.
+    constexpr int kOnePixelTiles = 10240;
+    const bool one = tiles_x * tiles_y <= kOnePixelTiles;
+#define FGS_BLEND(PX, CW, KL)                                                                                     \
+    hipLaunchKernelGGL((k_blend<PX, CW, KL>), grid, dim3(256 / PX), 0, s, gs, values, ranges, W, H, tiles_x, op, \
+                       rgb, T, last, work)
+    if (work) FGS_BLEND(2, true, true);
+    else if (one && last) FGS_BLEND(1, false, true);
+    else if (one) FGS_BLEND(1, false, false);
+    else if (last) FGS_BLEND(2, false, true);
+    else FGS_BLEND(2, false, false);
+#undef FGS_BLEND
 }
 
 }  // namespace fgs
