@@ -1155,9 +1155,9 @@ fgs_status fgs_render_backward(fgs_context *ctx, const fgs_frame *frame, const f
     const DevCamera dcam = to_dev(frame->cam);
     const FrameBuffers &fb = frame->fb;
     launch_blend_backward(fb.gs, frame->tiles_in_a ? fb.tv_a : fb.tv_b, fb.ranges, fb.T, fb.last, dL_drgb,
-                          frame->W, frame->H, dop, ctx->gacc, s);
+                          frame->W, frame->H, dop, ctx->gacc, kAccStride, s);
     const DevScene dsc = to_dev(*scene);
-    launch_preprocess_backward(dsc, dcam, dop, frame->W, frame->H, fb.gs, ctx->gacc, grad->means,
+    launch_preprocess_backward(dsc, dcam, dop, frame->W, frame->H, fb.gs, ctx->gacc, kAccStride, grad->means,
                                grad->log_scales, grad->quats, grad->opacity_logits, grad->sh, grad->plane_stride, s);
     HIP_TRY(ctx, hipGetLastError());
     return FGS_OK;
