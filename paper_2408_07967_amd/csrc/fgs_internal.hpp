@@ -242,7 +242,8 @@ void launch_preprocess_multi(const DevScene &sc, const DevPrepared &pp, const Mu
 
 // View-independent precompute (opacity, 3D covariance, k^2, log2 opacity,
 // Gaussian-major SH) for options op (alpha_min and cap_3sigma), stored in
-// slot order: slot i holds Gaussian perm[i] (orig[i] = perm[i]).
+// slot order: slot i holds Gaussian perm[i] (orig[i] = perm[i]).  perm: P
+// words, followed by P words of scratch (its inverse).
 void launch_prepare(const DevScene &sc, const DevOptions &op, const uint32_t *perm, float4 *pos_o, float4 *cov,
                     float *sh, float2 *bnd, uint32_t *orig, int sh_stride, hipStream_t s);
 // Batch bounds of a prepared scene (DevPrepared::blk, 3 float4 per batch of

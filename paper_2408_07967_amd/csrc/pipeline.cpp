@@ -247,7 +247,8 @@ DevScene to_dev(const fgs_scene &s) {
     return d;
 }
 
-hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBuffers &pb, hipStream_t s) {
+hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBuffers &pb, hipStream_t s,
+                          SpareBlock *spare) {
     free_prepared(pb);
     const int64_t P = sc.num_gaussians;
     const int ncoef = 3 * (sc.sh_degree + 1) * (sc.sh_degree + 1);
@@ -255,26 +256,70 @@ hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBu
     pb.sh_stride = (ncoef + 3) / 4 * 4;
     const size_t n = (size_t)(P > 0 ? P : 1);
     hipError_t e;
-    if ((e = hipMalloc((void **)&pb.pos_o, n * sizeof(float4))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&pb.cov, 2 * n * sizeof(float4))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&pb.sh, n * (size_t)pb.sh_stride * sizeof(float))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&pb.bnd, n * sizeof(float2))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&pb.orig, n * sizeof(uint32_t))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&pb.blk, 3 * (pb.batches() > 0 ? pb.batches() : 1) * sizeof(float4))) != hipSuccess)
-        return e;
+    // 256-byte aligned parts of one block; base null: only their extent
+    auto carve = [](char *base, size_t &used, size_t bytes) -> void * {
+        void *const p = base ? base + used : nullptr;
+        used += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    auto lay_out = [&](char *base) {
+        size_t used = 0;
+        pb.pos_o = static_cast<float4 *>(carve(base, used, n * sizeof(float4)));
+        pb.cov = static_cast<float4 *>(carve(base, used, 2 * n * sizeof(float4)));
+        pb.sh = static_cast<float *>(carve(base, used, n * (size_t)pb.sh_stride * sizeof(float)));
+        pb.bnd = static_cast<float2 *>(carve(base, used, n * sizeof(float2)));
+        pb.orig = static_cast<uint32_t *>(carve(base, used, n * sizeof(uint32_t)));
+        pb.blk = static_cast<float4 *>(carve(base, used, 3 * (pb.batches() > 0 ? pb.batches() : 1) * sizeof(float4)));
+        return used;
+    };
+    const size_t need = lay_out(nullptr);
+    if (spare && spare->block && spare->bytes >= need && spare->bytes / 2 <= need) {
+        pb.block = spare->block;
+        pb.block_bytes = spare->bytes;
+        *spare = SpareBlock{};
+    } else {
+        e = hipMalloc(&pb.block, need);
+        if (e == hipErrorOutOfMemory && spare && spare->block) {
+            (void)hipGetLastError();
+            spare->drop();
+            e = hipMalloc(&pb.block, need);
+        }
+        if (e != hipSuccess) {
+            pb.block = nullptr;
+            return e;
+        }
+        pb.block_bytes = need;
+    }
+    lay_out(static_cast<char *>(pb.block));
     // Slot order: the Gaussians sorted by the Morton code of their means
     // (stable, so equal codes keep index order), so that the candidates of a
     // frame's cull, which see one region of the scene, occupy few contiguous
     // runs of slots and their precompute is read line by line.
     const DevScene dsc = to_dev(sc);
-    uint32_t *tmp = nullptr;  // keys a, keys b, values a, values b (n each), bounds (8)
+    // keys a and b, values a (and the inverse order behind them) and b, the
+    // box of the means, the sort's scratch
     SortScratch ss;
-    if ((e = hipMalloc((void **)&tmp, (4 * n + 8) * sizeof(uint32_t))) != hipSuccess) return e;
-    if ((e = ensure_sort_scratch(ss)) != hipSuccess) {
-        (void)hipFree(tmp);
-        return e;
+    uint32_t *ka = nullptr, *kb = nullptr, *va = nullptr, *vb = nullptr, *bounds = nullptr;
+    auto lay_out_tmp = [&](char *base) {
+        size_t used = 0;
+        ka = static_cast<uint32_t *>(carve(base, used, n * sizeof(uint32_t)));
+        kb = static_cast<uint32_t *>(carve(base, used, n * sizeof(uint32_t)));
+        va = static_cast<uint32_t *>(carve(base, used, 2 * n * sizeof(uint32_t)));
+        vb = static_cast<uint32_t *>(carve(base, used, n * sizeof(uint32_t)));
+        bounds = static_cast<uint32_t *>(carve(base, used, 8 * sizeof(uint32_t)));
+        ss.rhist = static_cast<uint32_t *>(carve(base, used, (size_t)kSortBlocks * kRadixMax * sizeof(uint32_t)));
+        ss.gsum = static_cast<uint32_t *>(carve(base, used, (size_t)kGsumSlots * kGsumWords * sizeof(uint32_t)));
+        return used;
+    };
+    void *tmp = nullptr;
+    e = hipMalloc(&tmp, lay_out_tmp(nullptr));
+    if (e == hipErrorOutOfMemory && spare && spare->block) {
+        (void)hipGetLastError();
+        spare->drop();
+        e = hipMalloc(&tmp, lay_out_tmp(nullptr));
     }
-    uint32_t *ka = tmp, *kb = tmp + n, *va = tmp + 2 * n, *vb = tmp + 3 * n, *bounds = tmp + 4 * n;
+    if (e != hipSuccess) return e;
+    lay_out_tmp(static_cast<char *>(tmp));
     const uint32_t P32 = (uint32_t)(P > 0 ? P : 0);
     launch_spatial_keys(dsc, bounds, ka, s);
     launch_fill_u32(ss.slot(0), 0u, (size_t)kGsumWords, s);
@@ -288,18 +333,27 @@ hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBu
     // the temporary buffers are read by the work just enqueued
     const hipError_t e2 = hipStreamSynchronize(s);
     (void)hipFree(tmp);
-    free_sort_scratch(ss);
     return e != hipSuccess ? e : e2;
 }
 
 void free_prepared(PreparedBuffers &pb) {
-    free_p(*(void **)&pb.orig);
-    free_p(*(void **)&pb.pos_o);
-    free_p(*(void **)&pb.cov);
-    free_p(*(void **)&pb.sh);
-    free_p(*(void **)&pb.bnd);
-    free_p(*(void **)&pb.blk);
+    free_p(pb.block);
     pb = PreparedBuffers{};
+}
+
+void SpareBlock::drop() {
+    free_p(block);
+    bytes = 0;
+}
+
+void SpareBlock::take(PreparedBuffers &pb) {
+    if (pb.block && pb.block_bytes <= kMax && pb.block_bytes >= bytes) {
+        drop();
+        block = pb.block;
+        bytes = pb.block_bytes;
+        pb.block = nullptr;
+    }
+    free_prepared(pb);
 }
 
 hipError_t SideStream::create() {

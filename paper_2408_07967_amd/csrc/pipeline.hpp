@@ -180,8 +180,11 @@ void enqueue_front_rest(bool dense, uint32_t P32, const DevOptions &op, int W, i
                         SortScratch &ss, FrameCounters *fc, FrameCounters *host_fc, hipStream_t s,
                         const SideStream &side, const StageMarks &mk, hipEvent_t counters_ready = nullptr);
 
-// Device buffers of a scene's view-independent precompute.
+// Device buffers of a scene's view-independent precompute: parts of one
+// allocation.
 struct PreparedBuffers {
+    void *block = nullptr;
+    size_t block_bytes = 0;
     float4 *pos_o = nullptr;
     float4 *cov = nullptr;
     float *sh = nullptr;
@@ -198,9 +201,23 @@ struct PreparedBuffers {
     DevPrepared dev() const { return DevPrepared{pos_o, cov, sh, bnd, orig, sh_stride, blk}; }
 };
 
-// Allocate and fill the precompute of sc for options op on stream s, in a
-// spatial slot order (Morton order of the means); waits for the stream.
-hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBuffers &pb, hipStream_t s);
+// At most one released precompute block, of at most kMax bytes, kept for the
+// next scene of about its size: allocating and freeing 0.25 GB takes 0.3 ms at
+// best and has taken 3 ms, as long as building a 1M-Gaussian precompute and
+// its first frame.  Holds no live data: nothing on the device uses it.
+struct SpareBlock {
+    static constexpr size_t kMax = (size_t)512 << 20;
+    void *block = nullptr;
+    size_t bytes = 0;
+    void drop();                  // free it
+    void take(PreparedBuffers &pb);  // keep pb's block if it may be kept, else free it; empties pb
+};
+
+// Allocate (or take from spare, which may be NULL) and fill the precompute of
+// sc for options op on stream s, in a spatial slot order (Morton order of the
+// means); waits for the stream.
+hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBuffers &pb, hipStream_t s,
+                          SpareBlock *spare = nullptr);
 void free_prepared(PreparedBuffers &pb);
 
 // Stages 2b to 4: key emission (super-tile entries), their stable sort by
