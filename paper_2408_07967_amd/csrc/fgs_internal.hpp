@@ -78,8 +78,10 @@ struct alignas(16) GaussState {
     float4 f0, f1, f2;
 };
 
-// Frame-scoped device counters, cleared at the start of a frame.
-struct FrameCounters {
+// Frame-scoped device counters, cleared at the start of a frame (visible and
+// pairs are added to as one 64-bit word; a line of its own, so that the
+// cameras of a batch do not wait for each other's atomics).
+struct alignas(128) FrameCounters {
     uint32_t visible;  // Gaussians that passed preprocessing
     uint32_t pairs;    // total (Gaussian, tile) pairs: the preprocess adds the small rectangles' hits, the
                        // large-rectangle tests theirs
