@@ -142,26 +142,52 @@ __device__ __forceinline__ void tile_row_terms(float v, float A, float B, float 
 }
 
 // One edge: the chord [r-, r+] of the quadratic with discriminant d overlaps
-// the edge segment, given e1 = 2a s0 + bq and e2 = 2a s1 + bq at its ends.
+// the edge segment, given e1 = 2a s0 + bq and e2 = 2a s1 + bq at its ends:
+//   d >= 0 and (e1 <= 0 or e1^2 <= d) and (e2 >= 0 or e2^2 <= d).
 // (Bitwise, not short-circuit, so that the test compiles to straight-line
 // code.)
 __device__ __forceinline__ bool edge_hit(float e1, float e2, float d) {
     return (d >= 0.0f) & ((e1 <= 0.0f) | (e1 * e1 <= d)) & ((e2 >= 0.0f) | (e2 * e2 <= d));
 }
 
-__device__ __forceinline__ bool tile_hit_terms(const float4 ca, const float4 cb, const float4 ra, const float4 rb) {
-    const bool inside = (cb.z != 0.0f) & (rb.z != 0.0f);  // centre inside the hull
-    // horizontal edges y = y0, y1, then vertical edges x = x0, x1
-    return inside | edge_hit(ca.x + ra.x, ca.y + ra.x, ra.y) | edge_hit(ca.x + ra.z, ca.y + ra.z, ra.w) |
-           edge_hit(rb.x + ca.z, rb.y + ca.z, ca.w) | edge_hit(rb.x + cb.x, rb.y + cb.x, cb.y);
+// The same decision for finite e1 and e2 in three instructions instead of
+// seven: the conditions bind only for e1 > 0 and e2 < 0, rounded squares keep
+// their order, and 0 <= d is the third condition's case of neither, so they
+// hold exactly when the square of max(e1, -e2, 0) is at most d (a NaN d fails
+// both ways).
+__device__ __forceinline__ bool edge_hit_finite(float e1, float e2, float d) {
+    const float m = __builtin_fmaxf(__builtin_fmaxf(e1, -e2), 0.0f);
+    return m * m <= d;
 }
 
+// Whether every term of a Gaussian's tile tests is finite: all products of
+// the conic and two coordinates (hulls lie within 2^14) stay below 1e37.
+__device__ __forceinline__ bool tile_terms_finite(float u, float v, float A, float B, float C) {
+    return (fabsf(u) < 1e9f) & (fabsf(v) < 1e9f) & (fabsf(A) < 1e9f) & (fabsf(B) < 1e9f) & (fabsf(C) < 1e9f);
+}
+
+// kFinite: the terms are finite (tile_terms_finite)
+template <bool kFinite>
+__device__ __forceinline__ bool tile_hit_terms(const float4 ca, const float4 cb, const float4 ra, const float4 rb) {
+    const bool inside = (cb.z != 0.0f) & (rb.z != 0.0f);  // centre inside the hull
+    auto edge = [](float e1, float e2, float d) {
+        if constexpr (kFinite)
+            return edge_hit_finite(e1, e2, d);
+        else
+            return edge_hit(e1, e2, d);
+    };
+    // horizontal edges y = y0, y1, then vertical edges x = x0, x1
+    return inside | edge(ca.x + ra.x, ca.y + ra.x, ra.y) | edge(ca.x + ra.z, ca.y + ra.z, ra.w) |
+           edge(rb.x + ca.z, rb.y + ca.z, ca.w) | edge(rb.x + cb.x, rb.y + cb.x, cb.y);
+}
+
+template <bool kFinite>
 __device__ __forceinline__ bool tile_hit(float u, float v, float A, float B, float C, float k2, int tx, int ty,
                                          int W, int H) {
     float4 ca, cb, ra, rb;
     tile_col_terms(u, A, B, C, k2, tx, W, ca, cb);
     tile_row_terms(v, A, B, C, k2, ty, H, ra, rb);
-    return tile_hit_terms(ca, cb, ra, rb);
+    return tile_hit_terms<kFinite>(ca, cb, ra, rb);
 }
 
 // Row and column of row-major position idx in rows of ntx (idx < 2^24,
@@ -1211,6 +1237,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         sx[lane] = incl - items;
         s_mlo[wave][lane] = 0u;
         s_mhi[wave][lane] = 0u;
+        // (the wavefront's Gaussians are all finite but for adversarial input)
+        const bool finite = __ballot(small && !tile_terms_finite(u, v, A, B, C)) == 0;
         for (uint32_t b0 = 0; b0 < total; b0 += kWave) {
             const uint32_t item = b0 + (uint32_t)lane;
             const int L = owner_lane(sx, item < total ? item : total - 1u);
@@ -1220,7 +1248,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const int stx0 = __shfl(tx0, L, kWave), sty0 = __shfl(ty0, L, kWave), sntx = __shfl(ntx, L, kWave);
             if (item < total) {
                 const int ry = small_div(k, sntx), rx = (int)k - ry * sntx;
-                if (tile_hit(su, sv, sA, sB, sC, sk2, stx0 + rx, sty0 + ry, W, H))
+                if (finite ? tile_hit<true>(su, sv, sA, sB, sC, sk2, stx0 + rx, sty0 + ry, W, H)
+                           : tile_hit<false>(su, sv, sA, sB, sC, sk2, stx0 + rx, sty0 + ry, W, H))
                     atomicOr(k < 32u ? &s_mlo[wave][L] : &s_mhi[wave][L], 1u << (k & 31u));
             }
         }
@@ -1615,7 +1644,7 @@ __global__ __launch_bounds__(kBlock) void k_big_count(int W, int H, int binning,
                 int ry_a, rx_a, ry_b, rx_b;
                 row_col(i0, ntx, rcpn, ry_a, rx_a);
                 row_col(i1, ntx, rcpn, ry_b, rx_b);
-                const bool rows = binning == 0 && ry_b - ry_a < kWave;
+                const bool rows = binning == 0 && ry_b - ry_a < kWave && tile_terms_finite(u, v, A, B, C);
                 if (rows) {
                     wave_sync();  // every lane has read the previous chunk's terms
                     if (lane <= ry_b - ry_a) {
@@ -1637,9 +1666,9 @@ __global__ __launch_bounds__(kBlock) void k_big_count(int W, int H, int binning,
                         if (rows) {
                             float4 ca, cb;
                             tile_col_terms(u, A, B, C, k2, tx0 + rx, W, ca, cb);
-                            h = tile_hit_terms(ca, cb, s_ra[wv][ry - ry_a], s_rb[wv][ry - ry_a]);
+                            h = tile_hit_terms<true>(ca, cb, s_ra[wv][ry - ry_a], s_rb[wv][ry - ry_a]);
                         } else {
-                            h = binning != 0 || tile_hit(u, v, A, B, C, k2, tx0 + rx, ty0 + ry, W, H);
+                            h = binning != 0 || tile_hit<false>(u, v, A, B, C, k2, tx0 + rx, ty0 + ry, W, H);
                         }
                     }
                     bw[q] = __ballot(h);
