@@ -11,6 +11,7 @@
 
 #include "fgs_internal.hpp"
 #include "sh_basis.hpp"
+#include "tile_test.hpp"
 
 namespace fgs {
 namespace {
@@ -87,107 +88,6 @@ __device__ double canon_log(double x) {
 
 __device__ __forceinline__ float clampf_(float x, float lo, float hi) {
     return x < lo ? lo : (x > hi ? hi : x);
-}
-
-__device__ __forceinline__ float bcast(float x, int lane) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
-}
-__device__ __forceinline__ int bcast(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
-__device__ __forceinline__ uint32_t bcast(uint32_t x, int lane) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
-}
-
-// Exact test of the ellipse { d : A dx^2 + 2 B dx dy + C dy^2 <= k2 } around
-// (u, v) against the pixel-sample hull of tile (tx, ty) (Alg. 3; Eq. 7 with
-// the discriminant guard).  Centre inside -> hit; otherwise each edge line
-// meets the ellipse in a chord whose overlap with the edge segment is decided
-// without division or square root.
-//
-// The test splits into terms of the tile's column alone and of its row alone,
-// so that the tiles of one rectangle can share them; tile_hit is the two
-// halves combined, with the same binary32 operations in the same order.
-//
-// Column terms (hull x-range [x0, x1] relative to u):
-//   a = (2A x0, 2A x1, bq(x0), delta(x0)), b = (bq(x1), delta(x1), flag, 0)
-// with bq(x) = 2B x and delta(x) = bq^2 - 4C (A x^2 - k2) for the vertical
-// edge at x (quadratic in y), and flag = 1 if x0 <= 0 <= x1.
-__device__ __forceinline__ void tile_col_terms(float u, float A, float B, float C, float k2, int tx, int W,
-                                               float4 &a, float4 &b) {
-    int xe = kTile * tx + kTile;
-    xe = xe > W ? W : xe;
-    const float x0 = ((float)(kTile * tx) + 0.5f) - u;
-    const float x1 = ((float)xe - 0.5f) - u;
-    const float A2 = 2.0f * A, B2 = 2.0f * B, C4 = 4.0f * C;
-    const float bq0 = B2 * x0, bq1 = B2 * x1;
-    const float cq0 = (A * x0) * x0 - k2, cq1 = (A * x1) * x1 - k2;
-    a = make_float4(A2 * x0, A2 * x1, bq0, bq0 * bq0 - C4 * cq0);
-    b = make_float4(bq1, bq1 * bq1 - C4 * cq1, (x0 <= 0.0f && 0.0f <= x1) ? 1.0f : 0.0f, 0.0f);
-}
-
-// Row terms (hull y-range [y0, y1] relative to v):
-//   a = (bq(y0), delta(y0), bq(y1), delta(y1)), b = (2C y0, 2C y1, flag, 0)
-// with bq(y) = 2B y and delta(y) = bq^2 - 4A (C y^2 - k2) for the horizontal
-// edge at y (quadratic in x), and flag = 1 if y0 <= 0 <= y1.
-__device__ __forceinline__ void tile_row_terms(float v, float A, float B, float C, float k2, int ty, int H,
-                                               float4 &a, float4 &b) {
-    int ye = kTile * ty + kTile;
-    ye = ye > H ? H : ye;
-    const float y0 = ((float)(kTile * ty) + 0.5f) - v;
-    const float y1 = ((float)ye - 0.5f) - v;
-    const float B2 = 2.0f * B, C2 = 2.0f * C, A4 = 4.0f * A;
-    const float bq0 = B2 * y0, bq1 = B2 * y1;
-    const float cq0 = (C * y0) * y0 - k2, cq1 = (C * y1) * y1 - k2;
-    a = make_float4(bq0, bq0 * bq0 - A4 * cq0, bq1, bq1 * bq1 - A4 * cq1);
-    b = make_float4(C2 * y0, C2 * y1, (y0 <= 0.0f && 0.0f <= y1) ? 1.0f : 0.0f, 0.0f);
-}
-
-// One edge: the chord [r-, r+] of the quadratic with discriminant d overlaps
-// the edge segment, given e1 = 2a s0 + bq and e2 = 2a s1 + bq at its ends:
-//   d >= 0 and (e1 <= 0 or e1^2 <= d) and (e2 >= 0 or e2^2 <= d).
-// (Bitwise, not short-circuit, so that the test compiles to straight-line
-// code.)
-__device__ __forceinline__ bool edge_hit(float e1, float e2, float d) {
-    return (d >= 0.0f) & ((e1 <= 0.0f) | (e1 * e1 <= d)) & ((e2 >= 0.0f) | (e2 * e2 <= d));
-}
-
-// The same decision for finite e1 and e2 in three instructions instead of
-// seven: the conditions bind only for e1 > 0 and e2 < 0, rounded squares keep
-// their order, and 0 <= d is the third condition's case of neither, so they
-// hold exactly when the square of max(e1, -e2, 0) is at most d (a NaN d fails
-// both ways).
-__device__ __forceinline__ bool edge_hit_finite(float e1, float e2, float d) {
-    const float m = __builtin_fmaxf(__builtin_fmaxf(e1, -e2), 0.0f);
-    return m * m <= d;
-}
-
-// Whether every term of a Gaussian's tile tests is finite: all products of
-// the conic and two coordinates (hulls lie within 2^14) stay below 1e37.
-__device__ __forceinline__ bool tile_terms_finite(float u, float v, float A, float B, float C) {
-    return (fabsf(u) < 1e9f) & (fabsf(v) < 1e9f) & (fabsf(A) < 1e9f) & (fabsf(B) < 1e9f) & (fabsf(C) < 1e9f);
-}
-
-// kFinite: the terms are finite (tile_terms_finite)
-template <bool kFinite>
-__device__ __forceinline__ bool tile_hit_terms(const float4 ca, const float4 cb, const float4 ra, const float4 rb) {
-    const bool inside = (cb.z != 0.0f) & (rb.z != 0.0f);  // centre inside the hull
-    auto edge = [](float e1, float e2, float d) {
-        if constexpr (kFinite)
-            return edge_hit_finite(e1, e2, d);
-        else
-            return edge_hit(e1, e2, d);
-    };
-    // horizontal edges y = y0, y1, then vertical edges x = x0, x1
-    return inside | edge(ca.x + ra.x, ca.y + ra.x, ra.y) | edge(ca.x + ra.z, ca.y + ra.z, ra.w) |
-           edge(rb.x + ca.z, rb.y + ca.z, ca.w) | edge(rb.x + cb.x, rb.y + cb.x, cb.y);
-}
-
-template <bool kFinite>
-__device__ __forceinline__ bool tile_hit(float u, float v, float A, float B, float C, float k2, int tx, int ty,
-                                         int W, int H) {
-    float4 ca, cb, ra, rb;
-    tile_col_terms(u, A, B, C, k2, tx, W, ca, cb);
-    tile_row_terms(v, A, B, C, k2, ty, H, ra, rb);
-    return tile_hit_terms<kFinite>(ca, cb, ra, rb);
 }
 
 // Row and column of row-major position idx in rows of ntx (idx < 2^24,
@@ -1574,31 +1474,41 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Exact tile tests of the chunked Gaussians.  A wavefront takes 64
-// consecutive chunk slots: every lane loads one slot's descriptor and then
-// its Gaussian's rectangle, centre, conic and k^2, so that the 64 chunks cost
-// two memory round trips together; the chunks are then tested one after the
-// other with their values read from the owning lane (kChunkTiles tiles, 4
-// per lane, independent).  A chunk covers few tile rows, whose terms of the
-// test (tile_row_terms) are computed once per row into LDS; each tile adds
-// its column's terms and combines them (tile_hit_terms: the operations of
-// tile_hit).  The 8 mask words of a chunk are written by four
-// lanes, and the hits of a Gaussian's consecutive chunks are summed across
-// the lanes before one atomic per Gaussian and wavefront.  A workgroup adds
-// its hits to the frame's pair count once.  (With 64 slots per wavefront the
-// kernel runs as fewer, longer wavefronts, which leaves the depth sort
-// beside it more of each CU than one chunk per wavefront did.)
+// Exact tile tests of the chunked Gaussians, row by row.  A wavefront takes up
+// to 64 consecutive chunk slots: every lane loads one slot's descriptor and
+// then its Gaussian's rectangle, centre, conic and k^2, so that they cost two
+// memory round trips together, and leaves them with the row intervals' terms
+// in LDS.  The rows of all its chunks are then flattened over the lanes, one
+// (chunk, row) each: the row's columns that can be hit and those that
+// certainly are follow from two intervals (tile_test.hpp); the few between
+// them take the exact test, and the hits are runs of bits set in the chunk's
+// mask in LDS.  The masks are written out together, and the hits of a
+// Gaussian's consecutive chunks are summed across the lanes before one atomic
+// per Gaussian and wavefront; a workgroup adds its hits to the frame's pair
+// count once.
+// Bound by VALU and LDS latency (about 300 instructions per step of 64 rows).
+// One exact test per tile (60 instructions each) took 182 us beside the depth
+// sort for the 10M city at 4K (205k chunks) and 440 us at 8K (873k), and held
+// the sort's wavefronts back; the rows take 72 and 164 us, and a list of 83
+// chunks 11 us instead of 73.
 __global__ __launch_bounds__(kBlock) void k_big_count(int W, int H, int binning, const GaussState *__restrict__ gs,
                                                       const float4 *__restrict__ conic,
                                                       const uint4 *__restrict__ erec,
                                                       const uint2 *__restrict__ chunks, uint32_t chunk_cap,
                                                       uint32_t *__restrict__ chunk_mask, uint32_t *count,
                                                       FrameCounters *fc) {
-    constexpr int kPer = kChunkTiles / kWave;
-    static_assert(kPer == 4, "a chunk's mask is written as four 64-bit words");
+    constexpr int kWords = kChunkTiles / 32;  // mask words of a chunk
+    static_assert(kWords == 8, "a chunk's mask is two 16-byte words");
     __shared__ uint32_t s_hits[kBlock / kWave];
-    // the row terms of the chunk being tested (one lane per row)
-    __shared__ float4 s_ra[kBlock / kWave][kWave], s_rb[kBlock / kWave][kWave];
+    struct alignas(16) Slot {
+        float u, v, A, B, C, k2;
+        RowTest rt;
+        uint32_t cols, rows, first, i0;  // tx0 | ntx << 16, ty0 | (last tile - i0) << 16, first row, first tile
+    };
+    static_assert(sizeof(Slot) == 64, "four 16-byte reads");
+    __shared__ Slot s_slot[kBlock / kWave][kWave];
+    __shared__ alignas(16) uint32_t s_mask[kBlock / kWave][kWave * kWords];
+    __shared__ uint32_t s_excl[kBlock / kWave][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x / kWave;
     uint32_t whits = 0;  // wave-uniform
@@ -1607,83 +1517,131 @@ __global__ __launch_bounds__(kBlock) void k_big_count(int W, int H, int binning,
     if (!(fc->error & kErrChunkOverflow)) {
         const uint32_t n = fc->nchunks < chunk_cap ? fc->nchunks : chunk_cap;
         const uint32_t nwaves = gridDim.x * (kBlock / kWave);
-        uint64_t *const mask64 = reinterpret_cast<uint64_t *>(chunk_mask);
-        for (uint32_t c0 = (blockIdx.x * (kBlock / kWave) + (uint32_t)wv) * kWave; c0 < n; c0 += nwaves * kWave) {
+        // chunks per wavefront: as many as spread the list over the grid
+        // (which is resident at once), one per lane at most
+        const uint32_t share = (n + nwaves - 1u) / nwaves, per = share < (uint32_t)kWave ? share : (uint32_t)kWave;
+        uint32_t *const sx = s_excl[wv];
+        uint32_t *const sm = s_mask[wv];
+        for (uint32_t c0 = (blockIdx.x * (kBlock / kWave) + (uint32_t)wv) * per; c0 < n; c0 += nwaves * per) {
             const uint32_t c = c0 + (uint32_t)lane;
             uint2 e = make_uint2(kNoChunk, 0u);
-            if (c < n) e = chunks[c];
+            if ((uint32_t)lane < per && c < n) e = chunks[c];
             const bool have = e.x != kNoChunk;
-            // this lane's chunk: its Gaussian's record, centre, k^2 and conic
-            uint4 rr = make_uint4(0u, 0u, 0u, 0u);
-            float4 f0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), f1 = f0, cn = f0;
+            uint32_t items = 0;
+            bool slow = false;  // no intervals (a needle, or terms that may overflow): every tile is tested
             if (have) {
-                rr = erec[e.x];
+                const uint4 rr = erec[e.x];
+                Slot sl;
+                float4 f0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), f1 = f0, cn = f0;
                 if (binning == 0) {
                     const float4 *sp = reinterpret_cast<const float4 *>(gs + e.x);
                     f0 = sp[0];
                     f1 = sp[1];
                     cn = conic[e.x];
                 }
-            }
-            const uint32_t cidx = have ? c - e.y : 0u;  // chunk within its Gaussian
-            uint32_t my_hits = 0;
-            uint64_t todo = __ballot(have);
-            while (todo) {
-                const int j = __builtin_ctzll(todo);
-                todo &= todo - 1ull;
-                const uint32_t px = bcast(rr.x, j), py = bcast(rr.y, j), cc = bcast(cidx, j);
-                const float u = bcast(f0.x, j), v = bcast(f0.y, j), k2 = bcast(f1.y, j);
-                const float A = bcast(cn.x, j), B = bcast(cn.y, j), C = bcast(cn.z, j);
-                const int tx0 = (int)(px & 0xffffu), ntx = (int)(px >> 16) - tx0 + 1;
-                const int ty0 = (int)(py & 0xffffu), nt = ntx * ((int)(py >> 16) - ty0 + 1);
-                const float rcpn = __builtin_amdgcn_rcpf((float)ntx);
-                // the chunk's rows: their terms once each (a chunk over more
-                // rows than a wavefront has lanes tests tile by tile)
-                const int i0 = (int)cc * kChunkTiles;
+                sl.u = f0.x;
+                sl.v = f0.y;
+                sl.A = cn.x;
+                sl.B = cn.y;
+                sl.C = cn.z;
+                sl.k2 = f1.y;
+                sl.rt = row_test(sl.u, sl.v, sl.A, sl.B, sl.C, sl.k2);
+                const int tx0 = (int)(rr.x & 0xffffu), ntx = (int)(rr.x >> 16) - tx0 + 1;
+                const int ty0 = (int)(rr.y & 0xffffu), nt = ntx * ((int)(rr.y >> 16) - ty0 + 1);
+                const int i0 = (int)(c - e.y) * kChunkTiles;
                 const int i1 = (i0 + kChunkTiles < nt ? i0 + kChunkTiles : nt) - 1;
-                int ry_a, rx_a, ry_b, rx_b;
-                row_col(i0, ntx, rcpn, ry_a, rx_a);
-                row_col(i1, ntx, rcpn, ry_b, rx_b);
-                const bool rows = binning == 0 && ry_b - ry_a < kWave && tile_terms_finite(u, v, A, B, C);
-                if (rows) {
-                    wave_sync();  // every lane has read the previous chunk's terms
-                    if (lane <= ry_b - ry_a) {
-                        float4 ra, rb;
-                        tile_row_terms(v, A, B, C, k2, ty0 + ry_a + lane, H, ra, rb);
-                        s_ra[wv][lane] = ra;
-                        s_rb[wv][lane] = rb;
-                    }
-                    wave_sync();
-                }
-                uint64_t bw[kPer];
+                const float rcpn = __builtin_amdgcn_rcpf((float)ntx);
+                int ra, rb, x;
+                row_col(i0, ntx, rcpn, ra, x);
+                row_col(i1, ntx, rcpn, rb, x);
+                items = binning != 0 || sl.rt.fo > 0.0f ? (uint32_t)(rb - ra + 1) : 0u;
+                slow = items == 0;
+                sl.cols = (uint32_t)tx0 | ((uint32_t)ntx << 16);
+                sl.rows = (uint32_t)ty0 | ((uint32_t)(i1 - i0) << 16);
+                sl.first = (uint32_t)ra;
+                sl.i0 = (uint32_t)i0;
+                s_slot[wv][lane] = sl;
+            }
 #pragma unroll
-                for (int q = 0; q < kPer; ++q) {
-                    const int idx = i0 + q * kWave + lane;
-                    bool h = false;
-                    if (idx < nt) {
-                        int ry, rx;
-                        row_col(idx, ntx, rcpn, ry, rx);
-                        if (rows) {
-                            float4 ca, cb;
-                            tile_col_terms(u, A, B, C, k2, tx0 + rx, W, ca, cb);
-                            h = tile_hit_terms<true>(ca, cb, s_ra[wv][ry - ry_a], s_rb[wv][ry - ry_a]);
-                        } else {
-                            h = binning != 0 || tile_hit<false>(u, v, A, B, C, k2, tx0 + rx, ty0 + ry, W, H);
-                        }
+            for (int k = 0; k < kWords / 4; ++k)
+                reinterpret_cast<uint4 *>(sm)[lane * (kWords / 4) + k] = make_uint4(0u, 0u, 0u, 0u);
+            const uint32_t incl_i = wave_incl_scan(items, lane);
+            const uint32_t total = (uint32_t)__shfl((int)incl_i, kWave - 1, kWave);
+            sx[lane] = incl_i - items;
+            wave_sync();
+            for (uint32_t t0 = 0; t0 < total; t0 += kWave) {
+                const uint32_t item = t0 + (uint32_t)lane;
+                if (item >= total) continue;
+                const int L = owner_lane(sx, item);
+                const Slot sl = s_slot[wv][L];
+                const int row = (int)(sl.first + (item - sx[L]));
+                const int tx0 = (int)(sl.cols & 0xffffu), ntx = (int)(sl.cols >> 16);
+                const int ty = (int)(sl.rows & 0xffffu) + row;
+                // the chunk's tiles of this row, as columns
+                const int base = row * ntx - (int)sl.i0;  // bit of the row's column 0 in the chunk
+                const int last = (int)(sl.rows >> 16);
+                const int ca = base < 0 ? -base : 0, cb = base + ntx - 1 > last ? last - base : ntx - 1;
+                RowCols rc{tx0 + ca, tx0 + cb, tx0 + ca, tx0 + cb};
+                if (binning == 0) {
+                    float y0, y1;
+                    tile_row_span(sl.v, ty, H, y0, y1);
+                    rc = row_columns(sl.rt, sl.u, y0, y1, tx0 + ca, tx0 + cb, W);
+                }
+                uint32_t *const m = sm + L * kWords;
+                auto set_run = [&](int a, int b) {  // bits a..b of the chunk
+                    for (int w = a >> 5; w <= b >> 5; ++w) {
+                        const int lo = a - 32 * w > 0 ? a - 32 * w : 0, hi = b - 32 * w < 31 ? b - 32 * w : 31;
+                        atomicOr(&m[w], (~0u << lo) & (~0u >> (31 - hi)));
                     }
-                    bw[q] = __ballot(h);
+                };
+                const bool sure = rc.sure_first <= rc.sure_last;
+                if (sure) set_run(base + rc.sure_first - tx0, base + rc.sure_last - tx0);
+                // undecided columns: before the certain run and after it (all
+                // that can be hit if there is none)
+                const int before = (sure ? rc.sure_first : rc.last + 1) - rc.first;
+                const int after = sure ? rc.last - rc.sure_last : 0;
+                for (int k = 0; k < before + after; ++k) {
+                    const int tx = k < before ? rc.first + k : rc.sure_last + 1 + (k - before);
+                    if (tile_hit<true>(sl.u, sl.v, sl.A, sl.B, sl.C, sl.k2, tx, ty, W, H)) {
+                        const int b = base + tx - tx0;
+                        atomicOr(&m[b >> 5], 1u << (b & 31));
+                    }
                 }
-                const uint32_t tot = (uint32_t)(__popcll(bw[0]) + __popcll(bw[1]) + __popcll(bw[2]) + __popcll(bw[3]));
-                if (lane < kPer) {
-                    const uint64_t w = lane == 0 ? bw[0] : lane == 1 ? bw[1] : lane == 2 ? bw[2] : bw[3];
-                    mask64[(size_t)(c0 + (uint32_t)j) * kPer + (uint32_t)lane] = w;
+            }
+            // chunks without intervals: their tiles over the lanes
+            for (uint64_t todo = __ballot(slow); todo; todo &= todo - 1ull) {
+                const int L = __builtin_ctzll(todo);
+                const Slot sl = s_slot[wv][L];
+                const int tx0 = (int)(sl.cols & 0xffffu), ntx = (int)(sl.cols >> 16), ty0 = (int)(sl.rows & 0xffffu);
+                const int n_tiles = (int)(sl.rows >> 16) + 1;
+                const float rcpn = __builtin_amdgcn_rcpf((float)ntx);
+#pragma unroll
+                for (int q = 0; q < kChunkTiles / kWave; ++q) {
+                    bool h = false;
+                    if (q * kWave + lane < n_tiles) {
+                        int ry, rx;
+                        row_col((int)sl.i0 + q * kWave + lane, ntx, rcpn, ry, rx);
+                        h = tile_hit<false>(sl.u, sl.v, sl.A, sl.B, sl.C, sl.k2, tx0 + rx, ty0 + ry, W, H);
+                    }
+                    const uint64_t bal = __ballot(h);
+                    if (lane < 2) sm[L * kWords + 2 * q + lane] = lane ? (uint32_t)(bal >> 32) : (uint32_t)bal;
                 }
-                my_hits = lane == j ? tot : my_hits;
-                whits += tot;
+            }
+            wave_sync();
+            // this lane's chunk: its mask's hits, and the mask
+            const uint4 m0 = reinterpret_cast<const uint4 *>(sm)[lane * 2], m1 = reinterpret_cast<const uint4 *>(sm)[lane * 2 + 1];
+            const uint32_t my_hits =
+                (uint32_t)(__popc(m0.x) + __popc(m0.y) + __popc(m0.z) + __popc(m0.w) + __popc(m1.x) + __popc(m1.y) +
+                           __popc(m1.z) + __popc(m1.w));
+            if (have) {
+                uint4 *const dst = reinterpret_cast<uint4 *>(chunk_mask + (size_t)c * kWords);
+                dst[0] = m0;
+                dst[1] = m1;
             }
             // one atomic per run of lanes holding chunks of the same Gaussian
             // (a Gaussian's chunks are consecutive slots)
             const uint32_t incl = wave_incl_scan(my_hits, lane);
+            whits += (uint32_t)__shfl((int)incl, kWave - 1, kWave);
             const uint32_t gprev = (uint32_t)__shfl_up((int)e.x, 1, kWave);
             const uint32_t gnext = (uint32_t)__shfl_down((int)e.x, 1, kWave);
             const bool head = lane == 0 || gprev != e.x;
@@ -1694,6 +1652,7 @@ __global__ __launch_bounds__(kBlock) void k_big_count(int W, int H, int binning,
             const uint32_t before = (uint32_t)__shfl((int)incl, first > 0 ? first - 1 : 0, kWave);
             const uint32_t run = incl - (first > 0 ? before : 0u);
             if (have && tail && run) atomicAdd(&count[e.x], run);
+            wave_sync();  // every lane has read the masks before they are cleared
         }
     }
     if (lane == 0) s_hits[wv] = whits;
@@ -1799,7 +1758,8 @@ void launch_big_count(int W, int H, int binning, const GaussState *gs, const flo
                       const uint2 *chunks, uint32_t chunk_cap, uint32_t *chunk_mask, uint32_t *count,
                       FrameCounters *fc, hipStream_t s) {
     if (chunk_cap == 0) return;
-    hipLaunchKernelGGL(k_big_count, dim3(kPersistentBlocks), dim3(kBlock), 0, s, W, H, binning, gs, conic, erec,
+    static const unsigned grid = resident_blocks(k_big_count);
+    hipLaunchKernelGGL(k_big_count, dim3(grid), dim3(kBlock), 0, s, W, H, binning, gs, conic, erec,
                        chunks, chunk_cap, chunk_mask, count, fc);
 }
 
