@@ -89,9 +89,13 @@ struct alignas(128) FrameCounters {
     uint32_t nchunks;  // entries requested in the large-Gaussian chunk list
     uint32_t ncand;    // candidates of a prepared scene's cull (dense depth keys)
     uint32_t nlong;    // runs of more than kShortTieRun equal depths (prepared scene)
-    uint32_t entries;  // (Gaussian, super-tile) entries (written by the count scan)
     uint32_t cull_read;  // batches of kBlock slots a prepared scene's cull read (the others its
                          // batch bounds skipped; written by the preprocess)
+    // (Gaussian, super-tile) entries: added up by the preprocess, so that the
+    // host's copy need not wait for the depth order (the count scan writes the
+    // same total).  On a line of its own: its atomics and those above do not
+    // wait for each other.
+    alignas(128) uint32_t entries;
 };
 
 // Super-tiles: blocks of kSuper x kSuper tiles (the last row and column may be
@@ -303,7 +307,9 @@ __host__ __device__ inline uint32_t super_span(int tx0, int tx1, int ty0, int ty
 // slots).  Entries at or beyond ecap are dropped (the host sees the count
 // and renders again).  Also sets the super-tile ranges empty, (0xffffffff,
 // 0) for s < nsuper, and clears the first sort pass's group sums
-// (gsum_clear, kGsumWords words).
+// (gsum_clear, kGsumWords words).  chunk_mask NULL: without the chunked
+// Gaussians' entries; order NULL: only those (so that only they wait for
+// their tests).
 void launch_super_emit(int W, int H, const uint32_t *order, uint32_t visible, const uint32_t *visible_dev,
                        const uint32_t *offsets, const uint4 *erec, uint32_t ng, const uint2 *chunks, uint2 *big,
                        const uint32_t *chunk_mask, uint32_t chunk_cap, const FrameCounters *fc, uint16_t *skey,

@@ -683,18 +683,44 @@ __global__ __launch_bounds__(kBlock) void k_cull(DevScene sc, DevPrepared pp, De
 // arguments are then unused); the repeated reads of a Gaussian's precompute
 // for the second and later cameras follow the first within the same
 // wavefront and hit the caches.
+//
+// The arguments are one struct, read through the kernel-argument pointer,
+// which every batch takes anew: held in scalar registers across the batch
+// loop, the camera in both precisions and thirty pointers spill to vector
+// registers' lanes (280 of them from raw parameters), and those to memory.
+struct PreArgs {
+    DevScene sc;
+    DevPrepared pp;
+    DevCamera cam;
+    DevCam64 cam64;
+    DevOptions op;
+    int W, H;
+    GaussState *gs;
+    float4 *conic;
+    uint4 *rect;
+    uint32_t *count;
+    uint8_t *count8;
+    uint4 *erec;
+    uint32_t *dkey;
+    const uint32_t *cand, *seg_count;
+    uint32_t *gmap;
+    uint2 *chunks;
+    uint32_t chunk_cap;
+    FrameCounters *fc;
+    uint32_t *gsum_clear;
+    int full;
+    MultiOut mo;
+};
 template <bool kPrep, bool kMulti = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_preprocess(DevScene sc, DevPrepared pp, DevCamera cam, DevCam64 cam64, DevOptions op,
-                                                       int W_arg, int H_arg, GaussState *__restrict__ gs,
-                                                       float4 *__restrict__ conic,
-                                                       uint4 *__restrict__ rect, uint32_t *__restrict__ count,
-                                                       uint8_t *__restrict__ count8, uint4 *__restrict__ erec,
-                                                       uint32_t *__restrict__ dkey,
-                                                       const uint32_t *__restrict__ cand,
-                                                       const uint32_t *__restrict__ seg_count,
-                                                       uint32_t *__restrict__ gmap, uint2 *__restrict__ chunks,
-                                                       uint32_t chunk_cap, FrameCounters *fc,
-                                                       uint32_t *__restrict__ gsum_clear, int full, MultiOut mo) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_preprocess(PreArgs args_in_place) {
+    (void)args_in_place;
+    typedef const __attribute__((address_space(4))) PreArgs *ArgPtr;
+    const ArgPtr arg_ptr = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const PreArgs &args = *(const PreArgs *)arg_ptr;
+    const MultiOut &mo = args.mo;
+    const uint32_t *const seg_count = args.seg_count;
+    uint32_t *const gsum_clear = args.gsum_clear;
+    const int64_t P = args.sc.P;
     static_assert(!kMulti || kPrep, "a batch walks a union candidate list");
     // the first depth pass's group sums start at zero
     if constexpr (kMulti) {
@@ -715,10 +741,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ uint32_t s_excl[kBlock / kWave][kWave], s_mlo[kBlock / kWave][kWave], s_mhi[kBlock / kWave][kWave];
     const int wv = threadIdx.x / kWave;  // this lane's wavefront
     uint32_t w_nbig = 0, w_nch = 0;      // wave-uniform: pending entries and their chunks
-    uint32_t w_vis = 0;                  // wave-uniform: visible Gaussians so far
-    uint32_t l_pairs = 0;                // this lane's small-rectangle hits so far
-    __shared__ uint32_t s_vis[kBlock / kWave][kMulti ? kMaxCams : 1];  // per camera (kMulti)
+    // visible Gaussians, small-rectangle hits and super-tile entries so far (per
+    // camera; in LDS: the kernel has no register to spare)
+    __shared__ uint32_t s_vis[kBlock / kWave][kMulti ? kMaxCams : 1];
     __shared__ uint32_t s_pairs[kBlock / kWave][kMulti ? kMaxCams : 1];
+    __shared__ uint32_t s_ents[kBlock / kWave][kMulti ? kMaxCams : 1];
     // kMulti: the pending list holds entries of every camera, each tagged
     // with its camera; chunks are counted per camera, and a flush reserves
     // each camera's share of its own chunk list
@@ -727,13 +754,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ uint32_t s_bc[kBlock / kWave][kMB], s_nch[kBlock / kWave][kMC], s_cbase[kBlock / kWave][kMC];
     __shared__ uint2 *s_chunks[kMC];
     __shared__ uint4 *s_erec[kMC];
+    if ((threadIdx.x & (kWave - 1)) == 0)
+        for (int c = 0; c < (kMulti ? kMaxCams : 1); ++c) {
+            s_vis[wv][c] = 0;
+            s_pairs[wv][c] = 0;
+            s_ents[wv][c] = 0;
+            s_nch[wv][c] = 0;
+        }
     if constexpr (kMulti) {
-        if ((threadIdx.x & (kWave - 1)) == 0)
-            for (int c = 0; c < kMaxCams; ++c) {
-                s_vis[wv][c] = 0;
-                s_pairs[wv][c] = 0;
-                s_nch[wv][c] = 0;
-            }
         if (threadIdx.x == 0)
             for (int c = 0; c < mo.n; ++c) {
                 s_chunks[c] = mo.c[c].chunks;
@@ -861,8 +889,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                         mo.c[c].fc->cull_read = tot;
                     }
                 } else {
-                    fc->ncand = ncand;
-                    fc->cull_read = tot;
+                    args.fc->ncand = ncand;
+                    args.fc->cull_read = tot;
                 }
             }
         }
@@ -871,7 +899,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // contiguous per wavefront), of raw parameters to the Gaussian's index
     int64_t batch = blockIdx.x;  // batch of 256 list positions (prepared) or Gaussians (raw)
     for (;;) {
-    int64_t g = sc.P;
+    ArgPtr batch_ptr = arg_ptr;
+    asm volatile("" : "+s"(batch_ptr));
+    const PreArgs &ba = *(const PreArgs *)batch_ptr;
+    const DevScene &sc = ba.sc;
+    const DevPrepared &pp = ba.pp;
+    const DevOptions &op = ba.op;
+    const bool full = ba.full != 0;
+    int64_t g = P;
     uint32_t ii = 0;  // prepared: position in the candidate list
     if constexpr (kPrep) {
         if ((uint64_t)batch * kBlock >= ncand) break;
@@ -883,29 +918,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             for (uint32_t step = kCullBlocks / 2; step > 0; step >>= 1)
                 if (s_pref[sg + step] <= ii) sg += step;
             int64_t lo, hi;
-            cull_range(sc.P, sg, &lo, &hi);
-            g = (int64_t)cand[lo + (ii - s_pref[sg])];
+            cull_range(P, sg, &lo, &hi);
+            g = (int64_t)ba.cand[lo + (ii - s_pref[sg])];
         }
         batch += gridDim.x;
     } else {
-        if (batch * kBlock >= sc.P) break;
+        if (batch * kBlock >= P) break;
         const int64_t ii = batch * kBlock + threadIdx.x;
-        if (ii < sc.P) g = ii;
+        if (ii < P) g = ii;
         batch += gridDim.x;
     }
-    const int ncams = kMulti ? mo.n : 1;
+    const int ncams = kMulti ? ba.mo.n : 1;
     for (int ci = 0; ci < ncams; ++ci) {
     // this camera, its image size and its outputs
-    const DevCamera &cm = kMulti ? mo.c[ci].cam : cam;
-    const int W = kMulti ? mo.c[ci].W : W_arg, H = kMulti ? mo.c[ci].H : H_arg;
-    const DevCam64 &cm64 = kMulti ? mo.c[ci].cam64 : cam64;
-    GaussState *__restrict__ const gs_c = kMulti ? mo.c[ci].gs : gs;
-    float4 *__restrict__ const conic_c = kMulti ? mo.c[ci].conic : conic;
-    uint4 *__restrict__ const rect_c = kMulti ? mo.c[ci].rect : rect;
-    uint32_t *__restrict__ const count_c = kMulti ? mo.c[ci].count : count;
-    uint8_t *__restrict__ const count8_c = kMulti ? mo.c[ci].count8 : count8;
-    uint4 *__restrict__ const erec_c = kMulti ? mo.c[ci].erec : erec;
-    uint32_t *__restrict__ const dkey_c = kMulti ? mo.c[ci].dkey : dkey;
+    const DevCamera &cm = kMulti ? ba.mo.c[ci].cam : ba.cam;
+    const int W = kMulti ? ba.mo.c[ci].W : ba.W, H = kMulti ? ba.mo.c[ci].H : ba.H;
+    const DevCam64 &cm64 = kMulti ? ba.mo.c[ci].cam64 : ba.cam64;
+    GaussState *__restrict__ const gs_c = kMulti ? ba.mo.c[ci].gs : ba.gs;
+    float4 *__restrict__ const conic_c = kMulti ? ba.mo.c[ci].conic : ba.conic;
+    uint4 *__restrict__ const rect_c = kMulti ? ba.mo.c[ci].rect : ba.rect;
+    uint32_t *__restrict__ const count_c = kMulti ? ba.mo.c[ci].count : ba.count;
+    uint8_t *__restrict__ const count8_c = kMulti ? ba.mo.c[ci].count8 : ba.count8;
+    uint4 *__restrict__ const erec_c = kMulti ? ba.mo.c[ci].erec : ba.erec;
+    uint32_t *__restrict__ const dkey_c = kMulti ? ba.mo.c[ci].dkey : ba.dkey;
     const int64_t st = sc.stride;
     bool valid = false;
     float u = 0, v = 0, A = 0, B = 0, C = 0, k2 = 0, o = 0, tz = 0, l2o = 0;
@@ -913,7 +948,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     int tx0 = 0, tx1 = -1, ty0 = 0, ty1 = -1;
     float col[3] = {0, 0, 0};
 
-    if (g < sc.P) {
+    if (g < P) {
         float mx, my, mz, po = 0.0f;
         if constexpr (kPrep) {
             const float4 p4 = pp.pos_o[g];
@@ -1157,18 +1192,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         cnt = (uint32_t)__popcll(hm);
     }
 
-    if (g < sc.P) {
+    // entries: the overlapped super-tiles (at most 10 for a rectangle of at
+    // most kBigTiles tiles)
+    const uint32_t ents = valid ? super_span(tx0, tx1, ty0, ty1) : 0u;
+    if (g < P) {
         const uint32_t key = valid ? __float_as_uint(tz) : kInvalidKey;
         const int64_t oi = kPrep ? (int64_t)ii : g;  // output slot
         if constexpr (kPrep) {
             // the Gaussian of this list position, in the caller's indexing
-            uint32_t *const gmap_c = kMulti ? mo.c[ci].gmap : gmap;
+            uint32_t *const gmap_c = kMulti ? ba.mo.c[ci].gmap : ba.gmap;
             gmap_c[ii] = pp.orig[g];
         }
         dkey_c[oi] = key;
-        // entries: the overlapped super-tiles (at most 10 for a rectangle of
-        // at most kBigTiles tiles)
-        count8_c[oi] = chunked ? kCount8Big : (uint8_t)(valid ? super_span(tx0, tx1, ty0, ty1) : 0u);
+        count8_c[oi] = chunked ? kCount8Big : (uint8_t)ents;
         // the 4-byte count: a chunked rectangle's starts at 0 (k_big_count
         // adds its hits); the others are read from count8
         if (full || chunked) count_c[oi] = valid ? cnt : 0u;
@@ -1194,21 +1230,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             rect_c[oi] = make_uint4(0u, 0u, 0u, 0u);
         }
     }
-    if constexpr (kMulti) {
+    {
         const uint32_t nv = (uint32_t)__popcll(__ballot(valid));
-        uint32_t np = small ? cnt : 0u;
+        uint32_t np = small ? cnt : 0u, ne = ents;
 #pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) np += (uint32_t)__shfl_xor((int)np, d, kWave);
+        for (int d = 1; d < kWave; d <<= 1) {
+            np += (uint32_t)__shfl_xor((int)np, d, kWave);
+            ne += (uint32_t)__shfl_xor((int)ne, d, kWave);
+        }
         if (lane == 0) {
             s_vis[wv][ci] += nv;
             s_pairs[wv][ci] += np;
+            s_ents[wv][ci] += ne;
         }
-        if (w_nbig > (uint32_t)(kWaveBig - kWave)) flush_big_multi(lane);  // room for the next camera
-    } else {
-        l_pairs += small ? cnt : 0u;
-        w_vis += (uint32_t)__popcll(__ballot(valid));
-        if (w_nbig > (uint32_t)(kWaveBig - kWave))
-            flush_big(lane, fc, chunks, chunk_cap, erec);  // room for the next batch
+        if (w_nbig > (uint32_t)(kWaveBig - kWave)) {  // room for the next batch (or camera)
+            if constexpr (kMulti)
+                flush_big_multi(lane);
+            else
+                flush_big(lane, args.fc, args.chunks, args.chunk_cap, args.erec);
+        }
     }
     }  // camera loop
     }  // batch loop
@@ -1220,39 +1260,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     static_assert(offsetof(FrameCounters, pairs) == offsetof(FrameCounters, visible) + 4 &&
                       offsetof(FrameCounters, visible) % 8 == 0,
                   "one 64-bit counter");
-    auto add_counts = [](FrameCounters *f, uint32_t vis, uint32_t prs) {
+    auto add_counts = [&](FrameCounters *f, int c) {
+        uint32_t vis = 0, prs = 0, ents = 0;
+        for (int w = 0; w < kBlock / kWave; ++w) {
+            vis += s_vis[w][c];
+            prs += s_pairs[w][c];
+            ents += s_ents[w][c];
+        }
         if (vis | prs)
             atomicAdd(reinterpret_cast<unsigned long long *>(&f->visible),
                       (unsigned long long)vis | ((unsigned long long)prs << 32));
+        if (ents) atomicAdd(&f->entries, ents);
     };
+    if (w_nbig) {
+        if constexpr (kMulti)
+            flush_big_multi(lane);
+        else
+            flush_big(lane, args.fc, args.chunks, args.chunk_cap, args.erec);
+    }
+    __syncthreads();
     if constexpr (kMulti) {
-        if (w_nbig) flush_big_multi(lane);
-        __syncthreads();
-        if ((int)threadIdx.x < mo.n) {
-            uint32_t vis = 0, prs = 0;
-            for (int w = 0; w < kBlock / kWave; ++w) {
-                vis += s_vis[w][threadIdx.x];
-                prs += s_pairs[w][threadIdx.x];
-            }
-            add_counts(mo.c[threadIdx.x].fc, vis, prs);
-        }
+        if ((int)threadIdx.x < mo.n) add_counts(mo.c[threadIdx.x].fc, (int)threadIdx.x);
     } else {
-        if (w_nbig) flush_big(lane, fc, chunks, chunk_cap, erec);
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) l_pairs += (uint32_t)__shfl_xor((int)l_pairs, d, kWave);
-        if (lane == 0) {
-            s_vis[wv][0] = w_vis;
-            s_pairs[wv][0] = l_pairs;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t vis = 0, prs = 0;
-            for (int w = 0; w < kBlock / kWave; ++w) {
-                vis += s_vis[w][0];
-                prs += s_pairs[w][0];
-            }
-            add_counts(fc, vis, prs);
-        }
+        if (threadIdx.x == 0) add_counts(args.fc, 0);
     }
 }
 
@@ -1700,15 +1730,13 @@ void launch_preprocess(const DevScene &sc, const DevPrepared *pp, const DevCamer
                        uint32_t *gmap, uint2 *chunks, uint32_t chunk_cap, FrameCounters *fc, uint32_t *gsum_clear,
                        bool full, hipStream_t s) {
     if (sc.P <= 0) return;
-    if (pp) {
-        hipLaunchKernelGGL(k_preprocess<true>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, sc, *pp, cam, cam64, op,
-                           W, H, gs, conic, rect, count, count8, erec, dkey, cand, seg_count, gmap, chunks, chunk_cap,
-                           fc, gsum_clear, (int)full, MultiOut{});
-    } else {
-        hipLaunchKernelGGL(k_preprocess<false>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, sc, DevPrepared{},
-                           cam, cam64, op, W, H, gs, conic, rect, count, count8, erec, dkey, cand, seg_count, gmap,
-                           chunks, chunk_cap, fc, gsum_clear, (int)full, MultiOut{});
-    }
+    const PreArgs a{sc,   pp ? *pp : DevPrepared{}, cam,  cam64, op,        W,    H,      gs,        conic, rect, count,
+                    count8, erec, dkey, cand, seg_count, gmap, chunks, chunk_cap, fc,    gsum_clear, (int)full,
+                    MultiOut{}};
+    if (pp)
+        hipLaunchKernelGGL(k_preprocess<true>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_preprocess<false>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
 }
 
 void launch_cull(const DevScene &sc, const DevPrepared &pp, const DevCamera &cam, const DevOptions &op, int W, int H,
@@ -1724,9 +1752,10 @@ void launch_preprocess_multi(const DevScene &sc, const DevPrepared &pp, const Mu
     const CamOut &c0 = mo.c[0];
     hipLaunchKernelGGL(k_cull<true>, dim3(kCullBlocks), dim3(kBlock), 0, s, sc, pp, c0.cam, op, c0.W, c0.H, cand,
                        seg_count, c0.fc, mo);
-    hipLaunchKernelGGL((k_preprocess<true, true>), dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, sc, pp, c0.cam,
-                       c0.cam64, op, c0.W, c0.H, c0.gs, c0.conic, c0.rect, c0.count, c0.count8, c0.erec, c0.dkey, cand,
-                       seg_count, gmap, c0.chunks, c0.chunk_cap, c0.fc, c0.gsum_clear, 0, mo);
+    const PreArgs a{sc,        pp,      c0.cam,  c0.cam64, op,        c0.W,      c0.H,         c0.gs, c0.conic,
+                    c0.rect,   c0.count, c0.count8, c0.erec, c0.dkey,   cand,      seg_count,    gmap,  c0.chunks,
+                    c0.chunk_cap, c0.fc, c0.gsum_clear, 0,   mo};
+    hipLaunchKernelGGL((k_preprocess<true, true>), dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
 }
 
 void launch_prepare(const DevScene &sc, const DevOptions &op, const uint32_t *perm, float4 *pos_o, float4 *cov,
@@ -1770,11 +1799,13 @@ void launch_super_emit(int W, int H, const uint32_t *order, uint32_t visible, co
                        uint32_t *gsum_clear, hipStream_t s) {
     (void)H;
     if (visible == 0 && (!sranges || nsuper == 0) && !gsum_clear) return;
-    unsigned grid = emit_grid(visible);
-    if (sranges) grid = std::max(grid, std::min<unsigned>((nsuper + kBlock - 1) / kBlock, kPersistentBlocks));
-    hipLaunchKernelGGL(k_super_emit, dim3(grid), dim3(kBlock), 0, s, W, order, visible, visible_dev, offsets, erec,
-                       big, chunk_cap, skey, gidx, smask, ecap, sranges, nsuper, gsum_clear, fc);
-    if (chunk_cap == 0 || visible == 0) return;
+    if (order) {
+        unsigned grid = emit_grid(visible);
+        if (sranges) grid = std::max(grid, std::min<unsigned>((nsuper + kBlock - 1) / kBlock, kPersistentBlocks));
+        hipLaunchKernelGGL(k_super_emit, dim3(grid), dim3(kBlock), 0, s, W, order, visible, visible_dev, offsets, erec,
+                           big, chunk_cap, skey, gidx, smask, ecap, sranges, nsuper, gsum_clear, fc);
+    }
+    if (chunk_cap == 0 || visible == 0 || !chunk_mask) return;
     hipLaunchKernelGGL(k_big_entries, dim3(kPersistentBlocks), dim3(kBlock), 0, s, W, erec, ng, chunks, big,
                        chunk_cap, chunk_mask, fc, skey, gidx, smask, ecap);
 }

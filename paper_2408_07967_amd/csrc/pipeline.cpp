@@ -373,7 +373,7 @@ void SideStream::destroy() {
 void enqueue_front(const DevScene &sc, const DevPrepared *pp, const DevCamera &cam, const DevOptions &op, int W,
                    int H, FrameBuffers &fb, ChunkList &ch, SortScratch &ss, FrameCounters *fc,
                    FrameCounters *host_fc, hipStream_t s, const SideStream &side, const StageMarks &mk,
-                   hipEvent_t counters_ready, bool full) {
+                   hipEvent_t counters_ready, bool full, bool join_late) {
     const uint32_t chunk_cap = (uint32_t)std::min<size_t>(ch.cap, 0xffffffffu);
     // ---- stage 1: preprocess + exact tile count -------------------------------
     // (a prepared scene's cull clears the counters itself)
@@ -389,22 +389,28 @@ void enqueue_front(const DevScene &sc, const DevPrepared *pp, const DevCamera &c
     mk.mark(kMarkCulled, s);
     launch_preprocess(sc, pp, cam, to_dev64(cam, op, W, H), op, W, H, fb.gs, fb.conic, fb.rect, fb.count, fb.count8,
                       fb.erec, fb.dkey, fb.dv_b, fb.seg_count, fb.gmap, ch.chunks, chunk_cap, fc, ss.slot(0), full, s);
-    enqueue_front_rest(pp != nullptr, (uint32_t)sc.P, op, W, H, fb, ch, ss, fc, host_fc, s, side, mk, counters_ready);
+    enqueue_front_rest(pp != nullptr, (uint32_t)sc.P, op, W, H, fb, ch, ss, fc, host_fc, s, side, mk, counters_ready,
+                       join_late);
 }
 
 void enqueue_front_rest(bool dense, uint32_t P32, const DevOptions &op, int W, int H, FrameBuffers &fb, ChunkList &ch,
                         SortScratch &ss, FrameCounters *fc, FrameCounters *host_fc, hipStream_t s,
-                        const SideStream &side, const StageMarks &mk, hipEvent_t counters_ready) {
+                        const SideStream &side, const StageMarks &mk, hipEvent_t counters_ready, bool join_late) {
     const uint32_t chunk_cap = (uint32_t)std::min<size_t>(ch.cap, 0xffffffffu);
-    // the large rectangles' exact tests touch neither the depth keys nor the
-    // sort scratch: they run beside the depth sort
+    // The large rectangles' exact tests touch neither the depth keys nor the
+    // sort scratch: they run beside the depth sort.  With them every counter
+    // is final, so their copy to the host follows on the same stream, and the
+    // main stream has no marker of its own for it (an event record or wait
+    // between two kernels costs about 6 us).
     hipStream_t sb = s;
     if (side.side && hipEventRecord(side.fork, s) == hipSuccess &&
         hipStreamWaitEvent(side.side, side.fork, 0) == hipSuccess)
         sb = side.side;
     launch_big_count(W, H, op.binning, fb.gs, fb.conic, fb.erec, ch.chunks, chunk_cap, ch.mask, fb.count, fc, sb);
-    const bool joined = sb == s || hipEventRecord(side.join, sb) == hipSuccess;
+    bool joined = sb == s || hipEventRecord(side.join, sb) == hipSuccess;
     if (!joined) (void)hipStreamSynchronize(sb);  // cannot order the streams by an event: wait here instead
+    if (host_fc) (void)hipMemcpyAsync(host_fc, fc, sizeof(FrameCounters), hipMemcpyDeviceToHost, sb);
+    if (counters_ready) (void)hipEventRecord(counters_ready, sb);
     // ---- depth order of the visible Gaussians: 4 LSD passes over the depth
     // digits, hoisted before key duplication (the low half of the (tile |
     // depth) key is the same for every pair of a Gaussian) --------------------
@@ -430,22 +436,16 @@ void enqueue_front_rest(bool dense, uint32_t P32, const DevOptions &op, int W, i
     // (a large rectangle's entries follow from its rectangle: the scan does
     // not wait for its tests)
     launch_count_scan(fb.dv_a, fb.count8, fb.erec, P32, &fc->visible, fb.dk_b, ss.sums, fb.offsets, &fc->entries, s);
-    // the pair count and the emission read what the large-rectangle tests wrote
-    if (sb != s && joined && hipStreamWaitEvent(s, side.join, 0) != hipSuccess) (void)hipStreamSynchronize(sb);
+    // the large rectangles' entries read what their tests wrote (a second
+    // half that waits for them itself starts without them)
+    if (!join_late && sb != s && joined && hipStreamWaitEvent(s, side.join, 0) != hipSuccess)
+        (void)hipStreamSynchronize(sb);
     mk.mark(3, s);
-    // the second half reads the counters on the device; only the host waits
-    // for their copy, which therefore runs beside it when it can
-    hipStream_t sc2 = s;
-    if (counters_ready && side.side && hipEventRecord(side.fork, s) == hipSuccess &&
-        hipStreamWaitEvent(side.side, side.fork, 0) == hipSuccess)
-        sc2 = side.side;
-    if (host_fc) (void)hipMemcpyAsync(host_fc, fc, sizeof(FrameCounters), hipMemcpyDeviceToHost, sc2);
-    if (counters_ready) (void)hipEventRecord(counters_ready, sc2);
 }
 
 bool enqueue_back(int W, int H, const DevOptions &op, uint32_t P, FrameBuffers &fb, ChunkList &ch, SortScratch &ss,
                   FrameCounters *fc, float *rgb, float *T, uint32_t *last, unsigned long long *work, hipStream_t s,
-                  const StageMarks &mk, int blend_variant) {
+                  const StageMarks &mk, int blend_variant, hipEvent_t big_tests) {
     const uint32_t nsuper = super_count(W, H);
     const uint32_t chunk_cap = (uint32_t)std::min<size_t>(ch.cap, 0xffffffffu);
     const uint32_t pair_cap = (uint32_t)std::min<size_t>(fb.capN, 0xffffffffu);
@@ -466,9 +466,19 @@ bool enqueue_back(int W, int H, const DevOptions &op, uint32_t P, FrameBuffers &
     // the emission also sets every super-tile's range empty when a sort pass
     // records the ranges (one super-tile: no pass, its range holds every entry)
     static_assert(kGsumSlots >= 4 + 2, "four depth and up to two super-tile passes (ids < 65536)");
-    launch_super_emit(W, H, fb.dv_a, P, &fc->visible, fb.offsets, fb.erec, (uint32_t)std::min<size_t>(fb.capP, 0xffffffffu),
-                      ch.chunks, ch.big, ch.mask, chunk_cap, fc, skey_a, gidx_a, mask_a, ecap,
-                      npass > 0 ? fb.sranges : nullptr, nsuper, npass > 0 ? ss.slot(4) : nullptr, s);
+    auto emit = [&](const uint32_t *order, const uint32_t *chunk_mask) {
+        launch_super_emit(W, H, order, P, &fc->visible, fb.offsets, fb.erec,
+                          (uint32_t)std::min<size_t>(fb.capP, 0xffffffffu), ch.chunks, ch.big, chunk_mask, chunk_cap, fc,
+                          skey_a, gidx_a, mask_a, ecap, npass > 0 ? fb.sranges : nullptr, nsuper,
+                          npass > 0 ? ss.slot(4) : nullptr, s);
+    };
+    if (big_tests) {
+        emit(fb.dv_a, nullptr);
+        if (hipStreamWaitEvent(s, big_tests, 0) != hipSuccess) (void)hipEventSynchronize(big_tests);
+        emit(nullptr, ch.mask);
+    } else {
+        emit(fb.dv_a, ch.mask);
+    }
     mk.mark(4, s);
     // ---- stage 3: stable LSD sort of the entries by super-tile ----------------------
     uint16_t *ki = skey_a, *ko = skey_b;

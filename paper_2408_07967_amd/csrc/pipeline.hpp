@@ -160,25 +160,27 @@ struct SideStream {
 };
 
 // Stages 1 and 2a: preprocess with the exact tile count, depth order of the
-// visible Gaussians, scan of the tile counts in depth order.  The exact tests
-// of the large rectangles run on the side stream while the depth order is
-// sorted on s; the scan waits for both.  Ends with an asynchronous copy of
-// the frame counters to host_fc (pinned; NULL: no copy): on s when
-// counters_ready is NULL; otherwise on the side stream, followed there by
-// counters_ready, so that s goes straight on to the second half.
+// visible Gaussians, scan of the super-tile entry counts in depth order.  The
+// exact tests of the large rectangles run on the side stream while the depth
+// order is sorted on s, followed there by an asynchronous copy of the frame
+// counters to host_fc (pinned; NULL: no copy) and by counters_ready (if not
+// NULL); without a side stream all of it runs on s.  join_late: s does not
+// wait for the tests; the caller's second half does (enqueue_back's big_tests
+// = side.join).
 // pp: NULL (raw parameters) or the scene's view-independent precompute.
 // full: also write what only a kept frame's introspection reads (see
 // launch_preprocess).
 void enqueue_front(const DevScene &sc, const DevPrepared *pp, const DevCamera &cam, const DevOptions &op, int W,
                    int H, FrameBuffers &fb, ChunkList &ch, SortScratch &ss, FrameCounters *fc,
                    FrameCounters *host_fc, hipStream_t s, const SideStream &side, const StageMarks &mk,
-                   hipEvent_t counters_ready = nullptr, bool full = false);
+                   hipEvent_t counters_ready = nullptr, bool full = false, bool join_late = false);
 // The part of enqueue_front after the preprocess (for a preprocess run
 // elsewhere, as in a multi-camera batch).  dense: the outputs are over a
 // candidate list of fc->ncand positions (a prepared scene); P32 bounds it.
 void enqueue_front_rest(bool dense, uint32_t P32, const DevOptions &op, int W, int H, FrameBuffers &fb, ChunkList &ch,
                         SortScratch &ss, FrameCounters *fc, FrameCounters *host_fc, hipStream_t s,
-                        const SideStream &side, const StageMarks &mk, hipEvent_t counters_ready = nullptr);
+                        const SideStream &side, const StageMarks &mk, hipEvent_t counters_ready = nullptr,
+                        bool join_late = false);
 
 // Device buffers of a scene's view-independent precompute: parts of one
 // allocation.
@@ -226,9 +228,11 @@ void free_prepared(PreparedBuffers &pb);
 // sequence holds no host dependency and can be captured in a graph.  P
 // bounds the visible count; fb.capN bounds the pair count (and, through
 // entry_capacity, the entries).  The sorted values end in tv_b (returns
-// false: not in tv_a).  blend_variant: see launch_blend.
+// false: not in tv_a).  blend_variant: see launch_blend.  big_tests: an event
+// after the large rectangles' tests, which only their entries wait for (NULL:
+// s has waited; a captured graph takes no event from outside).
 bool enqueue_back(int W, int H, const DevOptions &op, uint32_t P, FrameBuffers &fb, ChunkList &ch, SortScratch &ss,
                   FrameCounters *fc, float *rgb, float *T, uint32_t *last, unsigned long long *work, hipStream_t s,
-                  const StageMarks &mk, int blend_variant = 0);
+                  const StageMarks &mk, int blend_variant = 0, hipEvent_t big_tests = nullptr);
 
 }  // namespace fgs

@@ -377,7 +377,7 @@ fgs_status render_impl(fgs_context *ctx, const fgs_scene *scene, const fgs_prepa
     for (int attempt = 0;; ++attempt) {
         const DevPrepared pdev = prep ? prep->pb.dev() : DevPrepared{};
         enqueue_front(dsc, prep ? &pdev : nullptr, dcam, dop, W, H, fb, ctx->ch, ctx->ss, ctx->fc_dev, ctx->fc_host,
-                      s, ctx->side, mk, ctx->front_done, saved != nullptr);
+                      s, ctx->side, mk, ctx->front_done, saved != nullptr, true);
         HIP_TRY(ctx, hipGetLastError());
         // The second half reads every count on the device and never writes
         // beyond the pair buffers, so it is enqueued at once with the buffers
@@ -386,7 +386,7 @@ fgs_status render_impl(fgs_context *ctx, const fgs_scene *scene, const fgs_prepa
         spec_cap = 0;
         if (!plan && !work && fb.capN > 0) {
             tiles_in_a = enqueue_back(W, H, dop, (uint32_t)P, fb, ctx->ch, ctx->ss, ctx->fc_dev, out_rgb, Tdst, Ldst,
-                                      nullptr, s, mk, ctx->blend_variant);
+                                      nullptr, s, mk, ctx->blend_variant, ctx->side.join);
             HIP_TRY(ctx, hipGetLastError());
             spec_cap = fb.capN;
         }
@@ -416,6 +416,7 @@ fgs_status render_impl(fgs_context *ctx, const fgs_scene *scene, const fgs_prepa
         break;
     }
     if (plan) {
+        HIP_TRY(ctx, hipStreamSynchronize(s));  // (the depth order may still run: leave the scratch idle)
         FrameBuffers need;
         need.capP = (size_t)P;
         need.capN = Ncap;
@@ -445,7 +446,7 @@ fgs_status render_impl(fgs_context *ctx, const fgs_scene *scene, const fgs_prepa
         if (spec_cap) HIP_TRY(ctx, hipStreamSynchronize(s));
         HIP_TRY_MEM(ctx, ensure_pairs(fb, Ncap));
         tiles_in_a = enqueue_back(W, H, dop, (uint32_t)P, fb, ctx->ch, ctx->ss, ctx->fc_dev, out_rgb, Tdst, Ldst,
-                                  work, s, mk, ctx->blend_variant);
+                                  work, s, mk, ctx->blend_variant, ctx->side.join);
     }
     HIP_TRY(ctx, hipGetLastError());
     if (timed) {
@@ -632,12 +633,13 @@ fgs_status fgs_render_noalloc(fgs_context *ctx, const fgs_scene *scene, const fg
     const DevCamera dcam = to_dev(*cam);
     const DevOptions dop = to_dev(opt);
     const StageMarks mk;  // no stage events
-    enqueue_front(dsc, nullptr, dcam, dop, W, H, fb, ch, ss, fc, ctx->fc_host, s, ctx->side, mk, ctx->front_done);
+    enqueue_front(dsc, nullptr, dcam, dop, W, H, fb, ch, ss, fc, ctx->fc_host, s, ctx->side, mk, ctx->front_done, false,
+                  true);
     HIP_TRY(ctx, hipGetLastError());
     // the second half reads the pair count on the device and stays within the
     // pair arrays, so it goes right behind the first
     enqueue_back(W, H, dop, (uint32_t)P, fb, ch, ss, fc, out_rgb, out_T, out_last, nullptr, s, mk,
-                 ctx->blend_variant);
+                 ctx->blend_variant, ctx->side.join);
     HIP_TRY(ctx, hipGetLastError());
     hipError_t q;
     while ((q = hipEventQuery(ctx->front_done)) == hipErrorNotReady) {
@@ -807,10 +809,11 @@ fgs_status fgs_render_prepared_batch(fgs_context *ctx, const fgs_prepared *p, co
         // for the counters) each camera's second half
         for (int c = 0; c < ncams; ++c) {
             auto &bc = ctx->batch[c];
+            // (the side stream runs in order: the last camera's event stands
+            // for every camera's counters)
             enqueue_front_rest(true, (uint32_t)P, dop, W, H, bc.fb, bc.ch, bc.ss, ctx->bfc_dev + c, ctx->bfc_host + c,
-                               s, ctx->side, nomk);
+                               s, ctx->side, nomk, ctx->front_done);
         }
-        HIP_TRY(ctx, hipEventRecord(ctx->front_done, s));
         // the cameras' second halves share no buffer: odd cameras run on the
         // side stream beside the even ones (one camera's sort passes, bound by
         // HBM, overlap another's blend, bound by the VALU), and s joins the

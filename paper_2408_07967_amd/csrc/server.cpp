@@ -192,8 +192,7 @@ void speculate_back(fgs_server *srv, Slot &s);
 void start_front(fgs_server *srv, Slot &s) {
     const DevCamera dcam = to_dev(s.req.cam);
     enqueue_front(srv->dsc, &srv->pdev, dcam, srv->dop, s.req.W, s.req.H, s.fb, s.ch, s.ss, s.fc_dev, s.fc_host,
-                  s.stream, s.side, StageMarks{});
-    (void)hipEventRecord(s.evA, s.stream);
+                  s.stream, s.side, StageMarks{}, s.evA);
     s.state = SlotState::FRONT;
     speculate_back(srv, s);
 }
@@ -237,8 +236,7 @@ void start_front_batch(fgs_server *srv, const std::vector<Slot *> &b) {
         Slot &s = *b[c];
         if (c > 0) (void)hipStreamWaitEvent(s.stream, s0.evP, 0);
         enqueue_front_rest(true, P, srv->dop, s.req.W, s.req.H, s.fb, s.ch, s.ss, s.fc_dev, s.fc_host, s.stream,
-                           s.side, StageMarks{});
-        (void)hipEventRecord(s.evA, s.stream);
+                           s.side, StageMarks{}, s.evA);
         s.state = SlotState::FRONT;
         speculate_back(srv, s);
     }
