@@ -20,8 +20,9 @@
 // run on the matrix cores: a wavefront leaves the w and a T of eight Gaussians
 // as the rows of a 16 x 64 matrix in LDS, whose product with the 64 x 9 matrix
 // of the quadrant's monomials and dL/dRGB (kept in registers) gives the sums
-// of all eight.  The monomials are taken about the tile's centre; the sums
-// about the Gaussian's centre follow once per Gaussian and tile.  (Summing the
+// of all eight.  The monomials are taken about the quadrant's centre (at most
+// 3.5 pixels away, so that moving the sums to the Gaussian's centre, done on
+// the product's lanes, cancels little).  (Summing the
 // nine terms over the lanes with DPP adds took 54 of about 130 VALU
 // instructions per step; with one plane per accumulator each of a Gaussian's
 // nine atomics was a request of its own.  1M Gaussians at 1920 x 1080: 897 ->
@@ -63,6 +64,12 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
         v = o > v ? o : v;
     }
     return v;
+}
+
+// Lane kLane of each row of 16 lanes, in all lanes of the row
+template <int kLane>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + kLane, 0xf, 0xf, false));  // row_newbcast
 }
 
 // LDS visibility of this wavefront's own writes to its own later reads
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(const GaussState *__restri
 #pragma unroll
         for (int s = 0; s < kWave / 4; ++s) {
             const int lx = qx * 8 + (s & 7), ly = qy * 8 + 2 * kb + (s >> 3);
-            const float x = (float)lx - 7.5f, y = (float)ly - 7.5f;
+            const float x = (float)(s & 7) - 3.5f, y = (float)(2 * kb + (s >> 3)) - 3.5f;
             const int i = tx * kTile + lx, j = ty * kTile + ly;
             float v = col == 0 ? 1.0f : col == 1 ? x * x : col == 2 ? x * y : col == 3 ? y * y : col == 4 ? x : y;
             if (col > 5) v = 0.0f;
@@ -132,6 +139,7 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(const GaussState *__restri
     const uint32_t start = ranges[tile].x;
 
     float(*const sw)[kRowPitch] = s_w[wave];
+    const float qcx = (float)(tx * kTile + qx * 8 + 4), qcy = (float)(ty * kTile + qy * 8 + 4);  // quadrant's centre
     int n_slots = 0;      // wave-uniform: rows filled
     uint64_t slot_j = 0;  // wave-uniform: the batch entry of each slot, one byte each
     static_assert(kBwdBatch <= 256 && kSlots == 8, "one byte per slot");
@@ -150,13 +158,29 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(const GaussState *__restri
             d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, bm[4 * q + 3], d, 0, 0, 0);
         }
         // lane l, element r: row 4 (l / 16) + r, column l % 16; rows 0..7 are
-        // the slots' w (columns 0..5), rows 8..15 their a T (columns 6..8)
+        // the slots' w (columns 0..5), rows 8..15 their a T (columns 6..8).
+        // The w sums are moved to the Gaussian's centre (u, v) (relative to
+        // the quadrant's) from the row's sums of 1, x and y:
+        //   sum w (x - u) = sx - u s0 = X,  sum w (x - u)^2 = sxx - u (sx + X),
+        //   sum w (x - u)(y - v) = sxy - u sy - v X, and so in y.
         const int col = lane & 15, blk = lane >> 4;
         const bool use = blk < 2 ? col < 6 : col >= 6 && col < kAcc;
         const uint32_t js = (blk & 1) ? (uint32_t)(slot_j >> 32) : (uint32_t)slot_j;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (use && 4 * (blk & 1) + r < n_slots) atomicAdd(&s_acc[(js >> (8 * r)) & 255u][col], d[r]);
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t j = (js >> (8 * r)) & 255u;
+            float o = d[r];
+            const float s0 = row_bcast<0>(o), sx = row_bcast<4>(o), sy = row_bcast<5>(o);
+            const float u = s_f0[j].x - qcx, v = s_f0[j].y - qcy;
+            const float X = fmaf(-u, s0, sx), Y = fmaf(-v, s0, sy);
+            if (blk < 2) {
+                o = col == 4 ? X : col == 5 ? Y : o;
+                o = col == 1 ? fmaf(-u, sx + X, o) : col == 2 ? fmaf(-v, X, fmaf(-u, sy, o)) : o;
+                o = col == 3 ? fmaf(-v, sy + Y, o) : o;
+                o *= -0.5f;  // w is -2 dL/dq
+            }
+            if (use && 4 * (blk & 1) + r < n_slots) atomicAdd(&s_acc[j][col], o);
+        }
         // every lane has read the rows before they are refilled
         wave_sync();
         n_slots = 0;
@@ -235,23 +259,6 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(const GaussState *__restri
                 }
             }
             if (n_slots) reduce_slots();
-        }
-        __syncthreads();
-        // sums of dL/dq (w is -2 times it) about the Gaussian's centre
-        if (tid < nb) {
-            const float u = s_f0[tid].x - ((float)(tx * kTile) + 8.0f), v = s_f0[tid].y - ((float)(ty * kTile) + 8.0f);
-            float *const S = s_acc[tid];
-            const float s0 = S[0], sx = S[4], sy = S[5];
-            const float dx = fmaf(-u, s0, sx), dy = fmaf(-v, s0, sy);
-            const float xx = fmaf(-u, dx, fmaf(-u, sx, S[1]));
-            const float xy = fmaf(-v, dx, fmaf(-u, sy, S[2]));
-            const float yy = fmaf(-v, dy, fmaf(-v, sy, S[3]));
-            S[0] = -0.5f * s0;
-            S[1] = -0.5f * xx;
-            S[2] = -0.5f * xy;
-            S[3] = -0.5f * yy;
-            S[4] = -0.5f * dx;
-            S[5] = -0.5f * dy;
         }
         __syncthreads();
         for (int e = tid; e < nb * kAccStride; e += kBlock) {
