@@ -137,13 +137,30 @@ __global__ __launch_bounds__(kScanBlock) void k_list_chunks(const uint2 *__restr
     }
     for (uint32_t s = s0; s < s1; ++s) {
         const uint2 r = super_entries(sranges, s, ecap);
-        const uint32_t n = (r.y - r.x + kListChunk - 1) / kListChunk;
         cbase[s] = base;
         rowsum[s] = 0;  // (the rows of super-tiles are at most nsuper)
-        for (uint32_t c = 0; c < n; ++c) csuper[base + c] = s;
-        base += n;
+        base += (r.y - r.x + kListChunk - 1) / kListChunk;
     }
     if (tid == 0) cbase[nsuper] = total;
+    __syncthreads();  // (and the bases are visible to the workgroup)
+    // the super-tile of every chunk: a wavefront takes its share of up to 64
+    // super-tiles and fills one's chunks after the other with all its lanes
+    // (one thread per super-tile, a dense one's hundreds of chunks in turn,
+    // took the kernel 19.0 us at 4K with 10M Gaussians and 6.2 at 1080p with 1M;
+    // now 8.5 and 4.6)
+    constexpr uint32_t kWaves = kScanBlock / kWave;
+    uint32_t share = (nsuper + kWaves - 1) / kWaves;
+    share = share < (uint32_t)kWave ? share : (uint32_t)kWave;
+    for (uint32_t b0 = (uint32_t)wave * share; b0 < nsuper; b0 += kWaves * share) {
+        const uint32_t s = b0 + (uint32_t)lane;
+        const bool mine = (uint32_t)lane < share && s < nsuper;
+        const uint32_t lo = mine ? cbase[s] : 0u, hi = mine ? cbase[s + 1] : 0u;
+        for (uint32_t j = 0; j < share; ++j) {
+            const uint32_t c1 = (uint32_t)__builtin_amdgcn_readlane((int)hi, (int)j);
+            for (uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)j) + (uint32_t)lane; c < c1; c += kWave)
+                csuper[c] = b0 + j;
+        }
+    }
 }
 
 __global__ __launch_bounds__(kListBlock) void k_list_count(const uint2 *__restrict__ sranges, uint32_t ecap,
