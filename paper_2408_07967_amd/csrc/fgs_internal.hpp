@@ -9,7 +9,7 @@ namespace fgs {
 
 constexpr int kTile = 16;          // tile edge in pixels (16 x 16 tiles)
 constexpr int kBlock = 256;        // threads per workgroup for 1D kernels
-constexpr int kSortItems = 16;     // keys per thread in a sort pass
+constexpr int kSortItems = 16;     // keys per thread in a sort pass, at most
 constexpr int kSortTile = kBlock * kSortItems;  // keys per sort workgroup
 constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
@@ -156,7 +156,7 @@ constexpr int kBigList = 512;                    // pending chunk reservations p
 // FrameCounters::error bits
 constexpr uint32_t kErrChunkOverflow = 2u;       // chunk list too small: render again
 
-// Radix sort / scan passes use a fixed grid of kSortBlocks workgroups,
+// Radix sort / scan passes use at most kSortBlocks workgroups,
 // grouped by kSortGroup for the offset computation.
 constexpr int kSortBlocks = 1024;
 constexpr int kSortGroup = 32;

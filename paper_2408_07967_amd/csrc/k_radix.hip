@@ -1,9 +1,10 @@
 // Stable LSD radix sort pass and exclusive scan without any wait between
 // workgroups (the sort stage of Sec. 2.2; the scan of Alg. 2's offsets).
 //
-// A pass over n keys uses a fixed grid of kSortBlocks workgroups; workgroup b
-// owns a contiguous range of 4096-key tiles (the range is derived on the
-// device from n, so n may be a device-side count):
+// A pass over n keys uses kSortBlocks workgroups (fewer if n is known to be
+// small); workgroup b owns a contiguous range of tiles of 1024 to 4096 keys
+// (range and tile size are derived on the device from n, so n may be a
+// device-side count):
 //   upsweep    - digit histogram of each workgroup's range   -> hist[b][d],
 //                and added (device-scope atomics) into the row
 //                of its group of kSortGroup workgroups       -> gsum[w][d]
@@ -42,6 +43,23 @@ __device__ __forceinline__ void block_range(uint32_t n, uint32_t b, uint32_t nb,
     const uint32_t h = t1 * granule;
     *hi = h < n ? h : n;
     if (*lo > *hi) *lo = *hi;
+}
+
+// Keys per thread in one tile of a sort pass over n keys: the smallest of 4, 8,
+// 12 and 16 with which one tile per workgroup is enough, so that a pass over
+// few keys spreads over the chip instead of over n / 4096 workgroups.  The
+// ranking is a serial chain per key of a wavefront, and a tile of 1024 keys has
+// a quarter of the chain of a tile of 4096; beyond kSortBlocks x 4096 keys the
+// large tiles' longer digit runs (fewer partial lines in the scatter) stay.
+// With tiles of 4096 keys throughout, a depth pass over 10,000 keys took
+// 12 us, now 7 (200,000: 14, now 8; 1M: 14.5, now 12.6), the super-tile pass
+// over eval-size frames' 0.6M entries 30 us, now 9.3.
+constexpr uint32_t kItemStep = 4;
+static_assert(kSortItems % kItemStep == 0, "whole steps");
+__device__ __forceinline__ uint32_t tile_items(uint32_t n, uint32_t nb) {
+    uint32_t items = kItemStep;
+    while (items < (uint32_t)kSortItems && n > nb * (kBlock * items)) items += kItemStep;
+    return items;
 }
 
 // Exclusive scan of one value per thread over a 256-thread workgroup.
@@ -86,34 +104,42 @@ __global__ __launch_bounds__(kBlock) void k_radix_upsweep(const KeyT *__restrict
     __syncthreads();
     const uint32_t n = count_of(n_host, n_dev);
     uint32_t lo, hi;
-    block_range(n, blockIdx.x, gridDim.x, &lo, &hi);
+    block_range(n, blockIdx.x, gridDim.x, &lo, &hi, kBlock * tile_items(n, gridDim.x));
     const uint32_t dmask = (1u << bits) - 1u;
-    // Each thread counts kSortItems consecutive keys of a tile (the histogram
-    // ignores their order), read with 16-byte loads where the tile is whole:
-    // all loads in flight before any use.
-    constexpr int kPerVec = 16 / (int)sizeof(KeyT);
-    static_assert(kSortItems % kPerVec == 0, "whole 16-byte groups per thread");
+    // The histogram ignores the keys' order: each thread takes every 256th
+    // 16-byte group of the range (lo is a whole number of groups), all loads
+    // of up to 4096 keys in flight before any use.
+    constexpr int kPerVec = 16 / (int)sizeof(KeyT), kVecs = kSortItems / kPerVec;
+    static_assert(kSortItems % kPerVec == 0 && (kBlock * (int)kItemStep) % kPerVec == 0, "whole 16-byte groups");
     for (uint32_t c0 = lo; c0 < hi; c0 += kSortTile) {
-        const uint32_t b = c0 + (uint32_t)tid * kSortItems;
-        uint32_t k[kSortItems];
-        if (b + kSortItems <= hi) {
-            uint4 q[kSortItems / kPerVec];
+        uint32_t k[kVecs * kPerVec];
 #pragma unroll
-            for (int j = 0; j < kSortItems / kPerVec; ++j) q[j] = reinterpret_cast<const uint4 *>(keys + b)[j];
-#pragma unroll
-            for (int j = 0; j < kSortItems / kPerVec; ++j) {
-                const uint32_t w[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
+        for (int j = 0; j < kVecs; ++j) {
+            const uint32_t g = c0 + ((uint32_t)(j * kBlock) + (uint32_t)tid) * kPerVec;
+            uint32_t w[4] = {0, 0, 0, 0};
+            if (g + kPerVec <= hi) {
+                const uint4 q = *reinterpret_cast<const uint4 *>(keys + g);
+                w[0] = q.x;
+                w[1] = q.y;
+                w[2] = q.z;
+                w[3] = q.w;
+            } else {
 #pragma unroll
                 for (int e = 0; e < kPerVec; ++e)
-                    k[j * kPerVec + e] = sizeof(KeyT) == 2 ? (w[e / 2] >> (16 * (e % 2))) & 0xffffu : w[e];
+                    if (g + e < hi) w[e * 4 / kPerVec] |= (uint32_t)keys[g + e] << (kPerVec == 8 ? 16 * (e % 2) : 0);
             }
-        } else {
 #pragma unroll
-            for (int i = 0; i < kSortItems; ++i) k[i] = b + i < hi ? (uint32_t)keys[b + i] : kInvalidKey;
+            for (int e = 0; e < kPerVec; ++e)
+                k[j * kPerVec + e] = sizeof(KeyT) == 2 ? (w[e / 2] >> (16 * (e % 2))) & 0xffffu : w[e];
         }
 #pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            if (b + i < hi && (!kFilter || k[i] != kInvalidKey)) atomicAdd(&s_h[wave][(k[i] >> shift) & dmask], 1u);
+        for (int j = 0; j < kVecs; ++j) {
+            const uint32_t g = c0 + ((uint32_t)(j * kBlock) + (uint32_t)tid) * kPerVec;
+#pragma unroll
+            for (int e = 0; e < kPerVec; ++e) {
+                const uint32_t kk = k[j * kPerVec + e];
+                if (g + e < hi && (!kFilter || kk != kInvalidKey)) atomicAdd(&s_h[wave][(kk >> shift) & dmask], 1u);
+            }
         }
     }
     __syncthreads();
@@ -167,7 +193,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kR
     const uint32_t n = count_of(n_host, n_dev);
     const uint32_t b = blockIdx.x, nb = gridDim.x;
     uint32_t lo, hi;
-    block_range(n, b, nb, &lo, &hi);
+    const uint32_t items = tile_items(n, nb), tile = kBlock * items;
+    block_range(n, b, nb, &lo, &hi, tile);
+    // uniform: no tile for this workgroup (the first one writes the runs)
+    if (lo >= hi && !(digit_run && b == 0)) return;
 
     // global offset of this workgroup's first key of each of the thread's
     // digits: every group sum and every earlier histogram row of the group is
@@ -224,7 +253,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kR
             dbase += dtot[q];
         }
     }
-    if (lo >= hi) return;  // uniform: no tile for this workgroup
+    if (lo >= hi) return;
 
     const uint32_t dmask = (1u << bits) - 1u;
     // A tile's loads are all issued before any use, and the next tile's are
@@ -234,9 +263,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kR
     // staged rather than held in registers)
     uint32_t key[kSortItems], val[kIdentityVals ? 1 : kSortItems], rank[kSortItems];
     auto load_tile = [&](uint32_t t) {
-        const uint32_t base = t + (uint32_t)wave * (kSortItems * kWave);
+        const uint32_t base = t + (uint32_t)wave * (items * kWave);
 #pragma unroll
         for (int i = 0; i < kSortItems; ++i) {
+            if (i % (int)kItemStep == 0 && (uint32_t)i >= items) break;
             const uint32_t idx = base + (uint32_t)(i * kWave + lane);
             const bool in = idx < hi;
             key[i] = in ? (uint32_t)keys_in[idx] : kInvalidKey;
@@ -244,12 +274,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kR
         }
     };
     load_tile(lo);
-    for (uint32_t t0 = lo; t0 < hi; t0 += kSortTile) {
+    for (uint32_t t0 = lo; t0 < hi; t0 += tile) {
         for (int i = tid; i < kWaves * kR; i += kBlock) (&s_wave[0][0])[i] = 0;
         __syncthreads();
-        const uint32_t base = t0 + (uint32_t)wave * (kSortItems * kWave);
+        const uint32_t base = t0 + (uint32_t)wave * (items * kWave);
 #pragma unroll
         for (int i = 0; i < kSortItems; ++i) {
+            if (i % (int)kItemStep == 0 && (uint32_t)i >= items) break;
             const uint32_t idx = base + (uint32_t)(i * kWave + lane);
             const bool in = idx < hi;
             const uint32_t k = key[i];
@@ -314,17 +345,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kR
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kSortItems; ++i) {
+            if (i % (int)kItemStep == 0 && (uint32_t)i >= items) break;
             if (rank[i] != 0xffffffffu) {
                 const uint32_t d = (key[i] >> shift) & dmask;
                 const uint32_t lp = s_excl[d] + s_wave[wave][d] + rank[i];
                 s_keys[lp] = (KeyT)key[i];
                 if constexpr (kIdentityVals)
-                    s_vals[lp] = t0 + (uint32_t)wave * (kSortItems * kWave) + (uint32_t)(i * kWave + lane);
+                    s_vals[lp] = t0 + (uint32_t)wave * (items * kWave) + (uint32_t)(i * kWave + lane);
                 else
                     s_vals[lp] = val[i];
             }
         }
-        if (t0 + kSortTile < hi) load_tile(t0 + kSortTile);
+        if (t0 + tile < hi) load_tile(t0 + tile);
         __syncthreads();
         const uint32_t nv = s_nv;
         for (uint32_t j = tid; j < nv; j += kBlock) {
@@ -670,50 +702,41 @@ void launch_radix_pass(const void *keys_in, const uint32_t *vals_in, void *keys_
                        uint32_t *hist, uint32_t *gsum, uint32_t *gsum_next, hipStream_t s, uint2 *run_ends,
                        uint32_t nruns, int key_bytes, const uint64_t *mask_in, uint64_t *mask_out, bool whole_key) {
     if (n_host == 0) return;
-    const unsigned nb = kSortBlocks;
     const bool k16 = key_bytes == 2;
-    const uint32_t *k32i = static_cast<const uint32_t *>(keys_in);
-    const uint16_t *k16i = static_cast<const uint16_t *>(keys_in);
     const bool wide = bits > kRadixBits;  // a 9-bit digit: 16-bit keys with a payload only
-    if (k16 && wide)
-        hipLaunchKernelGGL((k_radix_upsweep<false, uint16_t, kRadixBitsMax>), dim3(nb), dim3(kBlock), 0, s, k16i,
-                           n_host, n_dev, shift, bits, hist, gsum);
-    else if (k16)
-        hipLaunchKernelGGL((k_radix_upsweep<false, uint16_t>), dim3(nb), dim3(kBlock), 0, s, k16i, n_host, n_dev,
-                           shift, bits, hist, gsum);
-    else if (filter)
-        hipLaunchKernelGGL((k_radix_upsweep<true, uint32_t>), dim3(nb), dim3(kBlock), 0, s, k32i, n_host, n_dev,
-                           shift, bits, hist, gsum);
-    else
-        hipLaunchKernelGGL((k_radix_upsweep<false, uint32_t>), dim3(nb), dim3(kBlock), 0, s, k32i, n_host, n_dev,
-                           shift, bits, hist, gsum);
     const bool ident = vals_in == nullptr;
     uint32_t *ends = reinterpret_cast<uint32_t *>(run_ends);
-#define FGS_DS(I, F, K, T)                                                                                          \
-    hipLaunchKernelGGL((k_radix_downsweep<I, F, K, T>), dim3(nb), dim3(kBlock), 0, s, static_cast<const T *>(keys_in), \
-                       vals_in, static_cast<T *>(keys_out), vals_out, n_host, n_dev, shift, bits, hist, gsum,         \
-                       gsum_next, ends, nruns, nullptr, nullptr, nullptr)
-#define FGS_DSP(K, DB)                                                                                              \
-    hipLaunchKernelGGL((k_radix_downsweep<true, false, K, uint16_t, true, DB>), dim3(nb), dim3(kBlock), 0, s,     \
-                       static_cast<const uint16_t *>(keys_in), vals_in, static_cast<uint16_t *>(keys_out), vals_out,   \
-                       n_host, n_dev, shift, bits, hist, gsum, gsum_next, whole_key ? nullptr : ends, nruns, mask_in,  \
-                       mask_out, whole_key ? ends : nullptr)
+    // (never more workgroups than 1024-key tiles)
+    const uint32_t tiles = (n_host + kBlock * kItemStep - 1) / (kBlock * kItemStep);
+    const unsigned nb = tiles < (uint32_t)kSortBlocks ? tiles : (unsigned)kSortBlocks;
+#define FGS_US(F, T, DB)                                                                                            \
+    hipLaunchKernelGGL((k_radix_upsweep<F, T, DB>), dim3(nb), dim3(kBlock), 0, s, static_cast<const T *>(keys_in),    \
+                       n_host, n_dev, shift, bits, hist, gsum)
+    if (k16 && wide) FGS_US(false, uint16_t, kRadixBitsMax);
+    else if (k16) FGS_US(false, uint16_t, kRadixBits);
+    else if (filter) FGS_US(true, uint32_t, kRadixBits);
+    else FGS_US(false, uint32_t, kRadixBits);
+#undef FGS_US
+#define FGS_DS(I, F, K, T, P, DB)                                                                                   \
+    hipLaunchKernelGGL((k_radix_downsweep<I, F, K, T, P, DB>), dim3(nb), dim3(kBlock), 0, s,                         \
+                       static_cast<const T *>(keys_in), vals_in, static_cast<T *>(keys_out), vals_out, n_host, n_dev,  \
+                       shift, bits, hist, gsum, gsum_next, P && whole_key ? nullptr : ends, nruns,                    \
+                       P ? mask_in : nullptr, P ? mask_out : nullptr, P && whole_key ? ends : nullptr)
     // 16-bit keys with a payload: the super-tile passes (one 9-bit pass
     // sorts up to 512 super-tiles)
-    if (k16 && mask_in && wide && write_keys) FGS_DSP(true, kRadixBitsMax);
-    else if (k16 && mask_in && wide) FGS_DSP(false, kRadixBitsMax);
-    else if (k16 && mask_in && write_keys) FGS_DSP(true, kRadixBits);
-    else if (k16 && mask_in) FGS_DSP(false, kRadixBits);
+    if (k16 && mask_in && wide && write_keys) FGS_DS(true, false, true, uint16_t, true, kRadixBitsMax);
+    else if (k16 && mask_in && wide) FGS_DS(true, false, false, uint16_t, true, kRadixBitsMax);
+    else if (k16 && mask_in && write_keys) FGS_DS(true, false, true, uint16_t, true, kRadixBits);
+    else if (k16 && mask_in) FGS_DS(true, false, false, uint16_t, true, kRadixBits);
     // 16-bit keys: unfiltered, explicit values
-    else if (k16 && write_keys) FGS_DS(false, false, true, uint16_t);
-    else if (k16) FGS_DS(false, false, false, uint16_t);
-    else if (ident && filter && write_keys) FGS_DS(true, true, true, uint32_t);
-    else if (!ident && !filter && write_keys) FGS_DS(false, false, true, uint32_t);
-    else if (!ident && !filter && !write_keys) FGS_DS(false, false, false, uint32_t);
-    else if (ident && !filter && write_keys) FGS_DS(true, false, true, uint32_t);
-    else FGS_DS(false, true, true, uint32_t);
+    else if (k16 && write_keys) FGS_DS(false, false, true, uint16_t, false, kRadixBits);
+    else if (k16) FGS_DS(false, false, false, uint16_t, false, kRadixBits);
+    else if (ident && filter && write_keys) FGS_DS(true, true, true, uint32_t, false, kRadixBits);
+    else if (!ident && !filter && write_keys) FGS_DS(false, false, true, uint32_t, false, kRadixBits);
+    else if (!ident && !filter && !write_keys) FGS_DS(false, false, false, uint32_t, false, kRadixBits);
+    else if (ident && !filter && write_keys) FGS_DS(true, false, true, uint32_t, false, kRadixBits);
+    else FGS_DS(false, true, true, uint32_t, false, kRadixBits);
 #undef FGS_DS
-#undef FGS_DSP
 }
 
 void launch_count_scan(const uint32_t *order, const uint8_t *count8, const uint4 *erec, uint32_t n_host,
