@@ -46,19 +46,21 @@ __device__ __forceinline__ void block_range(uint32_t n, uint32_t b, uint32_t nb,
 }
 
 // Keys per thread in one tile of a sort pass over n keys: the smallest of 4, 8,
-// 12 and 16 with which one tile per workgroup is enough, so that a pass over
-// few keys spreads over the chip instead of over n / 4096 workgroups.  The
-// ranking is a serial chain per key of a wavefront, and a tile of 1024 keys has
-// a quarter of the chain of a tile of 4096; beyond kSortBlocks x 4096 keys the
-// large tiles' longer digit runs (fewer partial lines in the scatter) stay.
-// With tiles of 4096 keys throughout, a depth pass over 10,000 keys took
-// 12 us, now 7 (200,000: 14, now 8; 1M: 14.5, now 12.6), the super-tile pass
-// over eval-size frames' 0.6M entries 30 us, now 9.3.
+// 12 and 16 with which the workgroups' fewest rounds of tiles are enough.  Up
+// to kSortBlocks x 4096 keys that is one tile each, so that a pass over few
+// keys spreads over the chip instead of over n / 4096 workgroups (the ranking
+// is a serial chain per key of a wavefront: a tile of 1024 keys has a quarter
+// of the chain of a tile of 4096); beyond, every workgroup gets about the same
+// number of keys instead of some one tile of 4096 more than others.  With tiles
+// of 4096 keys throughout, a depth pass over 10,000 keys took 12 us, now 7
+// (200,000: 14, now 8; 1M: 14.5, now 12.6); the super-tile pass over 0.23M
+// entries 30 us, now 9.3; the two over 8.6M entries 141 + 114, now 110 + 91.
 constexpr uint32_t kItemStep = 4;
 static_assert(kSortItems % kItemStep == 0, "whole steps");
 __device__ __forceinline__ uint32_t tile_items(uint32_t n, uint32_t nb) {
+    const uint32_t rounds = n / (nb * (uint32_t)kSortTile) + 1u;
     uint32_t items = kItemStep;
-    while (items < (uint32_t)kSortItems && n > nb * (kBlock * items)) items += kItemStep;
+    while (items < (uint32_t)kSortItems && n > rounds * nb * (kBlock * items)) items += kItemStep;
     return items;
 }
 
@@ -155,13 +157,12 @@ __global__ __launch_bounds__(kBlock) void k_radix_upsweep(const KeyT *__restrict
 static_assert(kSortBlocks % kSortGroup == 0, "whole groups of workgroups");
 
 // (LDS holds four workgroups per CU, so registers are capped at what four
-// waves per SIMD allow; a 9-bit pass, whose digit bookkeeping needs more,
-// at what three allow.)
+// waves per SIMD allow.)
 // kPayload: the values are the input positions while ranking (as with
 // kIdentityVals), and each element's payload (vals_in, mask_in at that
 // position, inside the workgroup's tile) is read when it is stored.
 template <bool kIdentityVals, bool kFilter, bool kWriteKeys, class KeyT, bool kPayload = false, int kDB = kRadixBits>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kRadixBits ? 3 : 4))) void k_radix_downsweep(const KeyT *__restrict__ keys_in,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_radix_downsweep(const KeyT *__restrict__ keys_in,
                                                             const uint32_t *__restrict__ vals_in,
                                                             KeyT *__restrict__ keys_out,
                                                             uint32_t *__restrict__ vals_out, uint32_t n_host,
@@ -209,31 +210,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kR
 #pragma unroll
         for (int q = 0; q < kP; ++q) dtot[q] = dbefore[q] = 0;
         // the group sums of the thread's digits, then the earlier rows of its
-        // group (each phase's loads issued together)
-        {
-            uint32_t gv[kGroups][kP];
+        // group (kStep rows' loads issued together)
+        constexpr uint32_t kStep = 32 / kP;
+        static_assert(kGroups % kStep == 0 && kSortGroup % kStep == 0, "whole steps of rows");
+#pragma unroll 1
+        for (uint32_t w0 = 0; w0 < kGroups; w0 += kStep) {
+            uint32_t gv[kStep][kP];
 #pragma unroll
-            for (uint32_t w = 0; w < kGroups; ++w)
+            for (uint32_t w = 0; w < kStep; ++w)
 #pragma unroll
-                for (int q = 0; q < kP; ++q) gv[w][q] = gsum[(size_t)w * kR + tid * kP + q];
+                for (int q = 0; q < kP; ++q) gv[w][q] = gsum[(size_t)(w0 + w) * kR + tid * kP + q];
 #pragma unroll
-            for (uint32_t w = 0; w < kGroups; ++w)
+            for (uint32_t w = 0; w < kStep; ++w)
 #pragma unroll
                 for (int q = 0; q < kP; ++q) {
                     dtot[q] += gv[w][q];
-                    dbefore[q] += (w < mygroup) ? gv[w][q] : 0u;
+                    dbefore[q] += (w0 + w < mygroup) ? gv[w][q] : 0u;
                 }
         }
-        {
-            uint32_t hv[kSortGroup][kP];
+#pragma unroll 1
+        for (uint32_t r0 = 0; r0 < (uint32_t)kSortGroup; r0 += kStep) {
+            uint32_t hv[kStep][kP];
 #pragma unroll
-            for (uint32_t r = 0; r < (uint32_t)kSortGroup; ++r) {
-                const uint32_t row = mygroup * kSortGroup + r;
+            for (uint32_t r = 0; r < kStep; ++r) {
+                const uint32_t row = mygroup * kSortGroup + r0 + r;
 #pragma unroll
                 for (int q = 0; q < kP; ++q) hv[r][q] = row < b ? hist[(size_t)row * kR + tid * kP + q] : 0u;
             }
 #pragma unroll
-            for (uint32_t r = 0; r < (uint32_t)kSortGroup; ++r)
+            for (uint32_t r = 0; r < kStep; ++r)
 #pragma unroll
                 for (int q = 0; q < kP; ++q) dbefore[q] += hv[r][q];
         }
@@ -359,25 +364,47 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDB > kR
         if (t0 + tile < hi) load_tile(t0 + tile);
         __syncthreads();
         const uint32_t nv = s_nv;
-        for (uint32_t j = tid; j < nv; j += kBlock) {
-            const uint32_t k = s_keys[j];
-            const uint32_t d = (k >> shift) & dmask;
-            const uint32_t gpos = s_gbase[d] + j;
-            if (gpos < n) {  // never leave the output (n bounds the scattered count)
-                if (kWriteKeys) keys_out[gpos] = (KeyT)k;
-                if constexpr (kPayload) {
-                    const uint32_t src = s_vals[j];  // < hi: an element of this tile
-                    vals_out[gpos] = vals_in[src];
-                    mask_out[gpos] = mask_in[src];
-                } else {
-                    vals_out[gpos] = s_vals[j];
-                }
-                // last pass of a sort by the whole key: the keys of one
-                // digit run of this tile are in key order, so the first and
-                // last element of each key's stretch may start and end its run
-                if (run_end && k < nruns) {
-                    if (j == 0 || s_keys[j - 1] != k) atomicMin(&run_end[2 * (size_t)k], gpos);
-                    if (j + 1 == nv || s_keys[j + 1] != k) atomicMax(&run_end[2 * (size_t)k + 1], gpos + 1);
+        // (eight elements with a payload per thread at a time: their payload
+        // loads, whose latency this loop would otherwise wait for once per
+        // element, are in flight together: 9-bit pass over 5.0M entries 74 us,
+        // with four 65, with eight 61.5; without a payload one at a time is
+        // no slower)
+        constexpr int kOut = kPayload ? 8 : 1;
+        for (uint32_t j0 = tid; j0 < nv; j0 += kOut * kBlock) {
+            uint32_t k[kOut], src[kOut], gpos[kOut];
+#pragma unroll
+            for (int e = 0; e < kOut; ++e) {
+                const uint32_t j = j0 + (uint32_t)(e * kBlock), jc = j < nv ? j : nv - 1;
+                k[e] = s_keys[jc];
+                src[e] = s_vals[jc];
+                const uint32_t g = s_gbase[(k[e] >> shift) & dmask] + jc;
+                // never leave the output (n bounds the scattered count)
+                gpos[e] = j < nv && g < n ? g : 0xffffffffu;
+            }
+            uint64_t m[kPayload ? kOut : 1];
+            if constexpr (kPayload) {
+                // (src < hi: an element of this tile)
+                uint32_t v[kOut];
+#pragma unroll
+                for (int e = 0; e < kOut; ++e) v[e] = vals_in[src[e]];
+#pragma unroll
+                for (int e = 0; e < kOut; ++e) m[e] = mask_in[src[e]];
+#pragma unroll
+                for (int e = 0; e < kOut; ++e) src[e] = v[e];
+            }
+#pragma unroll
+            for (int e = 0; e < kOut; ++e) {
+                if (gpos[e] == 0xffffffffu) continue;
+                if (kWriteKeys) keys_out[gpos[e]] = (KeyT)k[e];
+                vals_out[gpos[e]] = src[e];
+                if constexpr (kPayload) mask_out[gpos[e]] = m[e];
+                // last pass of a sort by the whole key: the keys of one digit
+                // run of this tile are in key order, so the first and last
+                // element of each key's stretch may start and end its run
+                if (run_end && k[e] < nruns) {
+                    const uint32_t j = j0 + (uint32_t)(e * kBlock);
+                    if (j == 0 || s_keys[j - 1] != k[e]) atomicMin(&run_end[2 * (size_t)k[e]], gpos[e]);
+                    if (j + 1 == nv || s_keys[j + 1] != k[e]) atomicMax(&run_end[2 * (size_t)k[e] + 1], gpos[e] + 1);
                 }
             }
         }
