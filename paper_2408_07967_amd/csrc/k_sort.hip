@@ -278,8 +278,25 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_starts(uint2 *__restrict__ 
     }
 }
 
+// A wavefront's pairs of one stretch of a chunk, tile by tile, before they are
+// written: (tile << 8) | entry.  One 32-entry word has at most 32 x 64.
+constexpr uint32_t kPairCap = 32 * kWave;
+static_assert(kListChunk <= 256 && kWave * 256 <= 65536, "tile and entry in 16 bits");
+constexpr int kListWords = 8;  // 32-entry words of a tile's column
+static_assert(kListChunk == 32 * kListWords, "four 64-entry blocks");
+
 // kBuf: values are stored through a buffer resource of ncap words, whose
 // range check drops a store past the end (byte offsets: ncap < 2^29).
+//
+// Bound by instruction issue.  With a ballot per (tile, 64 entries) a store
+// had 5 active lanes of 64 (4K, 10M Gaussians); here the masks are transposed,
+// lane j walks the entries that its tile j hits and lists them in LDS behind
+// the earlier tiles', and the list is then written by all lanes: one step per
+// 64 pairs, with about as many separate lines as it has tiles' runs.
+// 27.2M pairs of a 4K frame: 73 us before, 64 now; 76.7M of an 8K frame: 153,
+// now 142 (write requests of 64 bytes: 5.1M for 307 MB of pairs); 4.6M of a
+// 1080p frame: 25, now 18.  With a buffer of 4096 pairs per wavefront, i.e. four
+// instead of seven workgroups per CU, the 1080p frame took 21.5.
 template <bool kBuf>
 __global__ __launch_bounds__(kListBlock) void k_list_write(const uint2 *__restrict__ sranges, uint32_t ecap,
                                                            const uint32_t *__restrict__ cbase, uint32_t nsuper,
@@ -290,8 +307,17 @@ __global__ __launch_bounds__(kListBlock) void k_list_write(const uint2 *__restri
                                                            const uint32_t *__restrict__ pre,
                                                            const uint2 *__restrict__ ranges,
                                                            uint32_t *__restrict__ values, uint32_t ncap) {
+    __shared__ uint16_t s_pairs[kListBlock / kWave][kPairCap];
+    __shared__ uint32_t s_g[kListBlock / kWave][kListChunk];
+    __shared__ uint32_t s_delta[kListBlock / kWave][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    uint16_t *pairs = s_pairs[wv];
+    uint32_t *gl = s_g[wv], *delta = s_delta[wv];
+    auto lds_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     const uint32_t n = cbase[nsuper];
     const __amdgpu_buffer_rsrc_t vrs =
         __builtin_amdgcn_make_buffer_rsrc(values, (short)0, kBuf ? (int)(ncap * 4u) : 0, 0x00020000);
@@ -311,29 +337,85 @@ __global__ __launch_bounds__(kListBlock) void k_list_write(const uint2 *__restri
         }
         // lane j: the first output position of tile j (bit j) of this super-tile
         const int64_t t = lane_tile(s, stx, tiles_x, tiles_y, lane);
-        const uint32_t first = t >= 0 ? ranges[t].x + pre[(size_t)q * kWave + lane] : 0u;
-        // tile by tile: the chunk's four 64-entry blocks in order, the
-        // running position kept as a wavefront-uniform value
+        uint32_t first = t >= 0 ? ranges[t].x + pre[(size_t)q * kWave + lane] : 0u;
+        // lane j: the entries that hit tile j
+        constexpr int kBlocks = kListWords / 2;
+        uint32_t col[kListWords];
+        uint32_t c01 = 0, c23 = 0;  // the lane's hits in the 64-entry blocks, two per word
 #pragma unroll
-        for (int j = 0; j < kWave; ++j) {
-            uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)first, j);
+        for (int k = 0; k < kBlocks; ++k) {
+            gl[k * kWave + lane] = g[k];
+            const uint64_t c = transpose64(m[k], lane);
+            col[2 * k] = (uint32_t)c;
+            col[2 * k + 1] = (uint32_t)(c >> 32);
+            (k < 2 ? c01 : c23) += (uint32_t)__popcll(c) << (16 * (k & 1));
+        }
+        // the whole chunk at once where its pairs fit, else by halves, blocks
+        // or words (which always fit)
+        uint32_t b01 = c01, b23 = c23;
 #pragma unroll
-            for (int k = 0; k < (int)(kListChunk / kWave); ++k) {
-                const uint32_t w = j < 32 ? (uint32_t)m[k] : (uint32_t)(m[k] >> 32);
-                const bool hit = ((w >> (j & 31)) & 1u) != 0u;
-                const uint64_t bal = __ballot(hit);
-                if (bal) {  // uniform
-                    const uint32_t pos =
-                        base + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-                    if (hit) {
-                        if constexpr (kBuf)
-                            __builtin_amdgcn_raw_buffer_store_b32(g[k], vrs, pos * 4u, 0, 0);
-                        else if (pos < ncap)  // never leave the values
-                            values[pos] = g[k];
-                    }
-                    base += (uint32_t)__popcll(bal);
+        for (int d = 1; d < kWave; d <<= 1) {
+            b01 += (uint32_t)__shfl_xor((int)b01, d, kWave);
+            b23 += (uint32_t)__shfl_xor((int)b23, d, kWave);
+        }
+        b01 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b01);
+        b23 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b23);
+        const uint32_t p0 = b01 & 0xffffu, p1 = b01 >> 16, p2 = b23 & 0xffffu, p3 = b23 >> 16;
+        const uint32_t half = p0 + p1 > p2 + p3 ? p0 + p1 : p2 + p3;
+        const uint32_t q01 = p0 > p1 ? p0 : p1, q23 = p2 > p3 ? p2 : p3;
+        const int step = p0 + p1 + p2 + p3 <= kPairCap         ? 8
+                         : half <= kPairCap                    ? 4
+                         : (q01 > q23 ? q01 : q23) <= kPairCap ? 2
+                                                               : 1;
+        for (int w0 = 0; w0 < kListWords; w0 += step) {
+            uint32_t cnt = 0;
+#pragma unroll
+            for (int w = 0; w < kListWords; ++w)
+                if (w >= w0 && w < w0 + step) cnt += (uint32_t)__popc(col[w]);  // uniform
+            uint32_t x = cnt;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const uint32_t y = (uint32_t)__shfl_up((int)x, d, kWave);
+                if (lane >= d) x += y;
+            }
+            const uint32_t np = (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+            uint32_t p = x - cnt;
+            delta[lane] = first - p;
+            first += cnt;
+#pragma unroll
+            for (int w = 0; w < kListWords; ++w) {
+                if (w < w0 || w >= w0 + step) continue;  // uniform
+                uint32_t bits = col[w];
+                const uint32_t tag = ((uint32_t)lane << 8) | (uint32_t)(w * 32);
+                while (bits) {
+                    pairs[p++] = (uint16_t)(tag + (uint32_t)__builtin_ctz(bits));
+                    bits &= bits - 1u;
                 }
             }
+            lds_order();
+            constexpr uint32_t kOut = 4;
+            for (uint32_t i0 = (uint32_t)lane; i0 < np; i0 += kOut * kWave) {
+                uint32_t u[kOut], gv[kOut], pos[kOut];
+#pragma unroll
+                for (uint32_t k = 0; k < kOut; ++k) {
+                    const uint32_t i = i0 + k * kWave;
+                    u[k] = pairs[i < np ? i : i0];
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < kOut; ++k) {
+                    gv[k] = gl[u[k] & 255u];
+                    pos[k] = delta[u[k] >> 8] + i0 + k * kWave;
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < kOut; ++k) {
+                    if (i0 + k * kWave >= np) continue;
+                    if constexpr (kBuf)
+                        __builtin_amdgcn_raw_buffer_store_b32(gv[k], vrs, pos[k] * 4u, 0, 0);
+                    else if (pos[k] < ncap)  // never leave the values
+                        values[pos[k]] = gv[k];
+                }
+            }
+            lds_order();
         }
     }
 }
