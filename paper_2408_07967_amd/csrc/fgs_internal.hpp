@@ -191,8 +191,10 @@ unsigned emit_grid(uint32_t visible);
 // seg_count[workgroup]), and the preprocess runs over those lists only, taken
 // as one list of fc->ncand positions: every per-Gaussian output (gs, rect,
 // count, erec, dkey, chunk entries) of position i goes to index i, and the
-// Gaussian of position i to gmap[i].  Without a precompute the outputs are
-// indexed by Gaussian and gmap is unused.
+// Gaussian of position i to gmap[i].  Without a precompute gmap is unused and
+// the outputs of Gaussian g go to slot g, except that a frame that is not kept
+// (full 0) may pack them: slots in the order of the Gaussians, the slots of
+// Gaussians without outputs marked by kInvalidKey in dkey.
 // seg_count holds 2 kCullBlocks words: the candidate counts, then the
 // batches each cull workgroup read.
 constexpr int kCullBlocks = 2048;

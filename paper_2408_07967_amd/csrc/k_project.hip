@@ -439,6 +439,49 @@ __device__ __forceinline__ bool cull_keep(const float4 &p4, const float2 &b, con
     return front & !out;
 }
 
+// The parameters that a raw Gaussian's keep test reads.
+struct RawTerms {
+    float x, y, z, ls0, ls1, ls2, logit, qw, qx, qy, qz;
+};
+__device__ __forceinline__ RawTerms raw_terms(const DevScene &sc, int64_t g) {
+    const int64_t st = sc.stride;
+    return {sc.means[g],
+            sc.means[st + g],
+            sc.means[2 * st + g],
+            sc.log_scales[g],
+            sc.log_scales[st + g],
+            sc.log_scales[2 * st + g],
+            sc.logits[g],
+            sc.quats[g],
+            sc.quats[st + g],
+            sc.quats[2 * st + g],
+            sc.quats[3 * st + g]};
+}
+
+// The cull's keep test on raw parameters: false only for a Gaussian that the
+// projection would find invisible.  The covariance's trace is the sum of the
+// squared scales (the rotation keeps it), k^2 is bounded by its value at
+// opacity 1 (and by 9 where it is capped), and the opacity is above alpha_min
+// only if the logit is above alpha_min's.  The factors and the 0.01 cover the
+// rounding of the hardware's exponential and logarithm (about 1e-5 relative)
+// many times over; a NaN or an infinity in a bound keeps the Gaussian, one in
+// the mean or the logit drops it as the projection does.  A quaternion so small
+// that its squared norm has lost its precision is normalised to something that
+// is no rotation: it is kept.
+__device__ __forceinline__ bool raw_keep(const RawTerms &r, const DevCamera &cam, const DevOptions &op, int W,
+                                         int H) {
+    constexpr float kLog2e2 = 2.885390082f, kLn2 = 0.6931471806f;
+    const float trace = (exp2f(r.ls0 * kLog2e2) + exp2f(r.ls1 * kLog2e2)) + exp2f(r.ls2 * kLog2e2);
+    const float k2 = op.cap_3sigma ? 9.0f : -2.0f * kLn2 * log2f(op.alpha_min);
+    const float logit_min = kLn2 * log2f(op.alpha_min / (1.0f - op.alpha_min)) - 0.01f;
+    const bool dim = !isfinite(r.logit) | (r.logit < logit_min);
+    // (an opacity that passes: dim stands for it)
+    const float4 p4 = make_float4(r.x, r.y, r.z, __builtin_inff());
+    const float n2 = ((r.qw * r.qw + r.qx * r.qx) + r.qy * r.qy) + r.qz * r.qz;
+    const float t = n2 >= 1e-30f ? trace * 1.001f : __builtin_inff();
+    return !dim & cull_keep(p4, make_float2(t, k2 * 1.001f + 1e-3f), cam, op, W, H);
+}
+
 // Whether the cull would drop every member of a batch whose bounds are
 // (lo, hi, kx) (DevPrepared::blk), for one camera.  A member is dropped if
 // its opacity is at most alpha_min, its view depth is not past the near
@@ -711,7 +754,7 @@ struct PreArgs {
     int full;
     MultiOut mo;
 };
-template <bool kPrep, bool kMulti = false>
+template <bool kPrep, bool kMulti = false, bool kList = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_preprocess(PreArgs args_in_place) {
     (void)args_in_place;
     typedef const __attribute__((address_space(4))) PreArgs *ArgPtr;
@@ -722,6 +765,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     uint32_t *const gsum_clear = args.gsum_clear;
     const int64_t P = args.sc.P;
     static_assert(!kMulti || kPrep, "a batch walks a union candidate list");
+    static_assert(!kList || !kPrep, "a list of raw Gaussians");
     // the first depth pass's group sums start at zero
     if constexpr (kMulti) {
         for (int c = 0; c < mo.n; ++c)
@@ -895,9 +939,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             }
         }
     }
+    // Raw parameters: a wavefront takes a contiguous range of Gaussians, drops
+    // those that are certainly not visible before the projection (raw_keep) and
+    // projects the others up to 64 at a time, from a ring of two wavefronts'
+    // Gaussians and their parameters in LDS.  Unless the frame is kept (`full`),
+    // its outputs are packed: the range's output slots from the first on, in
+    // the Gaussians' order (so equal depths keep it), the rest marked invalid.
+    // Bound by HBM: 10M Gaussians of degree 3, 29 % visible, in 4K: 608 us for
+    // 2.4 GB read (nearly every line of every plane holds a visible Gaussian's
+    // element) and 0.25 GB written.  One pass over all Gaussians took 754: every
+    // wavefront ran the whole projection, and 48-byte records 29 % apart were
+    // written as partial lines.  Listed, but written to the Gaussians' own
+    // slots, with a group's survivors split over two projections: 790.
+    constexpr uint32_t kRing = 2 * kWave;
+    constexpr int kTerms = sizeof(RawTerms) / sizeof(float);
+    __shared__ uint32_t s_rg[kList ? kBlock / kWave : 1][kList ? kRing : 1];
+    __shared__ float s_rt[kList ? kBlock / kWave : 1][kList ? kTerms : 1][kList ? kRing : 1];
+    uint32_t n_queue = 0, n_whole = 0, q_head = 0;  // wave-uniform
+    uint32_t grp = 0, grp_end = 0, slot = 0;  // wave-uniform: groups left, next output slot
+    if constexpr (!kPrep) {
+        const uint64_t groups = (uint64_t)((P + kWave - 1) / kWave), nw = (uint64_t)gridDim.x * (kBlock / kWave);
+        const uint64_t w = (uint64_t)blockIdx.x * (kBlock / kWave) + (uint32_t)__builtin_amdgcn_readfirstlane(wv);
+        grp = (uint32_t)(groups * w / nw);
+        grp_end = (uint32_t)(groups * (w + 1) / nw);
+        slot = grp * (uint32_t)kWave;
+    }
+    RawTerms rt = {};
     // outputs of a prepared scene go to the candidate's list position (dense,
-    // contiguous per wavefront), of raw parameters to the Gaussian's index
-    int64_t batch = blockIdx.x;  // batch of 256 list positions (prepared) or Gaussians (raw)
+    // contiguous per wavefront)
+    int64_t batch = blockIdx.x;  // prepared: batch of 256 list positions
     for (;;) {
     ArgPtr batch_ptr = arg_ptr;
     asm volatile("" : "+s"(batch_ptr));
@@ -907,7 +977,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const DevOptions &op = ba.op;
     const bool full = ba.full != 0;
     int64_t g = P;
-    uint32_t ii = 0;  // prepared: position in the candidate list
+    uint32_t ii = 0;  // output slot (prepared: position in the candidate list)
     if constexpr (kPrep) {
         if ((uint64_t)batch * kBlock >= ncand) break;
         ii = (uint32_t)batch * kBlock + threadIdx.x;
@@ -922,11 +992,64 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             g = (int64_t)ba.cand[lo + (ii - s_pref[sg])];
         }
         batch += gridDim.x;
+    } else if constexpr (kList) {
+        while (n_queue < (uint32_t)kWave && grp < grp_end) {
+            const int64_t gi = (int64_t)grp * kWave + lane;
+            const bool in = gi < P;
+            const RawTerms t = raw_terms(sc, in ? gi : P - 1);
+            const bool keep = in && raw_keep(t, ba.cam, op, ba.W, ba.H);
+            if (full && in && !keep) {
+                ba.dkey[gi] = kInvalidKey;
+                ba.count8[gi] = 0;
+                ba.count[gi] = 0;
+            }
+            const uint64_t km = __ballot(keep);
+            if (keep) {
+                const uint32_t at = (__builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)km, n_queue)) +
+                                     q_head) % kRing;
+                s_rg[wv][at] = (uint32_t)gi;
+                const float *f = reinterpret_cast<const float *>(&t);
+#pragma unroll
+                for (int j = 0; j < kTerms; ++j) s_rt[wv][j][at] = f[j];
+            }
+            n_whole = n_queue;
+            n_queue += (uint32_t)__popcll(km);
+            ++grp;
+        }
+        if (n_queue == 0) break;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // whole groups only: a group's survivors share the lines of every
+        // coefficient plane
+        const uint32_t take = n_queue <= (uint32_t)kWave ? n_queue : n_whole;
+        {
+            const uint32_t at = (q_head + (uint32_t)lane) % kRing;
+            if ((uint32_t)lane < take) g = (int64_t)s_rg[wv][at];
+            float *f = reinterpret_cast<float *>(&rt);
+#pragma unroll
+            for (int j = 0; j < kTerms; ++j) f[j] = s_rt[wv][j][at];
+        }
+        q_head = (q_head + take) % kRing;
+        n_queue -= take;
+        if (!full) {
+            ii = slot + (uint32_t)lane;
+            slot += take;
+        } else {
+            ii = (uint32_t)g;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     } else {
-        if (batch * kBlock >= P) break;
-        const int64_t ii = batch * kBlock + threadIdx.x;
-        if (ii < P) g = ii;
-        batch += gridDim.x;
+        if (grp >= grp_end) break;
+        const int64_t i = (int64_t)grp * kWave + lane;
+        if (i < P) {
+            g = i;
+            rt = raw_terms(sc, g);
+        }
+        ii = (uint32_t)i;
+        ++grp;
+        slot = grp * (uint32_t)kWave;
     }
     const int ncams = kMulti ? ba.mo.n : 1;
     for (int ci = 0; ci < ncams; ++ci) {
@@ -957,9 +1080,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             mz = p4.z;
             po = p4.w;
         } else {
-            mx = sc.means[g];
-            my = sc.means[st + g];
-            mz = sc.means[2 * st + g];
+            mx = rt.x;
+            my = rt.y;
+            mz = rt.z;
         }
         const float *R = cm.R;
         // view transform (p_view)
@@ -984,14 +1107,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     qu[0] = c1.x; qu[1] = c1.y; qu[2] = c1.z; qu[3] = c1.w;
                 }
             } else {
-                const float logit = sc.logits[g];
+                const float logit = rt.logit;
                 o = (float)(1.0 / (1.0 + canon_exp(-(double)logit)));
                 // opacity prefilter (Alg. 4: opacity > 1/255)
                 if (o > op.alpha_min && isfinite(logit)) {
-                    const float ls0 = sc.log_scales[g], ls1 = sc.log_scales[st + g],
-                                ls2 = sc.log_scales[2 * st + g];
-                    const float q4[4] = {sc.quats[g], sc.quats[st + g], sc.quats[2 * st + g], sc.quats[3 * st + g]};
-                    ok = scale_rot(ls0, ls1, ls2, q4, s3, qu);
+                    const float q4[4] = {rt.qw, rt.qx, rt.qy, rt.qz};
+                    ok = scale_rot(rt.ls0, rt.ls1, rt.ls2, q4, s3, qu);
                     if (ok) k2 = extent_k2(o, op);
                 }
             }
@@ -1136,13 +1257,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             uint32_t cbase = w_nch;
             if constexpr (kMulti) cbase = s_nch[wv][ci];
             if (chunked) {
-                const uint32_t slot = w_nbig + (uint32_t)__popcll(bm & ((1ull << lane) - 1ull));
-                if constexpr (kMulti) s_bc[wv][slot] = (uint32_t)ci;
-                s_bg[wv][slot] = kPrep ? ii : (uint32_t)g;
-                s_bn[wv][slot] = nch;
-                s_bx[wv][slot] = (uint32_t)tx0 | ((uint32_t)tx1 << 16);
-                s_by[wv][slot] = (uint32_t)ty0 | ((uint32_t)ty1 << 16);
-                s_boff[wv][slot] = cbase + incl - nch;
+                const uint32_t at = w_nbig + (uint32_t)__popcll(bm & ((1ull << lane) - 1ull));
+                if constexpr (kMulti) s_bc[wv][at] = (uint32_t)ci;
+                s_bg[wv][at] = ii;
+                s_bn[wv][at] = nch;
+                s_bx[wv][at] = (uint32_t)tx0 | ((uint32_t)tx1 << 16);
+                s_by[wv][at] = (uint32_t)ty0 | ((uint32_t)ty1 << 16);
+                s_boff[wv][at] = cbase + incl - nch;
             }
             w_nbig += (uint32_t)__popcll(bm);
             const uint32_t tot = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
@@ -1197,7 +1318,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const uint32_t ents = valid ? super_span(tx0, tx1, ty0, ty1) : 0u;
     if (g < P) {
         const uint32_t key = valid ? __float_as_uint(tz) : kInvalidKey;
-        const int64_t oi = kPrep ? (int64_t)ii : g;  // output slot
+        const int64_t oi = (int64_t)ii;
         if constexpr (kPrep) {
             // the Gaussian of this list position, in the caller's indexing
             uint32_t *const gmap_c = kMulti ? ba.mo.c[ci].gmap : ba.gmap;
@@ -1252,6 +1373,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
     }  // camera loop
     }  // batch loop
+    if constexpr (!kPrep) {
+        // the range's slots without a projected Gaussian
+        const int64_t end = (int64_t)grp_end * kWave < P ? (int64_t)grp_end * kWave : P;
+        if (kList && args.full == 0)
+            for (int64_t i = (int64_t)slot + lane; i < end; i += kWave) args.dkey[i] = kInvalidKey;
+    }
     // The workgroup's visible and pair counts (of each camera) in one 64-bit
     // atomic: atomics on one line take about 8 ns each, one after the other,
     // and the wavefronts of a frame all end at about the same time.  With two
@@ -1735,7 +1862,12 @@ void launch_preprocess(const DevScene &sc, const DevPrepared *pp, const DevCamer
                     MultiOut{}};
     if (pp)
         hipLaunchKernelGGL(k_preprocess<true>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
+    else if ((int64_t)preprocess_grid(sc.P) * kBlock < sc.P)
+        hipLaunchKernelGGL((k_preprocess<false, false, true>), dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
     else
+        // every wavefront has one group of 64: there is nothing to merge, and
+        // the list's test and its code would only add their latency (10,000
+        // Gaussians: 12.7 us with both forms in one kernel, 11.7 with this one)
         hipLaunchKernelGGL(k_preprocess<false>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
 }
 
