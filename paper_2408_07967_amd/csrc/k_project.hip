@@ -883,8 +883,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // A prepared scene walks the cull's candidates as one list: the exclusive
     // prefix of the segment counts maps a list position to its segment, and
     // workgroups take 256-position batches in turn, so every workgroup gets
-    // the same share whatever the segment sizes.  Raw parameters walk every
-    // Gaussian.  g = sc.P marks an idle lane.
+    // the same share whatever the segment sizes.  g = sc.P marks an idle lane.
     static_assert((kCullBlocks & (kCullBlocks - 1)) == 0 && kCullBlocks % kBlock == 0, "segment prefix layout");
     __shared__ uint32_t s_pref[kPrep ? kCullBlocks : 1];
     __shared__ uint32_t s_wtot[kBlock / kWave];

@@ -103,21 +103,33 @@ __device__ __forceinline__ ChunkWalk chunk_walk(uint32_t n, uint32_t wave_in_blo
 }
 
 constexpr int kListBlock = 256;  // chunk kernels: four wavefronts, one chunk each at a time
-constexpr int kScanBlock = 1024;
+// (The scans' workgroups are of four wavefronts too: one of sixteen starts only
+// where a CU has sixteen free wave slots at once, and beside another frame's
+// blend, whose small workgroups take every slot that falls free, k_list_scan
+// waited up to 290 us and k_tile_starts 270: four cameras in one batch, average
+// 42 and 79 us, now 28 and 27.)
+constexpr int kScanBlock = 256;
+constexpr int kScanWaves = kScanBlock / kWave;
+constexpr uint32_t kChunkBlocks = 16;  // workgroups of k_list_chunks, at most
 
 // cbase[s] = first chunk of super-tile s (cbase[nsuper] = the total), and
-// csuper[q] = the super-tile of chunk q.
+// csuper[q] = the super-tile of chunk q.  Every workgroup scans all super-tiles
+// (a few thousand ranges in L2) and writes the bases and the chunks of its
+// share of them: no workgroup waits for another one.
 __global__ __launch_bounds__(kScanBlock) void k_list_chunks(const uint2 *__restrict__ sranges, uint32_t nsuper,
-                                                            uint32_t ecap, uint32_t *__restrict__ cbase,
+                                                            uint32_t ecap, uint32_t *cbase,
                                                             uint32_t *__restrict__ csuper,
                                                             uint32_t *__restrict__ rowsum) {
-    __shared__ uint32_t s_w[kScanBlock / kWave];
+    __shared__ uint32_t s_w[kScanWaves];
     const uint32_t tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint32_t b_lo = (uint32_t)((uint64_t)nsuper * blockIdx.x / gridDim.x);
+    const uint32_t b_hi = (uint32_t)((uint64_t)nsuper * (blockIdx.x + 1) / gridDim.x);
     const uint32_t run = (nsuper + kScanBlock - 1) / kScanBlock;
     const uint32_t s0 = tid * run < nsuper ? tid * run : nsuper;
     const uint32_t s1 = s0 + run < nsuper ? s0 + run : nsuper;
     uint32_t own = 0;
+#pragma unroll 8
     for (uint32_t s = s0; s < s1; ++s) {
         const uint2 r = super_entries(sranges, s, ecap);
         own += (r.y - r.x + kListChunk - 1) / kListChunk;
@@ -130,30 +142,28 @@ __global__ __launch_bounds__(kScanBlock) void k_list_chunks(const uint2 *__restr
     }
     if (lane == kWave - 1) s_w[wave] = x;
     __syncthreads();
-    uint32_t base = x - own, total = 0;
-    for (int q = 0; q < kScanBlock / kWave; ++q) {
-        base += q < wave ? s_w[q] : 0u;
-        total += s_w[q];
-    }
-    for (uint32_t s = s0; s < s1; ++s) {
-        const uint2 r = super_entries(sranges, s, ecap);
-        cbase[s] = base;
-        rowsum[s] = 0;  // (the rows of super-tiles are at most nsuper)
-        base += (r.y - r.x + kListChunk - 1) / kListChunk;
-    }
-    if (tid == 0) cbase[nsuper] = total;
+    uint32_t base = x - own;
+    for (int q = 0; q < kScanWaves; ++q) base += q < wave ? s_w[q] : 0u;
+    // (the share's end, too: its last chunk ends there)
+    if (s0 <= b_hi && s1 >= b_lo)
+        for (uint32_t s = s0; s < s1; ++s) {
+            const uint2 r = super_entries(sranges, s, ecap);
+            if (s >= b_lo && s <= b_hi) cbase[s] = base;
+            if (s >= b_lo && s < b_hi) rowsum[s] = 0;  // (the rows of super-tiles are at most nsuper)
+            base += (r.y - r.x + kListChunk - 1) / kListChunk;
+        }
+    if (b_hi == nsuper && tid == kScanBlock - 1) cbase[nsuper] = base;
     __syncthreads();  // (and the bases are visible to the workgroup)
-    // the super-tile of every chunk: a wavefront takes its share of up to 64
+    // the super-tile of every chunk: a wavefront takes up to 64 of the share's
     // super-tiles and fills one's chunks after the other with all its lanes
     // (one thread per super-tile, a dense one's hundreds of chunks in turn,
-    // took the kernel 19.0 us at 4K with 10M Gaussians and 6.2 at 1080p with 1M;
-    // now 8.5 and 4.6)
-    constexpr uint32_t kWaves = kScanBlock / kWave;
-    uint32_t share = (nsuper + kWaves - 1) / kWaves;
+    // took the kernel 19.0 us at 4K with 10M Gaussians and 21.7 at 8K; filled by
+    // the sixteen wavefronts of one workgroup 8.1 and 19.1; now 5.9 and 9.5)
+    uint32_t share = (b_hi - b_lo + kScanWaves - 1) / kScanWaves;
     share = share < (uint32_t)kWave ? share : (uint32_t)kWave;
-    for (uint32_t b0 = (uint32_t)wave * share; b0 < nsuper; b0 += kWaves * share) {
+    for (uint32_t b0 = b_lo + (uint32_t)wave * share; b0 < b_hi; b0 += kScanWaves * share) {
         const uint32_t s = b0 + (uint32_t)lane;
-        const bool mine = (uint32_t)lane < share && s < nsuper;
+        const bool mine = (uint32_t)lane < share && s < b_hi;
         const uint32_t lo = mine ? cbase[s] : 0u, hi = mine ? cbase[s + 1] : 0u;
         for (uint32_t j = 0; j < share; ++j) {
             const uint32_t c1 = (uint32_t)__builtin_amdgcn_readlane((int)hi, (int)j);
@@ -195,29 +205,37 @@ __global__ __launch_bounds__(kListBlock) void k_list_count(const uint2 *__restri
 __global__ __launch_bounds__(kScanBlock) void k_list_scan(const uint32_t *__restrict__ cbase, uint32_t stx,
                                                           int tiles_x, int tiles_y, uint32_t *__restrict__ cnt,
                                                           uint2 *__restrict__ ranges, uint32_t *__restrict__ rowsum) {
-    constexpr int kWaves = kScanBlock / kWave;
-    __shared__ uint32_t s_sum[kWaves][kWave];
+    constexpr uint32_t kStep = 8;  // chunks whose counts are read together
+    __shared__ uint32_t s_sum[kScanWaves][kWave];
     const uint32_t s = blockIdx.x;
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const uint32_t c0 = cbase[s], n = cbase[s + 1] - c0;
-    const uint32_t per = (n + kWaves - 1) / kWaves;
+    const uint32_t per = (n + kScanWaves - 1) / kScanWaves;
     const uint32_t r0 = c0 + (w * per < n ? w * per : n), r1 = c0 + ((w + 1) * per < n ? (w + 1) * per : n);
     uint32_t sum = 0;
-    for (uint32_t q = r0; q < r1; ++q) sum += cnt[(size_t)q * kWave + lane];
+    for (uint32_t q = r0; q < r1; q += kStep) {
+#pragma unroll
+        for (uint32_t k = 0; k < kStep; ++k) sum += q + k < r1 ? cnt[(size_t)(q + k) * kWave + lane] : 0u;
+    }
     s_sum[w][lane] = sum;
     __syncthreads();
     uint32_t run = 0, tot = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < (uint32_t)kWaves; ++k) {
+    for (uint32_t k = 0; k < (uint32_t)kScanWaves; ++k) {
         const uint32_t v = s_sum[k][lane];
         run += k < w ? v : 0u;
         tot += v;
     }
-    for (uint32_t q = r0; q < r1; ++q) {
-        const uint32_t v = cnt[(size_t)q * kWave + lane];
-        cnt[(size_t)q * kWave + lane] = run;
-        run += v;
+    for (uint32_t q = r0; q < r1; q += kStep) {
+        uint32_t v[kStep];
+#pragma unroll
+        for (uint32_t k = 0; k < kStep; ++k) v[k] = q + k < r1 ? cnt[(size_t)(q + k) * kWave + lane] : 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < kStep; ++k) {
+            if (q + k < r1) cnt[(size_t)(q + k) * kWave + lane] = run;
+            run += v[k];
+        }
     }
     if (w == 0) {
         const int64_t t = lane_tile(s, stx, tiles_x, tiles_y, lane);
@@ -231,10 +249,12 @@ __global__ __launch_bounds__(kScanBlock) void k_list_scan(const uint32_t *__rest
 
 // Workgroup b: the tiles of super-tile row b (tile rows kSuper b ...
 // kSuper b + kSuper - 1, a contiguous range of tile ids).  Its first start is
-// the sum of the earlier rows; its tiles are scanned kScanBlock at a time.
+// the sum of the earlier rows; its tiles are scanned 1024 at a time, four
+// consecutive ones per thread.
 __global__ __launch_bounds__(kScanBlock) void k_tile_starts(uint2 *__restrict__ ranges, int tiles_x, uint32_t ntiles,
                                                             const uint32_t *__restrict__ rowsum, uint32_t ncap) {
-    __shared__ uint32_t s_w[kScanBlock / kWave];
+    constexpr uint32_t kPer = 4;
+    __shared__ uint32_t s_w[kScanWaves];
     __shared__ uint32_t s_base;
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
@@ -249,10 +269,14 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_starts(uint2 *__restrict__ 
     uint32_t start = s_base;
     const uint32_t band = (uint32_t)kSuper * (uint32_t)tiles_x;
     const uint32_t t_lo = b * band, t_hi = t_lo + band < ntiles ? t_lo + band : ntiles;
-    for (uint32_t r0 = t_lo; r0 < t_hi; r0 += kScanBlock) {
-        const uint32_t t = r0 + tid;
-        const uint32_t c = t < t_hi ? ranges[t].x : 0u;
-        uint32_t x = c;
+    for (uint32_t r0 = t_lo; r0 < t_hi; r0 += kScanBlock * kPer) {
+        const uint32_t t = r0 + tid * kPer;
+        uint32_t c[kPer], own = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k) c[k] = t + k < t_hi ? ranges[t + k].x : 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k) own += c[k];
+        uint32_t x = own;
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
             const uint32_t y = (uint32_t)__shfl_up((int)x, d, kWave);
@@ -262,17 +286,21 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_starts(uint2 *__restrict__ 
         __syncthreads();
         uint32_t before = 0, all = 0;
 #pragma unroll
-        for (int q = 0; q < kScanBlock / kWave; ++q) {
+        for (int q = 0; q < kScanWaves; ++q) {
             const uint32_t v = s_w[q];
             before += q < wave ? v : 0u;
             all += v;
         }
         __syncthreads();
-        const uint32_t a0 = start + before + x - c;
-        if (t < t_hi) {
-            const uint32_t a = a0 < ncap ? a0 : ncap;
-            const uint32_t e = a0 + c < ncap ? a0 + c : ncap;
-            ranges[t] = make_uint2(a, e);
+        uint32_t a0 = start + before + x - own;
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k) {
+            if (t + k < t_hi) {
+                const uint32_t a = a0 < ncap ? a0 : ncap;
+                const uint32_t e = a0 + c[k] < ncap ? a0 + c[k] : ncap;
+                ranges[t + k] = make_uint2(a, e);
+            }
+            a0 += c[k];
         }
         start += all;
     }
@@ -450,7 +478,8 @@ void launch_tile_lists(int W, int H, const uint2 *sranges, const uint32_t *gidx,
     // chunk grids: four chunks per workgroup, at most a few resident rounds,
     // a multiple of eight workgroups (every XCD's range has workgroups)
     const unsigned chunk_blocks = (unsigned)((std::min<size_t>((g + 3) / 4, 8192) + 7) / 8 * 8);
-    hipLaunchKernelGGL(k_list_chunks, dim3(1), dim3(kScanBlock), 0, s, sranges, nsuper, ecap, cbase, csuper, rowsum);
+    hipLaunchKernelGGL(k_list_chunks, dim3(std::min<uint32_t>((nsuper + 15) / 16, kChunkBlocks)), dim3(kScanBlock), 0, s,
+                       sranges, nsuper, ecap, cbase, csuper, rowsum);
     hipLaunchKernelGGL(k_list_count, dim3(chunk_blocks), dim3(kListBlock), 0, s, sranges, ecap, cbase, nsuper, csuper,
                        smask, cnt);
     hipLaunchKernelGGL(k_list_scan, dim3(nsuper), dim3(kScanBlock), 0, s, cbase, stx, tiles_x, tiles_y, cnt, ranges,
