@@ -16,6 +16,7 @@ constexpr int kRadix = 1 << kRadixBits;
 constexpr int kRadixBitsMax = 9;  // a single pass may take a 9-bit digit
 constexpr int kRadixMax = 1 << kRadixBitsMax;
 constexpr uint32_t kInvalidKey = 0xffffffffu;
+constexpr uint32_t kSmallSort = 16384;  // keys that one workgroup sorts
 
 // Camera and options passed by value: they land in the kernel-argument
 // segment and are read through scalar registers (the paper's constant-memory
@@ -333,7 +334,9 @@ void launch_tile_lists(int W, int H, const uint2 *sranges, const uint32_t *gidx,
 
 // One stable LSD radix pass of (key, value) pairs by the digit
 // (key >> shift) & ((1 << bits) - 1), bits <= kRadixBitsMax (9 only for
-// 16-bit keys with a payload).
+// 16-bit keys with a payload); or, with bits 32, the whole sort of at most
+// kSmallSort 32-bit keys by one workgroup (filtered, vals_in null, keys_out
+// used only with write_keys and then possibly keys_in; no scratch).
 //   n_host  upper bound on the number of keys; n_dev: if non-null, the
 //           actual count is read there on the device
 //   vals_in null: values are the input positions

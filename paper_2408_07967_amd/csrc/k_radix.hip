@@ -414,6 +414,228 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
 }
 
+// ---- the whole sort, and the scan, of a few keys in one workgroup -----------
+
+// A pass of the grid sort takes two launches of some 4 and 7 us, whatever the
+// number of keys; one workgroup holds up to kSmallSort keys in its registers and
+// LDS and does all passes there.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallWaves = kSmallBlock / kWave;
+constexpr int kSmallItems = 16;
+static_assert(kSmallSort == kSmallBlock * kSmallItems && kSmallSort <= 65536, "positions in 16 bits");
+
+// Exclusive scan of one value per thread over a 1024-thread workgroup.
+__device__ __forceinline__ uint32_t small_exclusive_scan(uint32_t v, uint32_t *s_tmp, uint32_t *total) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    uint32_t x = v;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)x, d, kWave);
+        if (lane >= d) x += y;
+    }
+    if (lane == kWave - 1) s_tmp[wave] = x;
+    __syncthreads();
+    uint32_t wpre = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        const uint32_t t = s_tmp[w];
+        wpre += (w < wave) ? t : 0u;
+        tot += t;
+    }
+    __syncthreads();
+    *total = tot;
+    return wpre + x - v;
+}
+
+// Stable sort of the valid keys (not kInvalidKey) by all 32 bits; values are the
+// input positions.  Each wavefront owns a contiguous stretch of the keys; a pass
+// ranks them as the grid sort does and exchanges them through LDS.  Digits that
+// all keys share (the keys are compared to the smallest one) take no pass: the
+// depths of a scene that spans less than a factor of four have at most 24 bits.
+//
+// Bound by the ranking's chain on one CU (about 0.4 us per key and lane).
+template <bool kWriteKeys>
+__global__ __launch_bounds__(kSmallBlock) void k_sort_small(const uint32_t *keys_in, uint32_t *keys_out,
+                                                            uint32_t *__restrict__ vals_out, uint32_t n_host,
+                                                            const uint32_t *n_dev) {
+    constexpr int kR = 1 << kRadixBits;
+    __shared__ uint32_t s_key[kSmallSort];
+    __shared__ uint16_t s_val[kSmallSort];
+    __shared__ uint16_t s_wave[kSmallWaves][kR];
+    __shared__ uint32_t s_base[kR];
+    __shared__ uint32_t s_tmp[kSmallWaves], s_lo[kSmallWaves], s_hi[kSmallWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint32_t n_in = count_of(n_host, n_dev);
+    // steps of 64 keys per wavefront, and a thread's element i of n elements
+    auto steps_of = [](uint32_t n) { return (n + kSmallBlock - 1) / kSmallBlock; };
+    uint32_t key[kSmallItems], val[kSmallItems];
+    // the valid keys, in order, to the front
+    uint32_t n = 0;
+    {
+        const uint32_t steps = steps_of(n_in);
+        const uint32_t b = (uint32_t)wave * steps * kWave + (uint32_t)lane;
+        uint32_t mine = 0, lo = kInvalidKey, hi = 0;
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            const uint32_t p = b + (uint32_t)(i * kWave);
+            key[i] = (uint32_t)i < steps && p < n_in ? keys_in[p] : kInvalidKey;
+        }
+        uint64_t bal[kSmallItems];
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            const bool ok = key[i] != kInvalidKey;
+            bal[i] = __ballot(ok);
+            mine += (uint32_t)__popcll(bal[i]);
+            lo = key[i] < lo ? key[i] : lo;
+            hi = ok && key[i] > hi ? key[i] : hi;
+        }
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t l = (uint32_t)__shfl_xor((int)lo, d, kWave), h = (uint32_t)__shfl_xor((int)hi, d, kWave);
+            lo = l < lo ? l : lo;
+            hi = h > hi ? h : hi;
+        }
+        if (lane == 0) {
+            s_tmp[wave] = mine;
+            s_lo[wave] = lo;
+            s_hi[wave] = hi;
+        }
+        __syncthreads();
+        uint32_t at = 0;
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) {
+            at += w < wave ? s_tmp[w] : 0u;
+            n += s_tmp[w];
+        }
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            if (key[i] != kInvalidKey) {
+                const uint32_t q = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[i] >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)bal[i], at));
+                s_key[q] = key[i];
+                s_val[q] = (uint16_t)(b + (uint32_t)(i * kWave));
+            }
+            at += (uint32_t)__popcll(bal[i]);
+        }
+    }
+    uint32_t lo = kInvalidKey, hi = 0;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        lo = s_lo[w] < lo ? s_lo[w] : lo;
+        hi = s_hi[w] > hi ? s_hi[w] : hi;
+    }
+    const uint32_t steps = steps_of(n);
+    const uint32_t b = (uint32_t)wave * steps * kWave + (uint32_t)lane;
+    const int bits = n ? 32 - __clz((int)((hi - lo) | 1u)) : 0;
+    for (int shift = 0; shift < bits; shift += kRadixBits) {
+        for (int i = tid; i < kSmallWaves * kR / 2; i += kSmallBlock) reinterpret_cast<uint32_t *>(&s_wave[0][0])[i] = 0;
+        __syncthreads();
+        uint32_t rank[kSmallItems];
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            if ((uint32_t)i >= steps) break;
+            const uint32_t p = b + (uint32_t)(i * kWave);
+            const bool ok = p < n;
+            key[i] = ok ? s_key[p] : kInvalidKey;
+            val[i] = ok ? s_val[p] : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            if ((uint32_t)i >= steps) break;
+            const bool ok = b + (uint32_t)(i * kWave) < n;
+            const uint32_t d = ((key[i] - lo) >> shift) & (kR - 1);
+            // lanes with the same digit (see k_radix_downsweep)
+            uint32_t diff_lo = 0, diff_hi = 0;
+#pragma unroll
+            for (int bb = 0; bb < kRadixBits; ++bb) {
+                uint32_t t;
+                asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(t) : "v"(d), "i"(bb));
+                const uint64_t m = __ballot(t != 0u);
+                diff_lo = __builtin_amdgcn_bitop3_b32(diff_lo, (uint32_t)m, t, 0xf6);
+                diff_hi = __builtin_amdgcn_bitop3_b32(diff_hi, (uint32_t)(m >> 32), t, 0xf6);
+            }
+            const uint64_t okm = __ballot(ok);
+            const uint32_t peers_lo = (uint32_t)okm & ~diff_lo, peers_hi = (uint32_t)(okm >> 32) & ~diff_hi;
+            const uint32_t before = __builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));
+            const uint32_t cnt = (uint32_t)__popc(peers_lo) + (uint32_t)__popc(peers_hi);
+            uint32_t prev = 0;
+            if (ok) prev = s_wave[wave][d];
+            if (ok && before == 0) s_wave[wave][d] = (uint16_t)(prev + cnt);
+            rank[i] = prev + before;
+        }
+        __syncthreads();
+        // thread d < kR: its digit's counts -> exclusive over wavefronts
+        uint32_t own = 0;
+        if (tid < kR) {
+#pragma unroll
+            for (int w = 0; w < kSmallWaves; ++w) {
+                const uint32_t c = s_wave[w][tid];
+                s_wave[w][tid] = (uint16_t)own;
+                own += c;
+            }
+        }
+        uint32_t all = 0;
+        const uint32_t ex = small_exclusive_scan(own, s_tmp, &all);
+        if (tid < kR) s_base[tid] = ex;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSmallItems; ++i) {
+            if ((uint32_t)i >= steps) break;
+            if (b + (uint32_t)(i * kWave) < n) {
+                const uint32_t d = ((key[i] - lo) >> shift) & (kR - 1);
+                const uint32_t q = s_base[d] + s_wave[wave][d] + rank[i];
+                s_key[q] = key[i];
+                s_val[q] = (uint16_t)val[i];
+            }
+        }
+        __syncthreads();
+    }
+    if (bits == 0) __syncthreads();
+    for (uint32_t q = tid; q < n; q += kSmallBlock) {
+        vals_out[q] = s_val[q];
+        if (kWriteKeys) keys_out[q] = s_key[q];
+    }
+}
+
+// The scan of k_scan_upsweep and k_scan_downsweep over up to kSmallSort entries.
+__global__ __launch_bounds__(kSmallBlock) void k_scan_small(const uint32_t *__restrict__ order,
+                                                            const uint8_t *__restrict__ count8,
+                                                            const uint4 *__restrict__ erec, uint32_t n_host,
+                                                            const uint32_t *n_dev, uint32_t *__restrict__ offsets,
+                                                            uint32_t *total) {
+    __shared__ uint32_t s_tmp[kSmallWaves];
+    const uint32_t n = count_of(n_host, n_dev);
+    const uint32_t per = (n + kSmallBlock - 1) / kSmallBlock, b = threadIdx.x * per;
+    uint32_t c[kSmallItems], own = 0;
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) c[k] = (uint32_t)k < per && b + k < n ? order[b + k] : kInvalidKey;
+    uint32_t g[kSmallItems];
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        g[k] = c[k];
+        c[k] = g[k] != kInvalidKey ? count8[g[k]] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        if (c[k] == kCount8Big) {  // a chunked rectangle (rare)
+            const uint4 r = erec[g[k]];
+            c[k] = super_span((int)(r.x & 0xffffu), (int)(r.x >> 16), (int)(r.y & 0xffffu), (int)(r.y >> 16));
+        }
+        own += c[k];
+    }
+    uint32_t all = 0;
+    uint32_t ex = small_exclusive_scan(own, s_tmp, &all);
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        if ((uint32_t)k < per && b + k < n) offsets[b + k] = ex;
+        ex += c[k];
+    }
+    if (threadIdx.x == 0) {
+        if (n) offsets[n] = all;
+        *total = all;
+    }
+}
+
 // ---- exclusive scan of per-Gaussian tile counts in depth order -------------
 
 // Workgroup ranges of the scan are whole 1024-entry tiles: the few million
@@ -729,6 +951,17 @@ void launch_radix_pass(const void *keys_in, const uint32_t *vals_in, void *keys_
                        uint32_t *hist, uint32_t *gsum, uint32_t *gsum_next, hipStream_t s, uint2 *run_ends,
                        uint32_t nruns, int key_bytes, const uint64_t *mask_in, uint64_t *mask_out, bool whole_key) {
     if (n_host == 0) return;
+    if (bits == 32) {
+        // the whole sort (unsigned 32-bit keys, identity values, at most kSmallSort)
+        if (write_keys)
+            hipLaunchKernelGGL(k_sort_small<true>, dim3(1), dim3(kSmallBlock), 0, s,
+                               static_cast<const uint32_t *>(keys_in), static_cast<uint32_t *>(keys_out), vals_out,
+                               n_host, n_dev);
+        else
+            hipLaunchKernelGGL(k_sort_small<false>, dim3(1), dim3(kSmallBlock), 0, s,
+                               static_cast<const uint32_t *>(keys_in), nullptr, vals_out, n_host, n_dev);
+        return;
+    }
     const bool k16 = key_bytes == 2;
     const bool wide = bits > kRadixBits;  // a 9-bit digit: 16-bit keys with a payload only
     const bool ident = vals_in == nullptr;
@@ -770,6 +1003,11 @@ void launch_count_scan(const uint32_t *order, const uint8_t *count8, const uint4
                        const uint32_t *n_dev, uint32_t *cs, uint32_t *sums, uint32_t *offsets, uint32_t *total,
                        hipStream_t s) {
     if (n_host == 0) return;
+    if (n_host <= kSmallSort) {
+        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kSmallBlock), 0, s, order, count8, erec, n_host, n_dev, offsets,
+                           total);
+        return;
+    }
     hipLaunchKernelGGL(k_scan_upsweep, dim3(kSortBlocks), dim3(kBlock), 0, s, order, count8, erec, n_host, n_dev, cs,
                        sums);
     hipLaunchKernelGGL(k_scan_downsweep, dim3(kSortBlocks), dim3(kBlock), 0, s, cs, n_host, n_dev, sums, offsets,
