@@ -41,6 +41,14 @@
 // of Sigma', Sigma' = T Sigma T^T + dilation I, T = J R_cam, Sigma = M M^T,
 // M = R(q / |q|) diag(exp(log-scale)), (u, v) and J from the camera-space
 // mean, opacity = sigmoid(logit), colour = max(0, SH . Y(d) + 1/2).
+// Bound by HBM: 1M Gaussians of degree 3 (94 % with gradients), 0.6 GB: 108 us.
+// It took 193 with the culled Gaussians' zeros in a branch of their own, so
+// that nearly every line of the 59 gradient planes was written twice, in parts,
+// and with the coefficients read one basis function at a time between the
+// stores (on gfx950 a wait for a load also waits for every earlier store); with
+// the coefficients read together 172.
+#include <type_traits>
+
 #include "fgs_internal.hpp"
 #include "blend_common.hpp"
 #include "sh_basis.hpp"
@@ -282,7 +290,13 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd(DevScene sc, DevCamer
                                                            const GaussState *__restrict__ gs,
                                                            const float *__restrict__ acc, DevGrad gr) {
     const int64_t st = sc.stride, gst = gr.stride;
-    const int nk = (sc.D + 1) * (sc.D + 1);
+    // the first coefficient of each degree (and the end), as constants
+    using std::integral_constant;
+    constexpr integral_constant<int, 0> c0{};
+    constexpr integral_constant<int, 1> c1{};
+    constexpr integral_constant<int, 4> c4{};
+    constexpr integral_constant<int, 9> c9{};
+    constexpr integral_constant<int, 16> c16{};
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < sc.P;
          g += (int64_t)gridDim.x * blockDim.x) {
         float S[kAcc];
@@ -297,147 +311,170 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd(DevScene sc, DevCamer
                 any |= S[k] != 0.0f;
             }
         }
-        if (!any) {
-            // culled, or no pixel depends on it
-            for (int e = 0; e < 3; ++e) gr.means[e * gst + g] = 0.0f;
-            for (int e = 0; e < 3; ++e) gr.log_scales[e * gst + g] = 0.0f;
-            for (int e = 0; e < 4; ++e) gr.quats[e * gst + g] = 0.0f;
-            gr.logits[g] = 0.0f;
-            for (int k = 0; k < 3 * nk; ++k) gr.sh[k * gst + g] = 0.0f;
-            continue;
-        }
-        const GaussState s = gs[g];
-        const float A = s.f0.z, B = s.f0.w, C = s.f1.x, o = s.f2.w;
-        const float col[3] = {s.f1.w, s.f2.x, s.f2.y};
-        // gradients of the blended state
-        const float gA = S[1], gB = 2.0f * S[2], gC = S[3];
-        const float gu = -2.0f * (A * S[4] + B * S[5]);
-        const float gv = -2.0f * (B * S[4] + C * S[5]);
-        const float go = -2.0f * S[0] / o;
-        float gcol[3];
-        for (int ch = 0; ch < 3; ++ch) gcol[ch] = col[ch] > 0.0f ? S[6 + ch] : 0.0f;
+        // zero for a Gaussian that is culled or that no pixel depends on; every
+        // lane's gradients are stored by the same instructions, as whole lines
+        float gm3[3] = {0.0f, 0.0f, 0.0f}, gls[3] = {0.0f, 0.0f, 0.0f}, gq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        float glogit = 0.0f, gcol[3] = {0.0f, 0.0f, 0.0f}, Y[16] = {};
+        if (any) {
+            const GaussState s = gs[g];
+            const float A = s.f0.z, B = s.f0.w, C = s.f1.x, o = s.f2.w;
+            const float col[3] = {s.f1.w, s.f2.x, s.f2.y};
+            // gradients of the blended state
+            const float gA = S[1], gB = 2.0f * S[2], gC = S[3];
+            const float gu = -2.0f * (A * S[4] + B * S[5]);
+            const float gv = -2.0f * (B * S[4] + C * S[5]);
+            const float go = -2.0f * S[0] / o;
+            for (int ch = 0; ch < 3; ++ch) gcol[ch] = col[ch] > 0.0f ? S[6 + ch] : 0.0f;
 
-        // ---- forward recomputation ----------------------------------------
-        const float m[3] = {sc.means[g], sc.means[st + g], sc.means[2 * st + g]};
-        const float ls[3] = {sc.log_scales[g], sc.log_scales[st + g], sc.log_scales[2 * st + g]};
-        const float qr[4] = {sc.quats[g], sc.quats[st + g], sc.quats[2 * st + g], sc.quats[3 * st + g]};
-        const float logit = sc.logits[g];
-        const float *Rc = cam.R;
-        float t[3];
-        for (int r = 0; r < 3; ++r) t[r] = Rc[3 * r] * m[0] + Rc[3 * r + 1] * m[1] + Rc[3 * r + 2] * m[2] + cam.t[r];
-        const float sc3[3] = {expf(ls[0]), expf(ls[1]), expf(ls[2])};
-        const float qn = sqrtf(qr[0] * qr[0] + qr[1] * qr[1] + qr[2] * qr[2] + qr[3] * qr[3]);
-        const float w = qr[0] / qn, x = qr[1] / qn, y = qr[2] / qn, z = qr[3] / qn;
-        const float iz = 1.0f / t[2];
-        const float xt = t[0] * iz, yt = t[1] * iz;
-        const float limx = op.jac_clip * (0.5f * (float)W / cam.fx);
-        const float limy = op.jac_clip * (0.5f * (float)H / cam.fy);
-        const bool clipx = xt < -limx || xt > limx, clipy = yt < -limy || yt > limy;
-        const float xc = fminf(fmaxf(xt, -limx), limx), yc = fminf(fmaxf(yt, -limy), limy);
-        const float J00 = cam.fx * iz, J02 = -cam.fx * xc * iz, J11 = cam.fy * iz, J12 = -cam.fy * yc * iz;
-        const float Rq[9] = {1.0f - 2.0f * (y * y + z * z), 2.0f * (x * y - w * z), 2.0f * (x * z + w * y),
-                             2.0f * (x * y + w * z), 1.0f - 2.0f * (x * x + z * z), 2.0f * (y * z - w * x),
-                             2.0f * (x * z - w * y), 2.0f * (y * z + w * x), 1.0f - 2.0f * (x * x + y * y)};
-        float M[9];
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) M[3 * i + j] = Rq[3 * i + j] * sc3[j];
-        float Sig[9];
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j)
-                Sig[3 * i + j] = M[3 * i] * M[3 * j] + M[3 * i + 1] * M[3 * j + 1] + M[3 * i + 2] * M[3 * j + 2];
-        float Tm[6];
-        for (int j = 0; j < 3; ++j) {
-            Tm[j] = J00 * Rc[j] + J02 * Rc[6 + j];
-            Tm[3 + j] = J11 * Rc[3 + j] + J12 * Rc[6 + j];
-        }
+            // ---- forward recomputation ----------------------------------------
+            const float m[3] = {sc.means[g], sc.means[st + g], sc.means[2 * st + g]};
+            const float ls[3] = {sc.log_scales[g], sc.log_scales[st + g], sc.log_scales[2 * st + g]};
+            const float qr[4] = {sc.quats[g], sc.quats[st + g], sc.quats[2 * st + g], sc.quats[3 * st + g]};
+            const float logit = sc.logits[g];
+            const float *Rc = cam.R;
+            float t[3];
+            for (int r = 0; r < 3; ++r)
+                t[r] = Rc[3 * r] * m[0] + Rc[3 * r + 1] * m[1] + Rc[3 * r + 2] * m[2] + cam.t[r];
+            const float sc3[3] = {expf(ls[0]), expf(ls[1]), expf(ls[2])};
+            const float qn = sqrtf(qr[0] * qr[0] + qr[1] * qr[1] + qr[2] * qr[2] + qr[3] * qr[3]);
+            const float w = qr[0] / qn, x = qr[1] / qn, y = qr[2] / qn, z = qr[3] / qn;
+            const float iz = 1.0f / t[2];
+            const float xt = t[0] * iz, yt = t[1] * iz;
+            const float limx = op.jac_clip * (0.5f * (float)W / cam.fx);
+            const float limy = op.jac_clip * (0.5f * (float)H / cam.fy);
+            const bool clipx = xt < -limx || xt > limx, clipy = yt < -limy || yt > limy;
+            const float xc = fminf(fmaxf(xt, -limx), limx), yc = fminf(fmaxf(yt, -limy), limy);
+            const float J00 = cam.fx * iz, J02 = -cam.fx * xc * iz, J11 = cam.fy * iz, J12 = -cam.fy * yc * iz;
+            const float Rq[9] = {1.0f - 2.0f * (y * y + z * z), 2.0f * (x * y - w * z), 2.0f * (x * z + w * y),
+                                 2.0f * (x * y + w * z), 1.0f - 2.0f * (x * x + z * z), 2.0f * (y * z - w * x),
+                                 2.0f * (x * z - w * y), 2.0f * (y * z + w * x), 1.0f - 2.0f * (x * x + y * y)};
+            float M[9];
+            for (int i = 0; i < 3; ++i)
+                for (int j = 0; j < 3; ++j) M[3 * i + j] = Rq[3 * i + j] * sc3[j];
+            float Sig[9];
+            for (int i = 0; i < 3; ++i)
+                for (int j = 0; j < 3; ++j)
+                    Sig[3 * i + j] = M[3 * i] * M[3 * j] + M[3 * i + 1] * M[3 * j + 1] + M[3 * i + 2] * M[3 * j + 2];
+            float Tm[6];
+            for (int j = 0; j < 3; ++j) {
+                Tm[j] = J00 * Rc[j] + J02 * Rc[6 + j];
+                Tm[3 + j] = J11 * Rc[3 + j] + J12 * Rc[6 + j];
+            }
 
-        // ---- conic = inverse of X = Sigma' + dilation I: dL/dX = -Y dL/dY Y
-        const float hB = 0.5f * gB;
-        const float t00 = A * gA + B * hB, t01 = A * hB + B * gC, t10 = B * gA + C * hB, t11 = B * hB + C * gC;
-        const float p00 = -(t00 * A + t01 * B), p01 = -(t00 * B + t01 * C);
-        const float p10 = -(t10 * A + t11 * B), p11 = -(t10 * B + t11 * C);
-        const float gSp[4] = {p00, p01, p10, p11};
-        // ---- Sigma' = T Sigma T^T ---------------------------------------------
-        // dL/dSigma = T^T gSp T;  dL/dT = (gSp + gSp^T) T Sigma
-        float gSig[9];
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) {
-                float a = 0.0f;
-                for (int u = 0; u < 2; ++u)
-                    for (int v = 0; v < 2; ++v) a += Tm[3 * u + i] * gSp[2 * u + v] * Tm[3 * v + j];
-                gSig[3 * i + j] = a;
-            }
-        float TS[6];
-        for (int u = 0; u < 2; ++u)
-            for (int j = 0; j < 3; ++j)
-                TS[3 * u + j] = Tm[3 * u] * Sig[j] + Tm[3 * u + 1] * Sig[3 + j] + Tm[3 * u + 2] * Sig[6 + j];
-        const float P2[4] = {2.0f * p00, p01 + p10, p01 + p10, 2.0f * p11};
-        float gT[6];
-        for (int u = 0; u < 2; ++u)
-            for (int j = 0; j < 3; ++j) gT[3 * u + j] = P2[2 * u] * TS[j] + P2[2 * u + 1] * TS[3 + j];
-        // ---- T = J R_cam: only J00, J02, J11, J12 vary ------------------------
-        const float gJ00 = gT[0] * Rc[0] + gT[1] * Rc[1] + gT[2] * Rc[2];
-        const float gJ02 = gT[0] * Rc[6] + gT[1] * Rc[7] + gT[2] * Rc[8];
-        const float gJ11 = gT[3] * Rc[3] + gT[4] * Rc[4] + gT[5] * Rc[5];
-        const float gJ12 = gT[3] * Rc[6] + gT[4] * Rc[7] + gT[5] * Rc[8];
-        // ---- Sigma = M M^T, M = R_q diag(s) ---------------------------------
-        float gR[9], gs3[3] = {0.0f, 0.0f, 0.0f};
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) {
-                float gm = 0.0f;
-                for (int l = 0; l < 3; ++l) gm += (gSig[3 * i + l] + gSig[3 * l + i]) * M[3 * l + j];
-                gR[3 * i + j] = gm * sc3[j];
-                gs3[j] += gm * Rq[3 * i + j];
-            }
-        for (int j = 0; j < 3; ++j) gr.log_scales[j * gst + g] = gs3[j] * sc3[j];
-        // ---- rotation of the unit quaternion, then the normalisation --------
-        const float gw = 2.0f * (-z * gR[1] + y * gR[2] + z * gR[3] - x * gR[5] - y * gR[6] + x * gR[7]);
-        const float gx = 2.0f * (y * gR[1] + z * gR[2] + y * gR[3] - 2.0f * x * gR[4] - w * gR[5] + z * gR[6] +
-                                 w * gR[7] - 2.0f * x * gR[8]);
-        const float gy = 2.0f * (-2.0f * y * gR[0] + x * gR[1] + w * gR[2] + x * gR[3] + z * gR[5] - w * gR[6] +
-                                 z * gR[7] - 2.0f * y * gR[8]);
-        const float gz = 2.0f * (-2.0f * z * gR[0] - w * gR[1] + x * gR[2] + w * gR[3] - 2.0f * z * gR[4] +
-                                 y * gR[5] + x * gR[6] + y * gR[7]);
-        const float dq = w * gw + x * gx + y * gy + z * gz;
-        const float iqn = 1.0f / qn;
-        gr.quats[g] = (gw - w * dq) * iqn;
-        gr.quats[gst + g] = (gx - x * dq) * iqn;
-        gr.quats[2 * gst + g] = (gy - y * dq) * iqn;
-        gr.quats[3 * gst + g] = (gz - z * dq) * iqn;
-        // ---- J and (u, v) from the camera-space mean ----------------------------
-        const float iz2 = iz * iz;
-        float gt[3] = {0.0f, 0.0f, 0.0f};
-        gt[2] += -(gJ00 * cam.fx + gJ11 * cam.fy) * iz2 + (gJ02 * cam.fx * xc + gJ12 * cam.fy * yc) * iz2;
-        float gxt = clipx ? 0.0f : -gJ02 * cam.fx * iz;
-        float gyt = clipy ? 0.0f : -gJ12 * cam.fy * iz;
-        gxt += gu * cam.fx;
-        gyt += gv * cam.fy;
-        gt[0] += gxt * iz;
-        gt[1] += gyt * iz;
-        gt[2] -= (gxt * t[0] + gyt * t[1]) * iz2;
-        float gm3[3];
-        for (int j = 0; j < 3; ++j) gm3[j] = Rc[j] * gt[0] + Rc[3 + j] * gt[1] + Rc[6 + j] * gt[2];
-        // ---- opacity ----------------------------------------------------------
-        gr.logits[g] = go * o * (1.0f - o);
-        // ---- SH colour at the view direction ------------------------------------
-        const float dw[3] = {m[0] - cam.eye[0], m[1] - cam.eye[1], m[2] - cam.eye[2]};
-        const float dn = sqrtf(dw[0] * dw[0] + dw[1] * dw[1] + dw[2] * dw[2]);
-        const float idn = 1.0f / dn;
-        const float d[3] = {dw[0] * idn, dw[1] * idn, dw[2] * idn};
-        float Y[16], wk[16];
-        sh_basis(d[0], d[1], d[2], sc.D, Y);
-        for (int k = 0; k < nk; ++k) {
-            float a = 0.0f;
-            for (int ch = 0; ch < 3; ++ch) {
-                gr.sh[(int64_t)(3 * k + ch) * gst + g] = gcol[ch] * Y[k];
-                a += gcol[ch] * sc.sh[(int64_t)(3 * k + ch) * st + g];
-            }
-            wk[k] = a;
+            // ---- conic = inverse of X = Sigma' + dilation I: dL/dX = -Y dL/dY Y
+            const float hB = 0.5f * gB;
+            const float t00 = A * gA + B * hB, t01 = A * hB + B * gC, t10 = B * gA + C * hB, t11 = B * hB + C * gC;
+            const float p00 = -(t00 * A + t01 * B), p01 = -(t00 * B + t01 * C);
+            const float p10 = -(t10 * A + t11 * B), p11 = -(t10 * B + t11 * C);
+            const float gSp[4] = {p00, p01, p10, p11};
+            // ---- Sigma' = T Sigma T^T ---------------------------------------------
+            // dL/dSigma = T^T gSp T;  dL/dT = (gSp + gSp^T) T Sigma
+            float gSig[9];
+            for (int i = 0; i < 3; ++i)
+                for (int j = 0; j < 3; ++j) {
+                    float a = 0.0f;
+                    for (int u = 0; u < 2; ++u)
+                        for (int v = 0; v < 2; ++v) a += Tm[3 * u + i] * gSp[2 * u + v] * Tm[3 * v + j];
+                    gSig[3 * i + j] = a;
+                }
+            float TS[6];
+            for (int u = 0; u < 2; ++u)
+                for (int j = 0; j < 3; ++j)
+                    TS[3 * u + j] = Tm[3 * u] * Sig[j] + Tm[3 * u + 1] * Sig[3 + j] + Tm[3 * u + 2] * Sig[6 + j];
+            const float P2[4] = {2.0f * p00, p01 + p10, p01 + p10, 2.0f * p11};
+            float gT[6];
+            for (int u = 0; u < 2; ++u)
+                for (int j = 0; j < 3; ++j) gT[3 * u + j] = P2[2 * u] * TS[j] + P2[2 * u + 1] * TS[3 + j];
+            // ---- T = J R_cam: only J00, J02, J11, J12 vary ------------------------
+            const float gJ00 = gT[0] * Rc[0] + gT[1] * Rc[1] + gT[2] * Rc[2];
+            const float gJ02 = gT[0] * Rc[6] + gT[1] * Rc[7] + gT[2] * Rc[8];
+            const float gJ11 = gT[3] * Rc[3] + gT[4] * Rc[4] + gT[5] * Rc[5];
+            const float gJ12 = gT[3] * Rc[6] + gT[4] * Rc[7] + gT[5] * Rc[8];
+            // ---- Sigma = M M^T, M = R_q diag(s) ---------------------------------
+            float gR[9], gs3[3] = {0.0f, 0.0f, 0.0f};
+            for (int i = 0; i < 3; ++i)
+                for (int j = 0; j < 3; ++j) {
+                    float gm = 0.0f;
+                    for (int l = 0; l < 3; ++l) gm += (gSig[3 * i + l] + gSig[3 * l + i]) * M[3 * l + j];
+                    gR[3 * i + j] = gm * sc3[j];
+                    gs3[j] += gm * Rq[3 * i + j];
+                }
+            for (int j = 0; j < 3; ++j) gls[j] = gs3[j] * sc3[j];
+            // ---- rotation of the unit quaternion, then the normalisation --------
+            const float gw = 2.0f * (-z * gR[1] + y * gR[2] + z * gR[3] - x * gR[5] - y * gR[6] + x * gR[7]);
+            const float gx = 2.0f * (y * gR[1] + z * gR[2] + y * gR[3] - 2.0f * x * gR[4] - w * gR[5] + z * gR[6] +
+                                     w * gR[7] - 2.0f * x * gR[8]);
+            const float gy = 2.0f * (-2.0f * y * gR[0] + x * gR[1] + w * gR[2] + x * gR[3] + z * gR[5] - w * gR[6] +
+                                     z * gR[7] - 2.0f * y * gR[8]);
+            const float gz = 2.0f * (-2.0f * z * gR[0] - w * gR[1] + x * gR[2] + w * gR[3] - 2.0f * z * gR[4] +
+                                     y * gR[5] + x * gR[6] + y * gR[7]);
+            const float dq = w * gw + x * gx + y * gy + z * gz;
+            const float iqn = 1.0f / qn;
+            gq[0] = (gw - w * dq) * iqn;
+            gq[1] = (gx - x * dq) * iqn;
+            gq[2] = (gy - y * dq) * iqn;
+            gq[3] = (gz - z * dq) * iqn;
+            // ---- J and (u, v) from the camera-space mean ----------------------------
+            const float iz2 = iz * iz;
+            float gt[3] = {0.0f, 0.0f, 0.0f};
+            gt[2] += -(gJ00 * cam.fx + gJ11 * cam.fy) * iz2 + (gJ02 * cam.fx * xc + gJ12 * cam.fy * yc) * iz2;
+            float gxt = clipx ? 0.0f : -gJ02 * cam.fx * iz;
+            float gyt = clipy ? 0.0f : -gJ12 * cam.fy * iz;
+            gxt += gu * cam.fx;
+            gyt += gv * cam.fy;
+            gt[0] += gxt * iz;
+            gt[1] += gyt * iz;
+            gt[2] -= (gxt * t[0] + gyt * t[1]) * iz2;
+            for (int j = 0; j < 3; ++j) gm3[j] = Rc[j] * gt[0] + Rc[3 + j] * gt[1] + Rc[6 + j] * gt[2];
+            // ---- opacity ----------------------------------------------------------
+            glogit = go * o * (1.0f - o);
+            // ---- SH colour at the view direction ------------------------------------
+            const float dw[3] = {m[0] - cam.eye[0], m[1] - cam.eye[1], m[2] - cam.eye[2]};
+            const float dn = sqrtf(dw[0] * dw[0] + dw[1] * dw[1] + dw[2] * dw[2]);
+            const float idn = 1.0f / dn;
+            const float d[3] = {dw[0] * idn, dw[1] * idn, dw[2] * idn};
+            float wk[16];
+            sh_basis(d[0], d[1], d[2], sc.D, Y);
+            // (all coefficients are read together: one memory round trip)
+            const float *shp = sc.sh + g;
+            float shv[48];
+            auto load_sh = [&](auto k0, auto k1) {
+#pragma unroll
+                for (int j = 3 * k0; j < 3 * k1; ++j, shp += st) shv[j] = *shp;
+            };
+            auto dot_sh = [&](auto k0, auto k1) {
+#pragma unroll
+                for (int k = k0; k < k1; ++k)
+                    wk[k] = gcol[0] * shv[3 * k] + gcol[1] * shv[3 * k + 1] + gcol[2] * shv[3 * k + 2];
+            };
+            load_sh(c0, c1);
+            if (sc.D >= 1) load_sh(c1, c4);
+            if (sc.D >= 2) load_sh(c4, c9);
+            if (sc.D >= 3) load_sh(c9, c16);
+            dot_sh(c0, c1);
+            if (sc.D >= 1) dot_sh(c1, c4);
+            if (sc.D >= 2) dot_sh(c4, c9);
+            if (sc.D >= 3) dot_sh(c9, c16);
+            float gd[3];
+            sh_basis_grad(d[0], d[1], d[2], sc.D, wk, gd);
+            const float dd = d[0] * gd[0] + d[1] * gd[1] + d[2] * gd[2];
+            for (int e = 0; e < 3; ++e) gm3[e] += (gd[e] - d[e] * dd) * idn;
         }
-        float gd[3];
-        sh_basis_grad(d[0], d[1], d[2], sc.D, wk, gd);
-        const float dd = d[0] * gd[0] + d[1] * gd[1] + d[2] * gd[2];
-        for (int e = 0; e < 3; ++e) gr.means[e * gst + g] = gm3[e] + (gd[e] - d[e] * dd) * idn;
+        for (int e = 0; e < 3; ++e) gr.means[e * gst + g] = gm3[e];
+        for (int e = 0; e < 3; ++e) gr.log_scales[e * gst + g] = gls[e];
+        for (int e = 0; e < 4; ++e) gr.quats[e * gst + g] = gq[e];
+        gr.logits[g] = glogit;
+        float *gsh = gr.sh + g;
+        auto store_sh = [&](auto k0, auto k1) {
+#pragma unroll
+            for (int k = k0; k < k1; ++k)
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch, gsh += gst) *gsh = gcol[ch] * Y[k];
+        };
+        store_sh(c0, c1);
+        if (sc.D >= 1) store_sh(c1, c4);
+        if (sc.D >= 2) store_sh(c4, c9);
+        if (sc.D >= 3) store_sh(c9, c16);
     }
 }
 

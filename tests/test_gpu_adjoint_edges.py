@@ -45,3 +45,23 @@ def test_centres_far_outside(orc, R, seed, W, H):  # noqa: F811
     g, _, dL = gpu_grads(R, sc, cam, W, H, o, dL=w)
     ref = orc.backward(orc.render(sc.astype(np.float64), cam, W, H, o, "f64"), dL)
     compare(g, ref, f"far{seed}", min_frac=0.99)
+
+
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+@pytest.mark.parametrize("P", [1, 63, 65, 300])
+def test_culled_among_seen(orc, R, deg, P):  # noqa: F811
+    """Every third Gaussian is behind the camera: exact zeros there, in the
+    lines of the seen ones' gradients."""
+    print(f"[bwd] culled degree {deg} P {P}", flush=True)
+    rng = np.random.default_rng(100 * deg + P)
+    W, H = 40, 30
+    sc = random_scene(rng, P, ls_mu=-2.5, sh_degree=deg)
+    sc.means[2, 1::3] = -3.0
+    cam = identity_camera(W, H, 0.9 * W)
+    o = opts()
+    w = np.random.default_rng(8).uniform(-1, 1, (3, H, W))
+    g, _, dL = gpu_grads(R, sc, cam, W, H, o, dL=w)
+    for name in g:
+        assert np.all(g[name][:, 1::3] == 0.0), name
+    ref = orc.backward(orc.render(sc.astype(np.float64), cam, W, H, o, "f64"), dL)
+    compare(g, ref, f"culled{deg}-{P}")
