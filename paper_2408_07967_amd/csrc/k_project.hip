@@ -905,6 +905,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             if (w < wave) run += s_wtot[w];
             ncand += s_wtot[w];
         }
+        ncand = (uint32_t)__builtin_amdgcn_readfirstlane((int)ncand);  // (the same in every lane)
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             s_pref[threadIdx.x * kPer + j] = run;
@@ -975,7 +976,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const DevPrepared &pp = ba.pp;
     const DevOptions &op = ba.op;
     const bool full = ba.full != 0;
-    int64_t g = P;
+    // (Gaussian indices are below 2^31; P32: an idle lane)
+    const uint32_t P32 = (uint32_t)P;
+    uint32_t g = P32;
     uint32_t ii = 0;  // output slot (prepared: position in the candidate list)
     if constexpr (kPrep) {
         if ((uint64_t)batch * kBlock >= ncand) break;
@@ -988,7 +991,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 if (s_pref[sg + step] <= ii) sg += step;
             int64_t lo, hi;
             cull_range(P, sg, &lo, &hi);
-            g = (int64_t)ba.cand[lo + (ii - s_pref[sg])];
+            g = ba.cand[lo + (ii - s_pref[sg])];
         }
         batch += gridDim.x;
     } else if constexpr (kList) {
@@ -1024,7 +1027,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const uint32_t take = n_queue <= (uint32_t)kWave ? n_queue : n_whole;
         {
             const uint32_t at = (q_head + (uint32_t)lane) % kRing;
-            if ((uint32_t)lane < take) g = (int64_t)s_rg[wv][at];
+            if ((uint32_t)lane < take) g = s_rg[wv][at];
             float *f = reinterpret_cast<float *>(&rt);
 #pragma unroll
             for (int j = 0; j < kTerms; ++j) f[j] = s_rt[wv][j][at];
@@ -1035,7 +1038,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             ii = slot + (uint32_t)lane;
             slot += take;
         } else {
-            ii = (uint32_t)g;
+            ii = g;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1043,7 +1046,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         if (grp >= grp_end) break;
         const int64_t i = (int64_t)grp * kWave + lane;
         if (i < P) {
-            g = i;
+            g = (uint32_t)i;
             rt = raw_terms(sc, g);
         }
         ii = (uint32_t)i;
@@ -1070,7 +1073,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     int tx0 = 0, tx1 = -1, ty0 = 0, ty1 = -1;
     float col[3] = {0, 0, 0};
 
-    if (g < P) {
+    if (g < P32) {
         float mx, my, mz, po = 0.0f;
         if constexpr (kPrep) {
             const float4 p4 = pp.pos_o[g];
@@ -1100,7 +1103,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 o = po;
                 ok = o > op.alpha_min;
                 if (ok) {
-                    const float4 c0 = pp.cov[2 * g], c1 = pp.cov[2 * g + 1];
+                    const float4 c0 = pp.cov[2 * (int64_t)g], c1 = pp.cov[2 * (int64_t)g + 1];
                     s3[0] = c0.x; s3[1] = c0.y; s3[2] = c0.z;
                     k2 = c0.w;
                     qu[0] = c1.x; qu[1] = c1.y; qu[2] = c1.z; qu[3] = c1.w;
@@ -1197,23 +1200,45 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                             const int nk = (sc.D + 1) * (sc.D + 1);
                             float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
                             // every coefficient load is issued before the first
-                            // use (one memory round trip, not one per coefficient)
-                            const int ncoef = 3 * nk;
+                            // use (one memory round trip, not one per coefficient),
+                            // a degree's loads behind one branch: with a branch per
+                            // load, and two registers spilled whose reload stood
+                            // between them, the 4K frame's kernel took 280 us, now
+                            // 250, the 1M Gaussians' 98 and 85, and 10,000 raw
+                            // ones' 11.9 and 10.6
                             float shv[48];
                             if constexpr (kPrep) {
                                 // Gaussian-major coefficients: one contiguous read
                                 const float4 *shg = reinterpret_cast<const float4 *>(pp.sh + (int64_t)g * pp.sh_stride);
+                                auto read_sh = [&](int j0, int j1) {
 #pragma unroll
-                                for (int j = 0; j < 12; ++j) {
-                                    const float4 q4 = 4 * j < ncoef ? shg[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-                                    shv[4 * j] = q4.x;
-                                    shv[4 * j + 1] = q4.y;
-                                    shv[4 * j + 2] = q4.z;
-                                    shv[4 * j + 3] = q4.w;
-                                }
+                                    for (int j = j0; j < j1; ++j) {
+                                        const float4 q4 = shg[j];
+                                        shv[4 * j] = q4.x;
+                                        shv[4 * j + 1] = q4.y;
+                                        shv[4 * j + 2] = q4.z;
+                                        shv[4 * j + 3] = q4.w;
+                                    }
+                                };
+                                // (1, 4, 9 or 16 coefficients of 3 channels, padded to 4 floats)
+#pragma unroll
+                                for (int j = 4; j < 48; ++j) shv[j] = 0.0f;
+                                read_sh(0, 1);
+                                if (sc.D >= 1) read_sh(1, 3);
+                                if (sc.D >= 2) read_sh(3, 7);
+                                if (sc.D >= 3) read_sh(7, 12);
                             } else {
+                                const float *shp = sc.sh + g;
+                                auto read_sh = [&](int j0, int j1) {
 #pragma unroll
-                                for (int j = 0; j < 48; ++j) shv[j] = j < ncoef ? sc.sh[(int64_t)j * st + g] : 0.0f;
+                                    for (int j = j0; j < j1; ++j, shp += st) shv[j] = *shp;
+                                };
+#pragma unroll
+                                for (int j = 3; j < 48; ++j) shv[j] = 0.0f;
+                                read_sh(0, 3);
+                                if (sc.D >= 1) read_sh(3, 12);
+                                if (sc.D >= 2) read_sh(12, 27);
+                                if (sc.D >= 3) read_sh(27, 48);
                             }
 #pragma unroll
                             for (int k = 0; k < 16; ++k) {
@@ -1256,7 +1281,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             uint32_t cbase = w_nch;
             if constexpr (kMulti) cbase = s_nch[wv][ci];
             if (chunked) {
-                const uint32_t at = w_nbig + (uint32_t)__popcll(bm & ((1ull << lane) - 1ull));
+                const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)bm, w_nbig));
                 if constexpr (kMulti) s_bc[wv][at] = (uint32_t)ci;
                 s_bg[wv][at] = ii;
                 s_bn[wv][at] = nch;
@@ -1315,7 +1341,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // entries: the overlapped super-tiles (at most 10 for a rectangle of at
     // most kBigTiles tiles)
     const uint32_t ents = valid ? super_span(tx0, tx1, ty0, ty1) : 0u;
-    if (g < P) {
+    if (g < P32) {
         const uint32_t key = valid ? __float_as_uint(tz) : kInvalidKey;
         const int64_t oi = (int64_t)ii;
         if constexpr (kPrep) {
