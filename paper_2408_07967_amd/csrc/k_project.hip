@@ -1553,14 +1553,19 @@ __global__ __launch_bounds__(kBlock) void k_super_emit(int W, const uint32_t *__
     }
 }
 
-// Entries of the chunked Gaussians.  Each wavefront takes 64 chunk slots,
-// one per lane; a Gaussian's first chunk holds, in `big`, its output slot
-// and entry offset.  The wavefront flattens the entries of its Gaussians so
+// Entries of the chunked Gaussians.  Each wavefront takes up to 64 chunk
+// slots, one per lane; the slot of a Gaussian's first chunk holds, in `big`,
+// its output slot and entry offset, and each of its chunks takes an even share
+// of its entries.  The wavefront flattens the entries of its chunks so
 // that every lane builds one entry per step: entry k of a Gaussian is
 // super-tile k of its rectangle's overlap in row-major order.  The chunk
 // masks of a Gaussian are one bit stream over its rectangle in row-major
 // order, so each of the super-tile's (at most kSuper) rows is a run of at
 // most kSuper consecutive bits, read from two words.
+//
+// Bound by its writes, short runs at depth-ordered places in three arrays (an
+// 8K frame's 844,000 chunks: 83 us; with all of a Gaussian's entries at its
+// first chunk, and so in one wavefront, 109; 4K, 200,000 chunks: 23, was 27).
 __global__ __launch_bounds__(kBlock) void k_big_entries(int W, const uint4 *__restrict__ erec, uint32_t ng,
                                                         const uint2 *__restrict__ chunks,
                                                         const uint2 *__restrict__ big, uint32_t chunk_cap,
@@ -1580,19 +1585,29 @@ __global__ __launch_bounds__(kBlock) void k_big_entries(int W, const uint4 *__re
     const uint32_t nwaves = gridDim.x * (kBlock / kWave);
     constexpr uint32_t kWordsPerChunk = kChunkTiles / 32;
     const size_t wlast = (size_t)chunk_cap * kWordsPerChunk - 1;
-    for (uint32_t c0 = (blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave) * kWave; c0 < n;
-         c0 += nwaves * kWave) {
-        const uint32_t c = c0 + (uint32_t)lane;
-        bool first = false;
+    // an even share of at most 64 chunk slots per wavefront and round
+    const uint32_t rounds = n / (nwaves * kWave) + 1u, per = (n + nwaves * rounds - 1u) / (nwaves * rounds);
+    const uint32_t w0 = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    for (uint32_t c0 = w0 * per; c0 < n; c0 += nwaves * per) {
+        const uint32_t c = (uint32_t)lane < per ? c0 + (uint32_t)lane : n;
+        uint32_t first = 0, k0 = 0, items = 0;
         uint2 gb = make_uint2(0u, 0u);
-        if (c < n) {
-            first = chunks[c].y == c;
-            gb = big[c];
-        }
-        first = first && gb.x < ng;
         uint4 rc = make_uint4(0u, 0u, 0u, 0u);
-        if (first) rc = unpack_rect(erec[gb.x]);
-        const uint32_t items = first ? super_span((int)rc.x, (int)rc.y, (int)rc.z, (int)rc.w) : 0u;
+        if (c < n) {
+            first = chunks[c].y;
+            gb = big[first];
+            if (gb.x < ng) {
+                rc = unpack_rect(erec[gb.x]);
+                const uint32_t nt = (rc.y - rc.x + 1u) * (rc.w - rc.z + 1u);
+                const uint32_t nch = (nt + kChunkTiles - 1) / kChunkTiles;
+                const uint32_t span = super_span((int)rc.x, (int)rc.y, (int)rc.z, (int)rc.w);
+                const uint32_t j = c - first;
+                if (j < nch) {
+                    k0 = (uint32_t)((uint64_t)span * j / nch);
+                    items = (uint32_t)((uint64_t)span * (j + 1u) / nch) - k0;
+                }
+            }
+        }
         const uint32_t incl = wave_incl_scan(items, lane);
         const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
         sx[lane] = incl - items;
@@ -1603,7 +1618,8 @@ __global__ __launch_bounds__(kBlock) void k_big_entries(int W, const uint4 *__re
         for (uint32_t i0 = 0; i0 < total; i0 += kWave) {
             const uint32_t item = i0 + (uint32_t)lane;
             const int L = owner_lane(sx, item < total ? item : total - 1u);
-            const uint32_t k = item < total ? item - sx[L] : 0u;  // (a spare lane redoes entry 0)
+            const uint32_t k = (uint32_t)__shfl((int)k0, L, kWave) + (item < total ? item - sx[L] : 0u);
+            const uint32_t fc0 = (uint32_t)__shfl((int)first, L, kWave);
             const uint32_t g = (uint32_t)__shfl((int)gb.x, L, kWave), base = (uint32_t)__shfl((int)gb.y, L, kWave);
             const uint32_t lx = (uint32_t)__shfl((int)px, L, kWave), ly = (uint32_t)__shfl((int)py, L, kWave);
             const int bx0 = (int)(lx & 0xffffu), bx1 = (int)(lx >> 16), by0 = (int)(ly & 0xffffu), by1 = (int)(ly >> 16);
@@ -1616,7 +1632,7 @@ __global__ __launch_bounds__(kBlock) void k_big_entries(int W, const uint4 *__re
             const int xa = xs > bx0 ? xs : bx0, xb = xs + kSuper - 1 < bx1 ? xs + kSuper - 1 : bx1;
             const int ya = ys > by0 ? ys : by0, yb = ys + kSuper - 1 < by1 ? ys + kSuper - 1 : by1;
             const uint64_t lmask = (1ull << (xb - xa + 1)) - 1ull;  // xb - xa + 1 <= kSuper
-            const size_t wbase = (size_t)(c0 + (uint32_t)L) * kWordsPerChunk;
+            const size_t wbase = (size_t)fc0 * kWordsPerChunk;
             // every row's two words are loaded (rows past yb repeat row yb)
             // before any is used: one memory round trip
             uint32_t lo[kSuper], hi[kSuper], sh[kSuper];
@@ -1624,10 +1640,10 @@ __global__ __launch_bounds__(kBlock) void k_big_entries(int W, const uint4 *__re
             for (int rr = 0; rr < kSuper; ++rr) {
                 const int ty = ya + rr < yb ? ya + rr : yb;
                 const uint32_t idx = (uint32_t)((ty - by0) * bntx + (xa - bx0));
-                const size_t w0 = wbase + idx / 32 < wlast ? wbase + idx / 32 : wlast;
-                const size_t w1 = w0 + 1 < wlast ? w0 + 1 : wlast;
-                lo[rr] = chunk_mask[w0];
-                hi[rr] = chunk_mask[w1];
+                const size_t wlo = wbase + idx / 32 < wlast ? wbase + idx / 32 : wlast;
+                const size_t whi = wlo + 1 < wlast ? wlo + 1 : wlast;
+                lo[rr] = chunk_mask[wlo];
+                hi[rr] = chunk_mask[whi];
                 sh[rr] = idx % 32;
             }
             uint64_t m = 0;
@@ -1963,7 +1979,8 @@ void launch_super_emit(int W, int H, const uint32_t *order, uint32_t visible, co
                            big, chunk_cap, skey, gidx, smask, ecap, sranges, nsuper, gsum_clear, fc);
     }
     if (chunk_cap == 0 || visible == 0 || !chunk_mask) return;
-    hipLaunchKernelGGL(k_big_entries, dim3(kPersistentBlocks), dim3(kBlock), 0, s, W, erec, ng, chunks, big,
+    static const unsigned big_grid = resident_blocks(k_big_entries);
+    hipLaunchKernelGGL(k_big_entries, dim3(big_grid), dim3(kBlock), 0, s, W, erec, ng, chunks, big,
                        chunk_cap, chunk_mask, fc, skey, gidx, smask, ecap);
 }
 
