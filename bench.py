@@ -55,7 +55,7 @@ VALU_PEAK_TSLOTS = 157.3 / 4
 BLEND_SLOTS_PER_EVAL = 12.6
 PROFILE_SOURCES = {
     "k_blend": ("k_blend.hip", "blend_common.hpp", "fgs_internal.hpp"),
-    "k_preprocess": ("k_project.hip", "fgs_internal.hpp", "sh_basis.hpp"),
+    "k_preprocess": ("k_project.hip", "fgs_internal.hpp", "sh_basis.hpp", "tile_test.hpp"),
 }
 
 
