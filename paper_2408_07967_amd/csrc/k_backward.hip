@@ -26,7 +26,7 @@
 // nine terms over the lanes with DPP adds took 54 of about 130 VALU
 // instructions per step; with one plane per accumulator each of a Gaussian's
 // nine atomics was a request of its own.  1M Gaussians at 1920 x 1080: 897 ->
-// 372 us, 10k at 256 x 256: 278 -> 100 us, the errors of the gradients against
+// 390 us, 10k at 256 x 256: 278 -> 113 us, the errors of the gradients against
 // binary64 unchanged.)
 // Accumulators per Gaussian (kAccStride floats, one 64-byte line):
 //     0: sum dL/dq            1..3: sum dL/dq dx^2, dx dy, dy^2

@@ -1407,8 +1407,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // The workgroup's visible and pair counts (of each camera) in one 64-bit
     // atomic: atomics on one line take about 8 ns each, one after the other,
     // and the wavefronts of a frame all end at about the same time.  With two
-    // per wavefront the kernel took 87 us for 200k Gaussians (now 26), 162 for
-    // 1M (98) and 344 for the 3M candidates of the 10M city (275).
+    // per wavefront the kernel took 87 us for 200k Gaussians (27 now), 162 for
+    // 1M (98 with this alone, 85 now) and 344 for the 3M candidates of the 10M
+    // city (275, 250 now).
     static_assert(offsetof(FrameCounters, pairs) == offsetof(FrameCounters, visible) + 4 &&
                       offsetof(FrameCounters, visible) % 8 == 0,
                   "one 64-bit counter");
