@@ -1957,9 +1957,16 @@ void launch_spatial_keys(const DevScene &sc, uint32_t *bounds, uint32_t *keys, h
     hipLaunchKernelGGL(k_spatial_keys, dim3(grid), dim3(kBlock), 0, s, sc, bounds, keys);
 }
 
+// (asked for by the first half already: the second one may be under capture)
+static unsigned big_entries_grid() {
+    static const unsigned grid = resident_blocks(k_big_entries);
+    return grid;
+}
+
 void launch_big_count(int W, int H, int binning, const GaussState *gs, const float4 *conic, const uint4 *erec,
                       const uint2 *chunks, uint32_t chunk_cap, uint32_t *chunk_mask, uint32_t *count,
                       FrameCounters *fc, hipStream_t s) {
+    (void)big_entries_grid();
     if (chunk_cap == 0) return;
     static const unsigned grid = resident_blocks(k_big_count);
     hipLaunchKernelGGL(k_big_count, dim3(grid), dim3(kBlock), 0, s, W, H, binning, gs, conic, erec,
@@ -1980,8 +1987,7 @@ void launch_super_emit(int W, int H, const uint32_t *order, uint32_t visible, co
                            big, chunk_cap, skey, gidx, smask, ecap, sranges, nsuper, gsum_clear, fc);
     }
     if (chunk_cap == 0 || visible == 0 || !chunk_mask) return;
-    static const unsigned big_grid = resident_blocks(k_big_entries);
-    hipLaunchKernelGGL(k_big_entries, dim3(big_grid), dim3(kBlock), 0, s, W, erec, ng, chunks, big,
+    hipLaunchKernelGGL(k_big_entries, dim3(big_entries_grid()), dim3(kBlock), 0, s, W, erec, ng, chunks, big,
                        chunk_cap, chunk_mask, fc, skey, gidx, smask, ecap);
 }
 
