@@ -66,22 +66,53 @@ __device__ __forceinline__ int64_t lane_tile(uint32_t s, uint32_t stx, int tiles
     return (tx < tiles_x && ty < tiles_y) ? (int64_t)ty * tiles_x + tx : -1;
 }
 
+// Lane l's value from lane l ^ kStep (kStep at most 16), in registers.
+template <int kStep>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t x, int lane) {
+    if constexpr (kStep == 16) {
+        // rows of 16: the second row of each pair from the first, and back
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (lane & 16) ? r[0] : r[1];
+    } else if constexpr (kStep == 8) {
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);  // row_ror:8
+    } else if constexpr (kStep == 4) {
+        const int m = __builtin_amdgcn_mov_dpp((int)x, 0x141, 0xf, 0xf, true);  // row_half_mirror: l ^ 7
+        return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1b, 0xf, 0xf, true);     // quad_perm [3, 2, 1, 0]: l ^ 3
+    } else if constexpr (kStep == 2) {
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4e, 0xf, 0xf, true);  // quad_perm [2, 3, 0, 1]
+    } else {
+        static_assert(kStep == 1, "a power of two");
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xb1, 0xf, 0xf, true);  // quad_perm [1, 0, 3, 2]
+    }
+}
+
+// One stage of the transpose below: the off-diagonal kStep x kStep blocks of
+// every 2 kStep x 2 kStep block change places (kLow: the low kStep bits of
+// each 2 kStep bits).
+template <int kStep, uint32_t kLow>
+__device__ __forceinline__ void transpose_stage(uint32_t &lo, uint32_t &hi, int lane) {
+    const bool up = (lane & kStep) != 0;
+    const uint32_t keep = up ? ~kLow : kLow;
+    const uint32_t rot = up ? kStep : 32 - kStep;  // to the right
+    const uint32_t a = from_lane_xor<kStep>(lo, lane), b = from_lane_xor<kStep>(hi, lane);
+    lo = (lo & keep) | (__builtin_amdgcn_alignbit(a, a, rot) & ~keep);
+    hi = (hi & keep) | (__builtin_amdgcn_alignbit(b, b, rot) & ~keep);
+}
+
 // Transpose of the 64 x 64 bit matrix whose row i is lane i's word: lane j
 // gets column j (bit i = bit j of row i).  Six butterfly stages swap the
-// off-diagonal s x s blocks of every 2s x 2s block (s = 32 ... 1).
+// off-diagonal s x s blocks of every 2s x 2s block (s = 32 ... 1), between
+// lanes by register moves: through the LDS permute and with 64-bit shifts
+// k_list_count took 16.4 us at 4K and 23.9 at 8K, now 13.6 and 20.5.
 __device__ __forceinline__ uint64_t transpose64(uint64_t x, int lane) {
-    const uint64_t kM[6] = {0x00000000ffffffffull, 0x0000ffff0000ffffull, 0x00ff00ff00ff00ffull,
-                            0x0f0f0f0f0f0f0f0full, 0x3333333333333333ull, 0x5555555555555555ull};
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const int sh = 32 >> k;
-        const uint64_t m = kM[k];
-        const uint32_t ylo = (uint32_t)__shfl_xor((int)(uint32_t)x, sh, kWave);
-        const uint32_t yhi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), sh, kWave);
-        const uint64_t y = (uint64_t)ylo | ((uint64_t)yhi << 32);
-        x = (lane & sh) ? ((x & ~m) | ((y >> sh) & m)) : ((x & m) | ((y & m) << sh));
-    }
-    return x;
+    const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)(x >> 32), false, false);
+    uint32_t lo = r[0], hi = r[1];
+    transpose_stage<16, 0x0000ffffu>(lo, hi, lane);
+    transpose_stage<8, 0x00ff00ffu>(lo, hi, lane);
+    transpose_stage<4, 0x0f0f0f0fu>(lo, hi, lane);
+    transpose_stage<2, 0x33333333u>(lo, hi, lane);
+    transpose_stage<1, 0x55555555u>(lo, hi, lane);
+    return (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
 // The chunks of [0, n) that this wavefront takes: n is cut into eight
@@ -321,9 +352,10 @@ static_assert(kListChunk == 32 * kListWords, "four 64-entry blocks");
 // lane j walks the entries that its tile j hits and lists them in LDS behind
 // the earlier tiles', and the list is then written by all lanes: one step per
 // 64 pairs, with about as many separate lines as it has tiles' runs.
-// 27.2M pairs of a 4K frame: 73 us before, 64 now; 76.7M of an 8K frame: 153,
-// now 142 (write requests of 64 bytes: 5.1M for 307 MB of pairs); 4.6M of a
-// 1080p frame: 25, now 18.  With a buffer of 4096 pairs per wavefront, i.e. four
+// 27.2M pairs of a 4K frame: 73 us before, 60 now; 76.7M of an 8K frame: 153,
+// now 141 (write requests of 64 bytes: 5.1M for 307 MB of pairs); 4.6M of a
+// 1080p frame: 25, now 18.  (With stores that bypass the L2's merging of the
+// runs' ends 115 and 320 us; with four pairs per lane and step 60 and 152.)  With a buffer of 4096 pairs per wavefront, i.e. four
 // instead of seven workgroups per CU, the 1080p frame took 21.5.
 template <bool kBuf>
 __global__ __launch_bounds__(kListBlock) void k_list_write(const uint2 *__restrict__ sranges, uint32_t ecap,
@@ -421,7 +453,7 @@ __global__ __launch_bounds__(kListBlock) void k_list_write(const uint2 *__restri
                 }
             }
             lds_order();
-            constexpr uint32_t kOut = 4;
+            constexpr uint32_t kOut = 2;
             for (uint32_t i0 = (uint32_t)lane; i0 < np; i0 += kOut * kWave) {
                 uint32_t u[kOut], gv[kOut], pos[kOut];
 #pragma unroll
