@@ -352,7 +352,7 @@ static_assert(kListChunk == 32 * kListWords, "four 64-entry blocks");
 // lane j walks the entries that its tile j hits and lists them in LDS behind
 // the earlier tiles', and the list is then written by all lanes: one step per
 // 64 pairs, with about as many separate lines as it has tiles' runs.
-// 27.2M pairs of a 4K frame: 73 us before, 60 now; 76.7M of an 8K frame: 153,
+// 27.2M pairs of a 4K frame: 73 us before, 61 now; 76.7M of an 8K frame: 153,
 // now 141 (write requests of 64 bytes: 5.1M for 307 MB of pairs); 4.6M of a
 // 1080p frame: 25, now 18.  (With stores that bypass the L2's merging of the
 // runs' ends 115 and 320 us; with four pairs per lane and step 60 and 152.)  With a buffer of 4096 pairs per wavefront, i.e. four
