@@ -355,8 +355,9 @@ static_assert(kListChunk == 32 * kListWords, "four 64-entry blocks");
 // 27.2M pairs of a 4K frame: 73 us before, 61 now; 76.7M of an 8K frame: 153,
 // now 141 (write requests of 64 bytes: 5.1M for 307 MB of pairs); 4.6M of a
 // 1080p frame: 25, now 18.  (With stores that bypass the L2's merging of the
-// runs' ends 115 and 320 us; with four pairs per lane and step 60 and 152.)  With a buffer of 4096 pairs per wavefront, i.e. four
-// instead of seven workgroups per CU, the 1080p frame took 21.5.
+// runs' ends 115 and 320 us; with four pairs per lane and step 60 and 152.)
+// With a buffer of 4096 pairs per wavefront, i.e. four instead of seven
+// workgroups per CU, the 1080p frame took 21.5.
 template <bool kBuf>
 __global__ __launch_bounds__(kListBlock) void k_list_write(const uint2 *__restrict__ sranges, uint32_t ecap,
                                                            const uint32_t *__restrict__ cbase, uint32_t nsuper,
