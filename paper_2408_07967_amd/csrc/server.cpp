@@ -74,7 +74,11 @@ struct Slot {
     SlotState state = SlotState::IDLE;
     hipStream_t stream = nullptr;
     hipEvent_t evA = nullptr, evB = nullptr;
-    hipEvent_t evP = nullptr;  // a batched front half's shared preprocess is complete
+    hipEvent_t evP = nullptr;  // a batched front half's shared preprocess is complete, or (tail) see below
+    // the slot was freed with work of its refused request still queued on its
+    // stream (evA passes on the side stream, beside the depth order); evP is
+    // behind it
+    bool tail = false;
     SideStream side;
     FrameBuffers fb;
     ChunkList ch;
@@ -228,6 +232,13 @@ void start_front_batch(fgs_server *srv, const std::vector<Slot *> &b) {
     }
     Slot &s0 = *b[0];
     const uint32_t P = (uint32_t)srv->scene.num_gaussians;
+    // the shared pass writes every member's buffers from s0's stream: behind
+    // what a member's own stream may still run of a refused request
+    for (size_t c = 0; c < b.size(); ++c) {
+        Slot &s = *b[c];
+        if (c > 0 && s.tail && hipStreamWaitEvent(s0.stream, s.evP, 0) != hipSuccess) (void)hipEventSynchronize(s.evP);
+        s.tail = false;
+    }
     if (P == 0)
         for (Slot *s : b) launch_fill_u32(reinterpret_cast<uint32_t *>(s->fc_dev), 0u, sizeof(FrameCounters) / 4, s0.stream);
     launch_preprocess_multi(srv->dsc, srv->pdev, mo, srv->dop, s0.fb.dv_b, s0.fb.seg_count, s0.fb.gmap, s0.stream);
@@ -340,7 +351,10 @@ void finish(fgs_server *srv, Slot &s, int32_t status) {
             srv->st.rejected += 1;
     }
     srv->cv_done.notify_all();
-    // a failed request holds no image: its slot is free again at once
+    // a failed request holds no image: its slot is free again at once (its own
+    // stream orders the next request; another slot's waits for the tail)
+    s.tail = status != FGS_OK;
+    if (s.tail && hipEventRecord(s.evP, s.stream) != hipSuccess) (void)hipStreamSynchronize(s.stream);
     s.state = status == FGS_OK ? SlotState::DONE : SlotState::IDLE;
 }
 
