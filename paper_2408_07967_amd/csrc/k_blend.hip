@@ -138,8 +138,9 @@ __global__ __launch_bounds__(256 / kPx) __attribute__((amdgpu_waves_per_eu(8))) 
                     X1i = X1i > W ? W : X1i;
                     Y1i = Y1i > H ? H : Y1i;
                     const bool in = (X0i < X1i) & (Y0i < Y1i);
-                    return in & rect_hit(s.f0.x, s.f0.y, s.f0.z, s.f0.w, s.f1.x, k2, (float)X0i + 0.5f,
-                                         (float)X1i - 0.5f, (float)Y0i + 0.5f, (float)Y1i - 0.5f);
+                    return in & ((k2 == INFINITY) | rect_hit(s.f0.x, s.f0.y, s.f0.z, s.f0.w, s.f1.x, k2,
+                                                             (float)X0i + 0.5f, (float)X1i - 0.5f, (float)Y0i + 0.5f,
+                                                             (float)Y1i - 0.5f));
                 };
                 // (a quadrant counts only where its half is met, so that both
                 // forms blend the same entries)
