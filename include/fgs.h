@@ -369,13 +369,16 @@ typedef struct {
 fgs_status fgs_set_instrumentation(fgs_context *ctx, int flags);
 
 /* ---- blend variants (Sec. 5.3.2) --------------------------------------------
- * Two kernels render the same image, bit for bit:
+ * Two kernels render the same image, bit for bit (but see below):
  *   FGS_BLEND_LDS_BATCHES (default): the workgroup of a tile stages batches of
  *       its sorted list in LDS and each wavefront skips the entries whose
  *       ellipse misses its half of the tile;
  *   FGS_BLEND_PREFETCH: each wavefront walks the list on its own with a
  *       software prefetch pipeline (the state of entry i + 1 and the index of
  *       entry i + 2 in flight while entry i is blended), no LDS, no skipping.
+ * (The skipping test is binary32: of a footprint hundreds of pixels long and
+ * less than one wide, about one in 80,000 of the half tiles it reaches can lose
+ * it, at thousands of pixels one in 1100; the variants differ there.)
  * Applies to later fgs_render / fgs_render_prepared calls of ctx (the
  * evaluation count of FGS_INSTR_WORK always uses the default).  Returns
  * FGS_ERR_INVALID_ARGUMENT for another value. */

@@ -13,10 +13,10 @@ constexpr float kHalfLog2e = 0.72134752044448170f;  // log2(e) / 2
 
 // Conservative ellipse / rectangle test used only to skip work: the
 // rectangle [X0, X1] x [Y0, Y1] in pixel-sample coordinates (Alg. 3 with the
-// chord-overlap condition of Eq. 7).  Callers inflate k2 slightly so that no
-// contributor is ever skipped.
+// chord-overlap condition of Eq. 7).  Callers inflate k2 slightly, against the
+// test's roundings.
 // (Straight-line, and with its roundings written out: the tests of a tile's
-// regions share their lines' terms, and every form of the blend takes the same
+// regions share their lines' terms, and the blend and its adjoint take the same
 // decisions.)
 __device__ __forceinline__ bool rect_hit(float u, float v, float A, float B, float C, float k2, float X0, float X1,
                                          float Y0, float Y1) {
@@ -44,7 +44,11 @@ __device__ __forceinline__ bool rect_hit(float u, float v, float A, float B, flo
     return hit;
 }
 
-// The inflated extent of that test for the halves of a tile.
+// The inflated extent of that test for the halves of a tile.  (It does not cover
+// the cancellation described below: of the halves that a footprint contributes
+// to, as narrow as the low-pass leaves it and with a standard deviation of 1000
+// pixels along its length, the test drops one in 1100; of 200 pixels one in
+// 80,000; of 15 pixels none of 317,000.)
 __device__ __forceinline__ float test_extent(const GaussState &s) { return fmaf(s.f1.y, 1.00002f, 1e-5f); }
 
 // And for parts of a half, where it must drop nothing that the half's test
@@ -57,6 +61,23 @@ __device__ __forceinline__ float test_extent_thin(const GaussState &s) {
     const float ac = s.f0.z * s.f1.x, det = fmaf(-s.f0.w, s.f0.w, ac);
     const float k2i = fmaf(s.f1.y, fmaf(1e-6f * ac, __builtin_amdgcn_rcpf(det), 1.00002f), 1e-5f);
     return (det > 1e-6f * ac) & (k2i < INFINITY) ? k2i : INFINITY;
+}
+
+// Whether a Gaussian's ellipse, inflated to k2, meets the region
+// [X0, X0 + w) x [Y0, Y0 + 8) of pixels, cut by the image.
+__device__ __forceinline__ bool region_hit(const GaussState &s, float k2, int X0, int w, int Y0, int W, int H) {
+    int X1 = X0 + w, Y1 = Y0 + 8;
+    X1 = X1 > W ? W : X1;
+    Y1 = Y1 > H ? H : Y1;
+    const bool in = (X0 < X1) & (Y0 < Y1);
+    return in & rect_hit(s.f0.x, s.f0.y, s.f0.z, s.f0.w, s.f1.x, k2, (float)X0 + 0.5f, (float)X1 - 0.5f,
+                         (float)Y0 + 0.5f, (float)Y1 - 0.5f);
+}
+
+// Whether the half's test can have dropped a half with a contributor: the
+// discriminant's error is then more than half of what test_extent allows for.
+__device__ __forceinline__ bool half_test_decides(const GaussState &s, float k2t) {
+    return k2t > fmaf(s.f1.y, 1.00004f, 1e-5f);
 }
 
 // Staged form of a Gaussian for the pixel loop.  With c = log2(e) / 2 the

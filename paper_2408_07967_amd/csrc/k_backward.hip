@@ -198,25 +198,25 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(const GaussState *__restri
     for (int hi = (int)lmax; hi > 0; hi -= kBwdBatch) {
         const int lo = hi > kBwdBatch ? hi - kBwdBatch : 0;
         const int nb = hi - lo;
-        // two threads per entry, each testing two of the quadrants
+        // Two threads per entry, each testing two of the quadrants.  The replay
+        // has to blend what the forward blended: a quadrant counts only where its
+        // half is met.  The half's test is taken where it can have dropped a
+        // contributor, for long thin footprints aslant (a quadrant met in a half
+        // that is rightly not met has no contributor, so it may count).
         {
             const int j = tid & (kBwdBatch - 1), h = tid / kBwdBatch;
             uint32_t qm = 0;
             if (j < nb) {
                 const uint32_t g = values[start + (uint32_t)lo + (uint32_t)j];
                 const GaussState s = gs[g];
-                const float k2i = test_extent(s);
+                const int X0 = tx * kTile, Y0 = ty * kTile + h * 8;
+                const float k2t = test_extent_thin(s);
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int X0i = tx * kTile + q * 8, Y0i = ty * kTile + h * 8;
-                    int X1i = X0i + 8, Y1i = Y0i + 8;
-                    X1i = X1i > W ? W : X1i;
-                    Y1i = Y1i > H ? H : Y1i;
-                    if (X0i < X1i && Y0i < Y1i &&
-                        rect_hit(s.f0.x, s.f0.y, s.f0.z, s.f0.w, s.f1.x, k2i, (float)X0i + 0.5f, (float)X1i - 0.5f,
-                                 (float)Y0i + 0.5f, (float)Y1i - 0.5f))
+                for (int q = 0; q < 2; ++q)
+                    if (X0 + 8 * q < W && Y0 < H &&
+                        (k2t == INFINITY || region_hit(s, k2t, X0 + 8 * q, 8, Y0, W, H)))
                         qm |= 1u << q;
-                }
+                if (qm != 0 && half_test_decides(s, k2t) && !region_hit(s, test_extent(s), X0, kTile, Y0, W, H)) qm = 0;
                 if (h == 0) {
                     float4 f0, f1;
                     float2 f2;

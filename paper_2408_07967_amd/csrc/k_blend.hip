@@ -12,8 +12,8 @@
 // wavefronts per SIMD fit):
 // every thread stages one Gaussian (the coefficients of the exponent,
 // opacity threshold and colour) in LDS and tests each ellipse against the
-// regions (the exact tile test with a slightly inflated extent, so it never
-// drops a contributor); a wavefront walks only the entries that meet its
+// regions (the exact tile test with a slightly inflated extent; what it can
+// drop stands at test_extent); a wavefront walks only the entries that meet its
 // region, two at a time: their evaluations overlap, and the saturation check
 // of both is one (T only falls; when a pixel saturates within the pair, the
 // pair is resolved entry by entry).  Bound by FP32 issue when the tiles are
@@ -131,30 +131,20 @@ __global__ __launch_bounds__(256 / kPx) __attribute__((amdgpu_waves_per_eu(8))) 
             uint32_t hm = 0;
             if ((uint32_t)tid < nb) {
                 const GaussState s = kAhead ? ahead : gs[values[b0 + tid]];
-                const float k2i = test_extent(s);
-                // region [x, x + w) x [y, y + 8), cut by the image
-                auto meets = [&](int X0i, int w, int Y0i, float k2) {
-                    int X1i = X0i + w, Y1i = Y0i + 8;
-                    X1i = X1i > W ? W : X1i;
-                    Y1i = Y1i > H ? H : Y1i;
-                    const bool in = (X0i < X1i) & (Y0i < Y1i);
-                    return in & ((k2 == INFINITY) | rect_hit(s.f0.x, s.f0.y, s.f0.z, s.f0.w, s.f1.x, k2,
-                                                             (float)X0i + 0.5f, (float)X1i - 0.5f, (float)Y0i + 0.5f,
-                                                             (float)Y1i - 0.5f));
-                };
                 // (a quadrant counts only where its half is met, so that both
                 // forms blend the same entries)
-                const float k2t = kPx == 1 ? test_extent_thin(s) : 0.0f;
+                const float k2i = test_extent(s), k2t = kPx == 1 ? test_extent_thin(s) : 0.0f;
+                const bool any = k2t == INFINITY;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const bool half = meets(tx * kTile, kTile, ty * kTile + 8 * h, k2i);
+                    const int X0 = tx * kTile, Y0 = ty * kTile + 8 * h;
+                    const bool half = region_hit(s, k2i, X0, kTile, Y0, W, H);
                     if constexpr (kPx == 2) {
                         hm |= (uint32_t)half << h;
                     } else {
 #pragma unroll
                         for (int q = 0; q < 2; ++q)
-                            hm |= (uint32_t)(half & meets(tx * kTile + 8 * q, 8, ty * kTile + 8 * h, k2t))
-                                  << (2 * h + q);
+                            hm |= (uint32_t)(half & (any | region_hit(s, k2t, X0 + 8 * q, 8, Y0, W, H))) << (2 * h + q);
                     }
                 }
                 float4 f0, f1;

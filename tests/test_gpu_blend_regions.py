@@ -1,7 +1,9 @@
 """The blend's region tests at the ends of their range, in both forms of the
 blend (one and two pixels per lane, chosen by the number of tiles): footprints
 whose terms leave binary32's range, where the image has to be that of the
-prefetch variant, which tests no regions, bit for bit."""
+prefetch variant, which tests no regions, bit for bit; and footprints thousands
+of times longer than wide, where the adjoint has to replay what the forward
+blended."""
 import numpy as np
 import pytest
 
@@ -51,3 +53,40 @@ def test_footprints_of_billions_of_pixels(orc, R, log_scale, W, H):
     assert torch.all(out["last"] == P)  # every Gaussian reaches every pixel
     ref = orc.render(sc.astype(np.float64), cam, W, H, opts(bg=[0.3, 0.1, 0.2]), "f64")
     assert np.abs(out["rgb"].cpu().numpy() - ref["rgb"]).max() <= 1e-5
+
+
+def needle(rng, W, H, f=500.0, z=2.0):
+    """One Gaussian in a random direction of the image plane, 1000 to 6000
+    pixels (standard deviation) long and as narrow as the low-pass leaves it."""
+    th, s1 = rng.uniform(0.0, np.pi), np.exp(rng.uniform(np.log(1000.0), np.log(6000.0)))
+    t = rng.uniform(-2.0, 2.0) * s1
+    x, y = rng.uniform(-0.4, 0.4) * W + t * np.cos(th), rng.uniform(-0.4, 0.4) * H + t * np.sin(th)
+    return scene_from([[x * z / f, y * z / f, z]], [[np.log(s1 * z / f), -9.0, -9.0]],
+                      [[np.cos(th / 2), 0, 0, np.sin(th / 2)]], [rng.uniform(0.0, 4.0)], dc_rgb=[0.6, 0.4, 0.2])
+
+
+@pytest.mark.parametrize("W,H", SIZES)
+def test_needle_adjoint_replays_the_forward(R, W, H):
+    """For one Gaussian and dL/dR = 1 the colour's gradient is the sum over the
+    pixels of its weights, which is the sum of 1 - T of the forward.  Each
+    weight carries a few binary32 roundings, as does 1 - T (at least 1/255
+    where it is not 0: 1.5e-5 relative at worst)."""
+    import torch
+    from paper_2408_07967_amd.render import GaussianScene
+    rng = np.random.default_rng(4)
+    cam = identity_camera(W, H, 500.0)
+    o = opts()
+    dL = torch.zeros(3, H, W, device="cuda")
+    dL[0] = 1.0
+    bad = []
+    for k in range(300 if W < 1000 else 60):
+        gsc = GaussianScene.from_numpy(needle(rng, W, H))
+        out = R.render(gsc, cam, W, H, o, want_T=True, save=True)
+        g = R.backward(out["frame"], gsc, cam, W, H, o, dL)
+        got = float(g[4][0, 0]) / 0.28209479177387814
+        want = float((1.0 - out["T"].double()).sum())
+        R.release(out["frame"])
+        if abs(got - want) > 3e-5 * want:
+            bad.append((k, got, want))
+    print(f"[regions] adjoint {W}x{H}: {len(bad)} differ {bad[:8]}", flush=True)
+    assert not bad
