@@ -939,18 +939,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             }
         }
     }
-    // Raw parameters: a wavefront takes a contiguous range of Gaussians, drops
-    // those that are certainly not visible before the projection (raw_keep) and
-    // projects the others up to 64 at a time, from a ring of two wavefronts'
-    // Gaussians and their parameters in LDS.  Unless the frame is kept (`full`),
-    // its outputs are packed: the range's output slots from the first on, in
-    // the Gaussians' order (so equal depths keep it), the rest marked invalid.
+    // Raw parameters (kList): a wavefront takes a contiguous range of Gaussians,
+    // drops those that are certainly not visible before the projection (raw_keep)
+    // and projects the others up to 64 at a time, from a ring of two wavefronts'
+    // Gaussians and their parameters in LDS.  Its outputs are packed: the range's
+    // output slots from the first on, in the Gaussians' order (so equal depths
+    // keep it), the rest marked invalid.
     // Bound by HBM: 10M Gaussians of degree 3, 29 % visible, in 4K: 608 us for
     // 2.4 GB read (nearly every line of every plane holds a visible Gaussian's
     // element) and 0.25 GB written.  One pass over all Gaussians took 754: every
     // wavefront ran the whole projection, and 48-byte records 29 % apart were
-    // written as partial lines.  Listed, but written to the Gaussians' own
-    // slots, with a group's survivors split over two projections: 790.
+    // written as partial lines.  (With a group's survivors split over two
+    // projections, whose lines are then read twice, it was slower than one pass.)
     constexpr uint32_t kRing = 2 * kWave;
     constexpr int kTerms = sizeof(RawTerms) / sizeof(float);
     __shared__ uint32_t s_rg[kList ? kBlock / kWave : 1][kList ? kRing : 1];
@@ -975,7 +975,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const DevScene &sc = ba.sc;
     const DevPrepared &pp = ba.pp;
     const DevOptions &op = ba.op;
-    const bool full = ba.full != 0;
+    const bool full = !kList && ba.full != 0;
     // (Gaussian indices are below 2^31; P32: an idle lane)
     const uint32_t P32 = (uint32_t)P;
     uint32_t g = P32;
@@ -1000,11 +1000,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const bool in = gi < P;
             const RawTerms t = raw_terms(sc, in ? gi : P - 1);
             const bool keep = in && raw_keep(t, ba.cam, op, ba.W, ba.H);
-            if (full && in && !keep) {
-                ba.dkey[gi] = kInvalidKey;
-                ba.count8[gi] = 0;
-                ba.count[gi] = 0;
-            }
             const uint64_t km = __ballot(keep);
             if (keep) {
                 const uint32_t at = (__builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32),
@@ -1034,12 +1029,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
         q_head = (q_head + take) % kRing;
         n_queue -= take;
-        if (!full) {
-            ii = slot + (uint32_t)lane;
-            slot += take;
-        } else {
-            ii = g;
-        }
+        ii = slot + (uint32_t)lane;
+        slot += take;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     } else {
@@ -1398,11 +1389,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
     }  // camera loop
     }  // batch loop
-    if constexpr (!kPrep) {
+    if constexpr (kList) {
         // the range's slots without a projected Gaussian
         const int64_t end = (int64_t)grp_end * kWave < P ? (int64_t)grp_end * kWave : P;
-        if (kList && args.full == 0)
-            for (int64_t i = (int64_t)slot + lane; i < end; i += kWave) args.dkey[i] = kInvalidKey;
+        for (int64_t i = (int64_t)slot + lane; i < end; i += kWave) args.dkey[i] = kInvalidKey;
     }
     // The workgroup's visible and pair counts (of each camera) in one 64-bit
     // atomic: atomics on one line take about 8 ns each, one after the other,
@@ -1904,12 +1894,17 @@ void launch_preprocess(const DevScene &sc, const DevPrepared *pp, const DevCamer
                     MultiOut{}};
     if (pp)
         hipLaunchKernelGGL(k_preprocess<true>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
-    else if ((int64_t)preprocess_grid(sc.P) * kBlock < sc.P)
+    else if (!full && (int64_t)preprocess_grid(sc.P) * kBlock < sc.P)
         hipLaunchKernelGGL((k_preprocess<false, false, true>), dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
     else
         // every wavefront has one group of 64: there is nothing to merge, and
         // the list's test and its code would only add their latency (10,000
-        // Gaussians: 12.7 us with both forms in one kernel, 11.7 with this one)
+        // Gaussians: 12.7 us with both forms in one kernel, 11.7 with this one);
+        // or a kept frame, whose outputs go to the Gaussians' own slots, so that
+        // a list has nothing to pack and gains nothing (listed / this one, us, at
+        // 1080p: 300,000 Gaussians, 93 % visible, 50 / 46; 1M of them 107 / 102;
+        // the city, 29 % visible, 2M 186 / 188, 6M 560 / 554, 10M 934 / 933; 3M
+        // Gaussians of which none is visible 40 / 42)
         hipLaunchKernelGGL(k_preprocess<false>, dim3(preprocess_grid(sc.P)), dim3(kBlock), 0, s, a);
 }
 
