@@ -16,7 +16,8 @@ constexpr int kRadix = 1 << kRadixBits;
 constexpr int kRadixBitsMax = 9;  // a single pass may take a 9-bit digit
 constexpr int kRadixMax = 1 << kRadixBitsMax;
 constexpr uint32_t kInvalidKey = 0xffffffffu;
-constexpr uint32_t kSmallSort = 16384;  // keys that one workgroup sorts
+constexpr uint32_t kSmallSort = 12288;  // keys that one workgroup sorts
+constexpr uint32_t kSmallScan = 6144;   // counts that one workgroup scans
 
 // Camera and options passed by value: they land in the kernel-argument
 // segment and are read through scalar registers (the paper's constant-memory

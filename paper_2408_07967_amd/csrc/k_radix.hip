@@ -32,8 +32,8 @@ __device__ __forceinline__ uint32_t count_of(uint32_t n_host, const uint32_t *n_
     return nd < n_host ? nd : n_host;
 }
 
-// key range [lo, hi) of workgroup b: whole tiles of `granule` keys (4096 for
-// the sort passes) split evenly
+// key range [lo, hi) of workgroup b: whole tiles of `granule` keys (a sort pass's
+// own tile size) split evenly
 __device__ __forceinline__ void block_range(uint32_t n, uint32_t b, uint32_t nb, uint32_t *lo, uint32_t *hi,
                                             uint32_t granule = kSortTile) {
     const uint32_t tiles = (n + granule - 1) / granule;
@@ -418,11 +418,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
 // A pass of the grid sort takes two launches of some 4 and 7 us, whatever the
 // number of keys; one workgroup holds up to kSmallSort keys in its registers and
-// LDS and does all passes there.
+// LDS and does all passes there.  Its passes grow with the keys, so the limits
+// lie where the two are level.  A frame at 256 x 256, us, one workgroup's and the
+// grid's, for depths of 24 bits (three passes) and of more (four):
+//   sort   4096 keys 107 / 127 and 109 / 127, 8192 126 / 143 and 132 / 141,
+//          10240 133 / 145 and 142 / 143, 12288 140 / 149 and 149 / 145,
+//          14336 148 / 154 and 159 / 153, 16384 160 / 164 and 171 / 164
+//   scan   4096 counts 127 / 131, 6144 132 / 135, 8192 142 / 139, 10240 144 / 142,
+//          12288 149 / 141, 16384 164 / 142
+// and of both together beyond the scan's limit, 12288 140 / 141 and 149 / 140,
+// 14336 148 / 141 and 159 / 141.
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallWaves = kSmallBlock / kWave;
-constexpr int kSmallItems = 16;
-static_assert(kSmallSort == kSmallBlock * kSmallItems && kSmallSort <= 65536, "positions in 16 bits");
+constexpr int kSmallItems = kSmallSort / kSmallBlock;
+static_assert(kSmallSort % kSmallBlock == 0 && kSmallSort <= 65536, "positions in 16 bits");
+constexpr int kScanItems = kSmallScan / kSmallBlock;
+static_assert(kSmallScan % kSmallBlock == 0, "whole counts per thread");
 
 // Exclusive scan of one value per thread over a 1024-thread workgroup.
 __device__ __forceinline__ uint32_t small_exclusive_scan(uint32_t v, uint32_t *s_tmp, uint32_t *total) {
@@ -597,7 +608,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_sort_small(const uint32_t *keys
     }
 }
 
-// The scan of k_scan_upsweep and k_scan_downsweep over up to kSmallSort entries.
+// The scan of k_scan_upsweep and k_scan_downsweep over up to kSmallScan entries.
 __global__ __launch_bounds__(kSmallBlock) void k_scan_small(const uint32_t *__restrict__ order,
                                                             const uint8_t *__restrict__ count8,
                                                             const uint4 *__restrict__ erec, uint32_t n_host,
@@ -606,17 +617,17 @@ __global__ __launch_bounds__(kSmallBlock) void k_scan_small(const uint32_t *__re
     __shared__ uint32_t s_tmp[kSmallWaves];
     const uint32_t n = count_of(n_host, n_dev);
     const uint32_t per = (n + kSmallBlock - 1) / kSmallBlock, b = threadIdx.x * per;
-    uint32_t c[kSmallItems], own = 0;
+    uint32_t c[kScanItems], own = 0;
 #pragma unroll
-    for (int k = 0; k < kSmallItems; ++k) c[k] = (uint32_t)k < per && b + k < n ? order[b + k] : kInvalidKey;
-    uint32_t g[kSmallItems];
+    for (int k = 0; k < kScanItems; ++k) c[k] = (uint32_t)k < per && b + k < n ? order[b + k] : kInvalidKey;
+    uint32_t g[kScanItems];
 #pragma unroll
-    for (int k = 0; k < kSmallItems; ++k) {
+    for (int k = 0; k < kScanItems; ++k) {
         g[k] = c[k];
         c[k] = g[k] != kInvalidKey ? count8[g[k]] : 0u;
     }
 #pragma unroll
-    for (int k = 0; k < kSmallItems; ++k) {
+    for (int k = 0; k < kScanItems; ++k) {
         if (c[k] == kCount8Big) {  // a chunked rectangle (rare)
             const uint4 r = erec[g[k]];
             c[k] = super_span((int)(r.x & 0xffffu), (int)(r.x >> 16), (int)(r.y & 0xffffu), (int)(r.y >> 16));
@@ -626,7 +637,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_scan_small(const uint32_t *__re
     uint32_t all = 0;
     uint32_t ex = small_exclusive_scan(own, s_tmp, &all);
 #pragma unroll
-    for (int k = 0; k < kSmallItems; ++k) {
+    for (int k = 0; k < kScanItems; ++k) {
         if ((uint32_t)k < per && b + k < n) offsets[b + k] = ex;
         ex += c[k];
     }
@@ -1003,7 +1014,7 @@ void launch_count_scan(const uint32_t *order, const uint8_t *count8, const uint4
                        const uint32_t *n_dev, uint32_t *cs, uint32_t *sums, uint32_t *offsets, uint32_t *total,
                        hipStream_t s) {
     if (n_host == 0) return;
-    if (n_host <= kSmallSort) {
+    if (n_host <= kSmallScan) {
         hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kSmallBlock), 0, s, order, count8, erec, n_host, n_dev, offsets,
                            total);
         return;
