@@ -69,9 +69,14 @@ int plan_tile_passes(int bits, int *shift, int *width) {
 
 }  // namespace
 
+// (Each capacity is 0 while its buffers grow: where an allocation fails, the next
+// call finds none of them and grows them all, instead of using those that were
+// not reached, freed or null.)
+
 hipError_t ensure_gauss(FrameBuffers &b, size_t P) {
-    if (P <= b.capP && b.gs) return hipSuccess;
+    if (P <= b.capP && b.capP > 0) return hipSuccess;
     const size_t cap = P + P / 8 + 1024;
+    b.capP = 0;
     FGS_GROW(b.gs, cap);
     FGS_GROW(b.conic, cap);
     FGS_GROW(b.rect, cap);
@@ -92,6 +97,8 @@ hipError_t ensure_gauss(FrameBuffers &b, size_t P) {
 hipError_t ensure_pairs(FrameBuffers &b, size_t N) {
     if (N <= b.capN && b.tk_a) return hipSuccess;
     const size_t cap = (N + N / 4 + 4096 + 63) / 64 * 64;
+    b.capN = 0;
+    b.tk_b = b.tv_a = b.tv_b = nullptr;
     // one block for the four arrays
     FGS_GROW(b.tk_a, 4 * cap);
     b.tk_b = b.tk_a + cap;
@@ -103,7 +110,8 @@ hipError_t ensure_pairs(FrameBuffers &b, size_t N) {
 }
 
 hipError_t ensure_tiles(FrameBuffers &b, size_t tiles) {
-    if (tiles <= b.capTiles && b.ranges) return hipSuccess;
+    if (tiles <= b.capTiles && b.capTiles > 0) return hipSuccess;
+    b.capTiles = 0;
     FGS_GROW(b.ranges, tiles);
     FGS_GROW(b.sranges, tiles);
     b.capTiles = tiles;
@@ -111,7 +119,8 @@ hipError_t ensure_tiles(FrameBuffers &b, size_t tiles) {
 }
 
 hipError_t ensure_pixels(FrameBuffers &b, size_t pix) {
-    if (pix <= b.capPix && b.T) return hipSuccess;
+    if (pix <= b.capPix && b.capPix > 0) return hipSuccess;
+    b.capPix = 0;
     FGS_GROW(b.T, pix);
     FGS_GROW(b.last, pix);
     b.capPix = pix;
@@ -119,7 +128,7 @@ hipError_t ensure_pixels(FrameBuffers &b, size_t pix) {
 }
 
 hipError_t ensure_sort_scratch(SortScratch &s) {
-    if (s.rhist) return hipSuccess;
+    if (s.rhist && s.gsum && s.sums) return hipSuccess;
     FGS_GROW(s.rhist, (size_t)kSortBlocks * kRadixMax);
     FGS_GROW(s.gsum, (size_t)kGsumSlots * kGsumWords);
     FGS_GROW(s.sums, (size_t)kSortBlocks);
@@ -128,7 +137,8 @@ hipError_t ensure_sort_scratch(SortScratch &s) {
 
 hipError_t ensure_chunks(ChunkList &c, size_t need) {
     need = (std::max<size_t>(need, 65536) + kChunkCapAlign - 1) / kChunkCapAlign * kChunkCapAlign;
-    if (need <= c.cap && c.chunks) return hipSuccess;
+    if (need <= c.cap && c.cap > 0) return hipSuccess;
+    c.cap = 0;
     FGS_GROW(c.chunks, need);
     FGS_GROW(c.mask, need * (kChunkTiles / 32));
     FGS_GROW(c.big, need);
