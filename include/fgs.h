@@ -238,8 +238,9 @@ fgs_status fgs_render_noalloc(fgs_context *ctx, const fgs_scene *scene, const fg
  * cull skips the batches whose every member it would cull.  Frames re-order
  * equal depths by Gaussian index, so the pair order is still the method's.
  * Device memory owned by the context: 60 B + 4 ceil4(3 (D+1)^2) B per
- * Gaussian (252 B at degree 3) and 48 B per batch, plus 16 B per Gaussian and
- * the sort scratch during the call.  It depends on the
+ * Gaussian (252 B at degree 3) and 48 B per batch, plus 20 B per Gaussian and
+ * the sort scratch during the call (a kept block, see below, may be up to twice
+ * as large as the scene needs).  It depends on the
  * scene's values (copy of the fgs_scene struct kept; the planes must stay
  * valid and unchanged for backward passes) and on opt->alpha_min and
  * opt->cap_3sigma.  Frames rendered from it are bit-identical to fgs_render
@@ -247,7 +248,12 @@ fgs_status fgs_render_noalloc(fgs_context *ctx, const fgs_scene *scene, const fg
 typedef struct fgs_prepared fgs_prepared;
 fgs_status fgs_prepare_scene(fgs_context *ctx, const fgs_scene *scene, const fgs_options *opt, fgs_prepared **out,
                              void *stream);
-/* Waits for the device, then frees the precompute (NULL is ignored). */
+/* Waits for the device, then gives the precompute up (NULL is ignored).  Its
+ * memory is freed, except that while a quarter of the device's memory is free
+ * the context keeps one such block, of at most 512 MiB, for the next scene it
+ * prepares.  The block counts in fgs_scratch_bytes; it is freed as soon as an
+ * allocation of any context or server of the process on that device would
+ * otherwise fail, and by fgs_destroy. */
 fgs_status fgs_prepared_release(fgs_context *ctx, fgs_prepared *prepared);
 /* fgs_render from a prepared scene.  opt: NULL means defaults; its
  * alpha_min and cap_3sigma must equal those of the preparation. */

@@ -7,6 +7,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
+#include <vector>
 
 namespace fgs {
 
@@ -21,7 +23,7 @@ hipError_t grow(T *&p, size_t n_need) {
         (void)hipFree(p);
     }
     p = nullptr;
-    return hipMalloc((void **)&p, (n_need ? n_need : 1) * sizeof(T));
+    return device_malloc((void **)&p, (n_need ? n_need : 1) * sizeof(T));
 }
 
 #define FGS_GROW(p, n)                       \
@@ -283,17 +285,9 @@ hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBu
         return used;
     };
     const size_t need = lay_out(nullptr);
-    if (spare && spare->block && spare->bytes >= need && spare->bytes / 2 <= need) {
-        pb.block = spare->block;
-        pb.block_bytes = spare->bytes;
-        *spare = SpareBlock{};
-    } else {
-        e = hipMalloc(&pb.block, need);
-        if (e == hipErrorOutOfMemory && spare && spare->block) {
-            (void)hipGetLastError();
-            spare->drop();
-            e = hipMalloc(&pb.block, need);
-        }
+    pb.block = spare ? spare->get(need, &pb.block_bytes) : nullptr;
+    if (!pb.block) {
+        e = device_malloc(&pb.block, need);
         if (e != hipSuccess) {
             pb.block = nullptr;
             return e;
@@ -322,12 +316,7 @@ hipError_t build_prepared(const fgs_scene &sc, const fgs_options &op, PreparedBu
         return used;
     };
     void *tmp = nullptr;
-    e = hipMalloc(&tmp, lay_out_tmp(nullptr));
-    if (e == hipErrorOutOfMemory && spare && spare->block) {
-        (void)hipGetLastError();
-        spare->drop();
-        e = hipMalloc(&tmp, lay_out_tmp(nullptr));
-    }
+    e = device_malloc(&tmp, lay_out_tmp(nullptr));
     if (e != hipSuccess) return e;
     lay_out_tmp(static_cast<char *>(tmp));
     const uint32_t P32 = (uint32_t)(P > 0 ? P : 0);
@@ -351,19 +340,87 @@ void free_prepared(PreparedBuffers &pb) {
     pb = PreparedBuffers{};
 }
 
-void SpareBlock::drop() {
-    free_p(block);
-    bytes = 0;
+namespace {
+// the spare blocks of the process's contexts (never destroyed: a context may
+// outlive the library's statics)
+struct SpareList {
+    std::mutex mu;
+    std::vector<SpareBlock *> all;
+};
+SpareList &spare_list() {
+    static SpareList *const l = new SpareList();
+    return *l;
+}
+}  // namespace
+
+SpareBlock::SpareBlock() {
+    SpareList &l = spare_list();
+    std::lock_guard<std::mutex> lk(l.mu);
+    l.all.push_back(this);
 }
 
-void SpareBlock::take(PreparedBuffers &pb) {
-    if (pb.block && pb.block_bytes <= kMax && pb.block_bytes >= bytes) {
-        drop();
-        block = pb.block;
-        bytes = pb.block_bytes;
+SpareBlock::~SpareBlock() {
+    SpareList &l = spare_list();
+    std::lock_guard<std::mutex> lk(l.mu);
+    l.all.erase(std::find(l.all.begin(), l.all.end(), this));
+}
+
+void SpareBlock::drop() {
+    std::lock_guard<std::mutex> lk(spare_list().mu);
+    free_p(block_);
+    bytes_ = 0;
+}
+
+void SpareBlock::put(PreparedBuffers &pb) {
+    size_t free_bytes = 0, total = 0;
+    const bool roomy = pb.block && pb.block_bytes <= kMax && hipMemGetInfo(&free_bytes, &total) == hipSuccess &&
+                       free_bytes >= total / 4;
+    std::lock_guard<std::mutex> lk(spare_list().mu);
+    if (roomy && pb.block_bytes >= bytes_ && hipGetDevice(&device_) == hipSuccess) {
+        free_p(block_);
+        block_ = pb.block;
+        bytes_ = pb.block_bytes;
         pb.block = nullptr;
     }
     free_prepared(pb);
+}
+
+void *SpareBlock::get(size_t need, size_t *bytes) {
+    std::lock_guard<std::mutex> lk(spare_list().mu);
+    if (!block_ || bytes_ < need || bytes_ / 2 > need) return nullptr;
+    void *const p = block_;
+    *bytes = bytes_;
+    block_ = nullptr;
+    bytes_ = 0;
+    return p;
+}
+
+size_t SpareBlock::held() const {
+    std::lock_guard<std::mutex> lk(spare_list().mu);
+    return bytes_;
+}
+
+bool release_spare_blocks(int device) {
+    SpareList &l = spare_list();
+    std::lock_guard<std::mutex> lk(l.mu);
+    bool any = false;
+    for (SpareBlock *s : l.all)
+        if (s->block_ && s->device_ == device) {
+            free_p(s->block_);
+            s->bytes_ = 0;
+            any = true;
+        }
+    return any;
+}
+
+hipError_t device_malloc(void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    int device = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&device) == hipSuccess && release_spare_blocks(device)) {
+        (void)hipGetLastError();
+        e = hipMalloc(p, bytes);
+    }
+    return e;
 }
 
 hipError_t SideStream::create() {

@@ -206,14 +206,37 @@ struct PreparedBuffers {
 // At most one released precompute block, of at most kMax bytes, kept for the
 // next scene of about its size: allocating and freeing 0.25 GB takes 0.3 ms at
 // best and has taken 3 ms, as long as building a 1M-Gaussian precompute and
-// its first frame.  Holds no live data: nothing on the device uses it.
-struct SpareBlock {
+// its first frame.  Holds no live data: nothing on the device uses it.  Kept
+// only while a quarter of the device's memory is free, and given back as soon
+// as an allocation of any context or server of the process fails for want of
+// memory (device_malloc); the blocks of all contexts are listed for that, under
+// one lock, so each context may be on its own thread.
+class SpareBlock {
+  public:
     static constexpr size_t kMax = (size_t)512 << 20;
-    void *block = nullptr;
-    size_t bytes = 0;
-    void drop();                  // free it
-    void take(PreparedBuffers &pb);  // keep pb's block if it may be kept, else free it; empties pb
+    SpareBlock();
+    ~SpareBlock();
+    SpareBlock(const SpareBlock &) = delete;
+    SpareBlock &operator=(const SpareBlock &) = delete;
+    void drop();                               // free it
+    void put(PreparedBuffers &pb);             // keep pb's block if it may be kept, else free it; empties pb
+    void *get(size_t need, size_t *bytes);     // the block, if it holds need bytes and not twice as many
+    size_t held() const;                       // its bytes
+
+  private:
+    friend bool release_spare_blocks(int device);
+    void *block_ = nullptr;
+    size_t bytes_ = 0;
+    int device_ = 0;
 };
+
+// Frees the blocks that contexts of this process keep on a device; whether there
+// was one.
+bool release_spare_blocks(int device);
+
+// hipMalloc on the current device; where it fails for want of memory, once more
+// after the kept blocks are freed.
+hipError_t device_malloc(void **p, size_t bytes);
 
 // Allocate (or take from spare, which may be NULL) and fill the precompute of
 // sc for options op on stream s, in a spatial slot order (Morton order of the

@@ -109,19 +109,6 @@ fgs_status hip_fail(fgs_context *ctx, hipError_t e, const char *what) {
         if (e_ != hipSuccess) return hip_fail(ctx, e_, #expr); \
     } while (0)
 
-// An allocation: the spare block is given back before it fails for want of
-// memory.
-#define HIP_TRY_MEM(ctx, expr)                                    \
-    do {                                                          \
-        hipError_t e_ = (expr);                                   \
-        if (e_ == hipErrorOutOfMemory && (ctx)->spare.block) {    \
-            (void)hipGetLastError();                              \
-            (ctx)->spare.drop();                                  \
-            e_ = (expr);                                          \
-        }                                                         \
-        if (e_ != hipSuccess) return hip_fail(ctx, e_, #expr);    \
-    } while (0)
-
 fgs_status validate(fgs_context *ctx, const fgs_scene *sc, const fgs_camera *cam, int32_t W, int32_t H,
                     const fgs_options *opt) {
     std::string m;
@@ -230,7 +217,7 @@ fgs_status fgs_create(int device, fgs_context **out) {
     if (hipSetDevice(device) != hipSuccess) return fail(nullptr, FGS_ERR_DEVICE, "hipSetDevice failed");
     fgs_context *ctx = new fgs_context();
     ctx->device = device;
-    if (hipMalloc((void **)&ctx->fc_dev, sizeof(FrameCounters)) != hipSuccess ||
+    if (device_malloc((void **)&ctx->fc_dev, sizeof(FrameCounters)) != hipSuccess ||
         hipHostMalloc((void **)&ctx->fc_host, sizeof(FrameCounters), hipHostMallocDefault) != hipSuccess) {
         fgs_destroy(ctx);
         return fail(nullptr, FGS_ERR_OUT_OF_MEMORY, "cannot allocate frame counters");
@@ -296,12 +283,12 @@ fgs_status fgs_reserve(fgs_context *ctx, int64_t max_gaussians, int64_t max_pair
     if (max_gaussians > 0x7fffffffLL || max_pairs > 0xffffffffLL)
         return fail(ctx, FGS_ERR_INVALID_ARGUMENT, "reservation beyond 32-bit indices");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY_MEM(ctx, ensure_gauss(ctx->fb, (size_t)max_gaussians));
-    HIP_TRY_MEM(ctx, ensure_pairs(ctx->fb, (size_t)max_pairs));
+    HIP_TRY(ctx, ensure_gauss(ctx->fb, (size_t)max_gaussians));
+    HIP_TRY(ctx, ensure_pairs(ctx->fb, (size_t)max_pairs));
     const size_t tiles = (size_t)((max_w + kTile - 1) / kTile) * ((max_h + kTile - 1) / kTile);
-    HIP_TRY_MEM(ctx, ensure_tiles(ctx->fb, tiles));
-    HIP_TRY_MEM(ctx, ensure_chunks(ctx->ch, (size_t)max_gaussians / 8));
-    HIP_TRY_MEM(ctx, ensure_sort_scratch(ctx->ss));
+    HIP_TRY(ctx, ensure_tiles(ctx->fb, tiles));
+    HIP_TRY(ctx, ensure_chunks(ctx->ch, (size_t)max_gaussians / 8));
+    HIP_TRY(ctx, ensure_sort_scratch(ctx->ss));
     return FGS_OK;
 }
 
@@ -309,8 +296,8 @@ size_t fgs_scratch_bytes(const fgs_context *ctx) {
     if (!ctx) return 0;
     size_t b = ctx->fb.bytes() + sizeof(FrameCounters) + ctx->ch.bytes() + (ctx->ss.rhist ? SortScratch::bytes() : 0);
     b += kAccStride * ctx->gacc_cap * sizeof(float);
-    for (const fgs_prepared *p : ctx->prepared) b += p->pb.bytes();
-    b += ctx->spare.bytes;
+    for (const fgs_prepared *p : ctx->prepared) b += p->pb.block_bytes;
+    b += ctx->spare.held();
     for (const FrameBuffers &p : ctx->pool) b += p.bytes();
     for (const fgs_frame *f : ctx->frames) b += f->fb.bytes();
     for (const auto &bc : ctx->batch)
@@ -355,11 +342,11 @@ fgs_status render_impl(fgs_context *ctx, const fgs_scene *scene, const fgs_prepa
     const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kTile - 1) / kTile;
     const uint32_t ntiles = (uint32_t)tiles_x * (uint32_t)tiles_y;
     const size_t npix = (size_t)W * H;
-    HIP_TRY_MEM(ctx, ensure_gauss(fb, (size_t)P));
-    HIP_TRY_MEM(ctx, ensure_tiles(fb, ntiles));
-    HIP_TRY_MEM(ctx, ensure_sort_scratch(ctx->ss));
-    if (saved) HIP_TRY_MEM(ctx, ensure_pixels(fb, npix));
-    HIP_TRY_MEM(ctx, ensure_chunks(ctx->ch, (size_t)P / 8));
+    HIP_TRY(ctx, ensure_gauss(fb, (size_t)P));
+    HIP_TRY(ctx, ensure_tiles(fb, ntiles));
+    HIP_TRY(ctx, ensure_sort_scratch(ctx->ss));
+    if (saved) HIP_TRY(ctx, ensure_pixels(fb, npix));
+    HIP_TRY(ctx, ensure_chunks(ctx->ch, (size_t)P / 8));
 
     const DevScene dsc = to_dev(*scene);
     const DevCamera dcam = to_dev(*cam);
@@ -407,7 +394,7 @@ fgs_status render_impl(fgs_context *ctx, const fgs_scene *scene, const fgs_prepa
             // the large rectangles; it is redone)
             if (attempt > 0) return fail(ctx, FGS_ERR_INTERNAL, "chunk list overflow after resizing");
             if (spec_cap) HIP_TRY(ctx, hipStreamSynchronize(s));  // the list is in use
-            HIP_TRY_MEM(ctx, ensure_chunks(ctx->ch, (size_t)ctx->fc_host->nchunks + (size_t)ctx->fc_host->nchunks / 8));
+            HIP_TRY(ctx, ensure_chunks(ctx->ch, (size_t)ctx->fc_host->nchunks + (size_t)ctx->fc_host->nchunks / 8));
             continue;
         }
         V = ctx->fc_host->visible;
@@ -447,7 +434,7 @@ fgs_status render_impl(fgs_context *ctx, const fgs_scene *scene, const fgs_prepa
         // no second half yet, or it ran out of pair buffer: grow the buffers
         // (after it has finished with them) and enqueue it again
         if (spec_cap) HIP_TRY(ctx, hipStreamSynchronize(s));
-        HIP_TRY_MEM(ctx, ensure_pairs(fb, Ncap));
+        HIP_TRY(ctx, ensure_pairs(fb, Ncap));
         tiles_in_a = enqueue_back(W, H, dop, (uint32_t)P, fb, ctx->ch, ctx->ss, ctx->fc_dev, out_rgb, Tdst, Ldst,
                                   work, s, mk, ctx->blend_variant, ctx->side.join);
     }
@@ -713,7 +700,7 @@ fgs_status fgs_prepared_release(fgs_context *ctx, fgs_prepared *p) {
             (void)hipSetDevice(ctx->device);
             // frames may still read it; a failure stays with the block
             if (hipDeviceSynchronize() == hipSuccess)
-                ctx->spare.take(p->pb);
+                ctx->spare.put(p->pb);
             else
                 free_prepared(p->pb);
             delete p;
@@ -764,16 +751,16 @@ fgs_status fgs_render_prepared_batch(fgs_context *ctx, const fgs_prepared *p, co
     const int64_t P = p->scene.num_gaussians;
     const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kTile - 1) / kTile;
     const uint32_t ntiles = (uint32_t)tiles_x * (uint32_t)tiles_y;
-    if (!ctx->bfc_dev) HIP_TRY_MEM(ctx, hipMalloc((void **)&ctx->bfc_dev, kMaxCams * sizeof(FrameCounters)));
+    if (!ctx->bfc_dev) HIP_TRY(ctx, device_malloc((void **)&ctx->bfc_dev, kMaxCams * sizeof(FrameCounters)));
     if (!ctx->bfc_host)
         HIP_TRY(ctx, hipHostMalloc((void **)&ctx->bfc_host, kMaxCams * sizeof(FrameCounters), hipHostMallocDefault));
     if (ctx->batch.size() < (size_t)ncams) ctx->batch.resize(ncams);
     for (int c = 0; c < ncams; ++c) {
         auto &bc = ctx->batch[c];
-        HIP_TRY_MEM(ctx, ensure_gauss(bc.fb, (size_t)P));
-        HIP_TRY_MEM(ctx, ensure_tiles(bc.fb, ntiles));
-        HIP_TRY_MEM(ctx, ensure_sort_scratch(bc.ss));
-        HIP_TRY_MEM(ctx, ensure_chunks(bc.ch, (size_t)P / 8));
+        HIP_TRY(ctx, ensure_gauss(bc.fb, (size_t)P));
+        HIP_TRY(ctx, ensure_tiles(bc.fb, ntiles));
+        HIP_TRY(ctx, ensure_sort_scratch(bc.ss));
+        HIP_TRY(ctx, ensure_chunks(bc.ch, (size_t)P / 8));
     }
     const DevScene dsc = to_dev(p->scene);
     const DevOptions dop = to_dev(opt);
@@ -871,7 +858,7 @@ fgs_status fgs_render_prepared_batch(fgs_context *ctx, const fgs_prepared *p, co
         HIP_TRY(ctx, hipStreamSynchronize(s));  // the lists are in use (s has joined the side stream)
         for (int c = 0; c < ncams; ++c) {
             const size_t need = ctx->bfc_host[c].nchunks;
-            HIP_TRY_MEM(ctx, ensure_chunks(ctx->batch[c].ch, need + need / 8));
+            HIP_TRY(ctx, ensure_chunks(ctx->batch[c].ch, need + need / 8));
         }
     }
     bool synced = false;
@@ -885,7 +872,7 @@ fgs_status fgs_render_prepared_batch(fgs_context *ctx, const fgs_prepared *p, co
             // the side stream) and enqueue it on s
             if (!synced) HIP_TRY(ctx, hipStreamSynchronize(s));
             synced = true;
-            HIP_TRY_MEM(ctx, ensure_pairs(bc.fb, Ncap));
+            HIP_TRY(ctx, ensure_pairs(bc.fb, Ncap));
             (void)enqueue_back(W, H, dop, (uint32_t)P, bc.fb, bc.ch, bc.ss, ctx->bfc_dev + c, out_rgb[c],
                                out_T ? out_T[c] : nullptr, out_last ? out_last[c] : nullptr, nullptr, s, nomk,
                                ctx->blend_variant);
@@ -1049,7 +1036,7 @@ fgs_status fgs_set_instrumentation(fgs_context *ctx, int flags) {
             for (hipEvent_t &e : set)
                 if (!e) HIP_TRY(ctx, hipEventCreate(&e));
     if ((flags & FGS_INSTR_WORK) && !ctx->work_dev)
-        HIP_TRY_MEM(ctx, hipMalloc((void **)&ctx->work_dev, 2 * sizeof(unsigned long long)));
+        HIP_TRY(ctx, device_malloc((void **)&ctx->work_dev, 2 * sizeof(unsigned long long)));
     if (ctx->work_dev) HIP_TRY(ctx, hipMemset(ctx->work_dev, 0, 2 * sizeof(unsigned long long)));
     ctx->instr = flags;
     ctx->ev_pending = -1;
@@ -1122,9 +1109,9 @@ fgs_status fgs_measure_peaks(fgs_context *ctx, fgs_peaks *out) {
         }
         return hipGetLastError();
     };
-    hipError_t e = hipMalloc((void **)&sink, sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&a, copy_bytes);
-    if (e == hipSuccess) e = hipMalloc(&b, copy_bytes);
+    hipError_t e = device_malloc((void **)&sink, sizeof(float));
+    if (e == hipSuccess) e = device_malloc(&a, copy_bytes);
+    if (e == hipSuccess) e = device_malloc(&b, copy_bytes);
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e == hipSuccess) e = hipMemsetAsync(a, 0, copy_bytes, s);
@@ -1189,7 +1176,7 @@ fgs_status fgs_render_backward(fgs_context *ctx, const fgs_frame *frame, const f
             ctx->gacc = nullptr;
             ctx->gacc_cap = 0;
         }
-        HIP_TRY_MEM(ctx, hipMalloc((void **)&ctx->gacc, kAccStride * cap * sizeof(float)));
+        HIP_TRY(ctx, device_malloc((void **)&ctx->gacc, kAccStride * cap * sizeof(float)));
         ctx->gacc_cap = cap;
     }
     // cleared with a fill kernel (no memset node if the caller captures a graph)

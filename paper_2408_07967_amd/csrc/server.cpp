@@ -617,7 +617,7 @@ fgs_status fgs_server_create(int device, const fgs_scene *scene, const fgs_optio
     const size_t tiles =
         (size_t)((cfg->max_width + kTile - 1) / kTile) * (size_t)((cfg->max_height + kTile - 1) / kTile);
     const size_t pix = (size_t)cfg->max_width * cfg->max_height;
-    hipError_t e = hipMalloc((void **)&srv->arena_base, (size_t)cfg->budget_bytes);
+    hipError_t e = device_malloc((void **)&srv->arena_base, (size_t)cfg->budget_bytes);
     if (e == hipSuccess) e = build_prepared(*scene, srv->opt, srv->prep, nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     srv->pdev = srv->prep.dev();
@@ -637,9 +637,9 @@ fgs_status fgs_server_create(int device, const fgs_scene *scene, const fgs_optio
         if ((e = ensure_tiles(s.fb, tiles)) != hipSuccess) break;
         if ((e = ensure_chunks(s.ch, P / 8)) != hipSuccess) break;
         if ((e = ensure_sort_scratch(s.ss)) != hipSuccess) break;
-        if ((e = hipMalloc((void **)&s.fc_dev, sizeof(FrameCounters))) != hipSuccess) break;
+        if ((e = device_malloc((void **)&s.fc_dev, sizeof(FrameCounters))) != hipSuccess) break;
         if ((e = hipHostMalloc((void **)&s.fc_host, sizeof(FrameCounters), hipHostMallocDefault)) != hipSuccess) break;
-        if ((e = hipMalloc((void **)&s.img, 3 * pix * sizeof(float))) != hipSuccess) break;
+        if ((e = device_malloc((void **)&s.img, 3 * pix * sizeof(float))) != hipSuccess) break;
         s.fb.pairs_owned = false;
         slot_bytes += s.fb.bytes() + s.ch.bytes() + SortScratch::bytes() + 3 * pix * sizeof(float);
     }

@@ -32,7 +32,7 @@ def driver():
     shutil.rmtree(td, ignore_errors=True)
 
 
-@pytest.mark.parametrize("what", ["growth"])
+@pytest.mark.parametrize("what", ["growth", "spare", "threads"])
 def test_memory(driver, what):
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "memory ok" in r.stdout, r.stdout + r.stderr[:4000]
