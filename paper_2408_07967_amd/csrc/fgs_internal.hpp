@@ -380,8 +380,9 @@ void launch_count_scan(const uint32_t *order, const uint8_t *count8, const uint4
 void launch_single_range(uint2 *ranges, uint32_t n, const uint32_t *n_dev, hipStream_t s);
 
 // work: if non-null, work[0] += the number of list entries every pixel
-// examines, work[1] += the (wavefront, entry) steps the blend executes (a
-// separate, slower kernel instantiation)
+// examines, work[1] += the (wavefront, entry) steps that the form with two
+// pixels per lane executes (a separate, slower instantiation of that form,
+// whatever the number of tiles)
 // variant: 0 the LDS-batched blend; 1 the prefetch-pipeline blend (same
 // image bit for bit; not with work).  nvalues, ngs: entries held by the
 // values and gs buffers (the bounds of the variant's buffer loads).
@@ -390,7 +391,8 @@ void launch_blend(const GaussState *gs, const uint32_t *values, const uint2 *ran
                   int variant, uint32_t nvalues, uint32_t ngs, hipStream_t s);
 
 // Adjoint of the blend: accumulates per-Gaussian sums (acc_stride floats per
-// Gaussian, always kAccStride: one 64-byte line; cleared by the caller) from
+// Gaussian, kAccStride: one 64-byte line, any other stride is a launch error;
+// cleared by the caller) from
 // dL/dRGB, replaying each pixel's tile list back to front from its final
 // transmittance and last contributor.
 constexpr int kAccStride = 16;

@@ -480,24 +480,28 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd(DevScene sc, DevCamer
 
 }  // namespace
 
+// Threads of a workgroup for accumulators of acc_stride floats per Gaussian: the
+// kernels know one layout, and a launch of no threads is refused by the runtime,
+// so that the caller's check of its last error sees another one.
+static unsigned bwd_threads(int64_t acc_stride) { return acc_stride == kAccStride ? (unsigned)kBlock : 0u; }
+
 void launch_blend_backward(const GaussState *gs, const uint32_t *values, const uint2 *ranges, const float *Tfin,
                            const uint32_t *last, const float *dL, int W, int H, const DevOptions &op, float *acc,
                            int64_t acc_stride, hipStream_t s) {
-    if (acc_stride != kAccStride) return;  // (the kernels' layout)
     const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kTile - 1) / kTile;
-    hipLaunchKernelGGL(k_blend_bwd, dim3((unsigned)(tiles_x * tiles_y)), dim3(kBlock), 0, s, gs, values, ranges,
-                       Tfin, last, dL, W, H, tiles_x, op, acc);
+    hipLaunchKernelGGL(k_blend_bwd, dim3((unsigned)(tiles_x * tiles_y)), dim3(bwd_threads(acc_stride)), 0, s, gs,
+                       values, ranges, Tfin, last, dL, W, H, tiles_x, op, acc);
 }
 
 void launch_preprocess_backward(const DevScene &sc, const DevCamera &cam, const DevOptions &op, int W, int H,
                                 const GaussState *gs, const float *acc, int64_t acc_stride, float *g_means,
                                 float *g_log_scales, float *g_quats, float *g_logits, float *g_sh,
                                 int64_t grad_stride, hipStream_t s) {
-    if (sc.P <= 0 || acc_stride != kAccStride) return;
+    if (sc.P <= 0) return;
     DevGrad gr{g_means, g_log_scales, g_quats, g_logits, g_sh, grad_stride};
     const int64_t blocks = (sc.P + kBlock - 1) / kBlock;
     const unsigned grid = (unsigned)(blocks < 8192 ? blocks : 8192);
-    hipLaunchKernelGGL(k_preprocess_bwd, dim3(grid), dim3(kBlock), 0, s, sc, cam, op, W, H, gs, acc, gr);
+    hipLaunchKernelGGL(k_preprocess_bwd, dim3(grid), dim3(bwd_threads(acc_stride)), 0, s, sc, cam, op, W, H, gs, acc, gr);
 }
 
 }  // namespace fgs

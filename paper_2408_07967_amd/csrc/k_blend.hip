@@ -81,6 +81,7 @@ __global__ __launch_bounds__(256 / kPx) __attribute__((amdgpu_waves_per_eu(8))) 
     // whole pairs with entry kBatch).  kPx == 2: s_rel[h][w]: bit i set iff
     // entry 64 w + i meets region h; its set bits are walked in scalar code.
     constexpr bool kList = kPx == 1;
+    static_assert(!kList || !kCountWork, "work is counted on the halves");
     __shared__ uint8_t s_hit[kList ? kBatch : 1];
     __shared__ alignas(4) uint16_t s_list[kList ? kRegions : 1][kList ? kBatch + 2 : 2];
     __shared__ uint32_t s_rel[kList ? 1 : kRegions][kWords][2];
@@ -257,7 +258,6 @@ __global__ __launch_bounds__(256 / kPx) __attribute__((amdgpu_waves_per_eu(8))) 
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 for (uint32_t q = 0; q < n; q += 2) {
                     const uint32_t pair = *reinterpret_cast<const uint32_t *>(list + q);
-                    if (kCountWork) wsteps += q + 1 < n ? 2u : 1u;
                     if (blend_two(pair & 0xffffu, pair >> 16)) break;
                 }
             } else {
