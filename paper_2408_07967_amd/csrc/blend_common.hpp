@@ -56,11 +56,13 @@ __device__ __forceinline__ float test_extent(const GaussState &s) { return fmaf(
 // ellipse's height (y^2 <= k^2 A / det) its terms reach 4 A k^2 (A C / det),
 // so a few roundings of them move it as a change of about 5e-7 (A C / det) in
 // k^2 would.  Twice that, and 2e-5 for the rest; a conic too thin to tell, or
-// whose products leave binary32's range, always hits (INFINITY).
+// whose products leave binary32's range (0 times infinity), always hits.  (The
+// extent is then large, but finite: the test multiplies it by a conic entry,
+// which may be 0.)
 __device__ __forceinline__ float test_extent_thin(const GaussState &s) {
     const float ac = s.f0.z * s.f1.x, det = fmaf(-s.f0.w, s.f0.w, ac);
     const float k2i = fmaf(s.f1.y, fmaf(1e-6f * ac, __builtin_amdgcn_rcpf(det), 1.00002f), 1e-5f);
-    return (det > 1e-6f * ac) & (k2i < INFINITY) ? k2i : INFINITY;
+    return det > 1e-6f * ac ? fminf(k2i, 1e36f) : 1e36f;
 }
 
 // Whether a Gaussian's ellipse, inflated to k2, meets the region

@@ -213,9 +213,7 @@ __global__ __launch_bounds__(kBlock) void k_blend_bwd(const GaussState *__restri
                 const float k2t = test_extent_thin(s);
 #pragma unroll
                 for (int q = 0; q < 2; ++q)
-                    if (X0 + 8 * q < W && Y0 < H &&
-                        (k2t == INFINITY || region_hit(s, k2t, X0 + 8 * q, 8, Y0, W, H)))
-                        qm |= 1u << q;
+                    if (X0 + 8 * q < W && Y0 < H && region_hit(s, k2t, X0 + 8 * q, 8, Y0, W, H)) qm |= 1u << q;
                 if (qm != 0 && half_test_decides(s, k2t) && !region_hit(s, test_extent(s), X0, kTile, Y0, W, H)) qm = 0;
                 if (h == 0) {
                     float4 f0, f1;

@@ -135,7 +135,6 @@ __global__ __launch_bounds__(256 / kPx) __attribute__((amdgpu_waves_per_eu(8))) 
                 // (a quadrant counts only where its half is met, so that both
                 // forms blend the same entries)
                 const float k2i = test_extent(s), k2t = kPx == 1 ? test_extent_thin(s) : 0.0f;
-                const bool any = k2t == INFINITY;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int X0 = tx * kTile, Y0 = ty * kTile + 8 * h;
@@ -145,7 +144,7 @@ __global__ __launch_bounds__(256 / kPx) __attribute__((amdgpu_waves_per_eu(8))) 
                     } else {
 #pragma unroll
                         for (int q = 0; q < 2; ++q)
-                            hm |= (uint32_t)(half & (any | region_hit(s, k2t, X0 + 8 * q, 8, Y0, W, H))) << (2 * h + q);
+                            hm |= (uint32_t)(half & region_hit(s, k2t, X0 + 8 * q, 8, Y0, W, H)) << (2 * h + q);
                     }
                 }
                 float4 f0, f1;
