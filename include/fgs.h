@@ -108,9 +108,11 @@ typedef struct {
     int64_t visible;   /* Gaussians that survived preprocessing          */
     int64_t pairs;     /* Gaussian-tile key/value pairs emitted          */
     int32_t tiles_x, tiles_y;
-    int32_t sort_passes; /* radix passes: 4 over the depth keys, then those
-                           over the super-tile ids of the entries (one of up
-                           to 9 bits, else 8 bits each)                      */
+    int32_t sort_passes; /* radix passes: 4 over the depth keys (counted so also
+                           where one workgroup sorts few Gaussians and passes
+                           over the digits on which the depths differ), then
+                           those over the super-tile ids of the entries (one of
+                           up to 9 bits, else 8 bits each)                   */
     int32_t big_chunks; /* 256-tile chunks of the rectangles of more than 64
                            tiles, tested by wavefronts across the GPU        */
     int64_t candidates; /* Gaussians preprocessed: the cull's candidates of a
@@ -276,9 +278,10 @@ fgs_status fgs_render_prepared(fgs_context *ctx, const fgs_prepared *prepared, c
  * fgs_render_prepared for camera c alone.  No frame is saved (a batch has
  * no backward) and a batch collects neither stage times nor work counts.
  * Device memory: one set of frame buffers per camera slot, grown on demand
- * (fgs_reserve does not size them) and kept by the context for later batches.  Enqueued on `stream`: the second halves of odd
- * cameras run on the context's own second stream, which `stream` waits for
- * on the device, so later work on `stream` sees every output.  Like
+ * (fgs_reserve does not size them) and kept by the context for later batches.
+ * Enqueued on `stream`: after the shared preprocess the odd cameras run on the
+ * context's own second stream, which `stream` waits for on the device, so later
+ * work on `stream` sees every output.  Like
  * fgs_render_prepared it returns once the frame counters are on the host.
  * Errors as for fgs_render_prepared, and INVALID_ARGUMENT for ncams out of
  * range. */
@@ -309,7 +312,7 @@ fgs_status fgs_render_prepared_batch(fgs_context *ctx, const fgs_prepared *prepa
  * Enqueued on `stream`, which first waits for the forward's work if it ran
  * on another stream.  Floating-point atomics make the summation order, and so
  * the last bits of the gradients, vary from run to run.  The context's
- * accumulation buffer (9 floats per Gaussian) grows on first use. */
+ * accumulation buffer (16 floats per Gaussian) grows on first use. */
 fgs_status fgs_render_backward(fgs_context *ctx, const fgs_frame *frame, const fgs_scene *scene,
                                const fgs_camera *cam, const fgs_options *opt, const float *dL_drgb,
                                const fgs_scene_grad *grad, void *stream);
@@ -365,10 +368,12 @@ typedef struct {
                                   the entry at which it stops, else the whole list),
                                   summed over the instrumented frames                */
     double ms_cull;            /* the cull of a prepared scene (0 for raw parameters) */
-    int64_t blend_wave_steps;  /* with FGS_INSTR_WORK: (wavefront, list entry) steps the
-                                  blend executes; each evaluates one entry at the
-                                  wavefront's 128 pixels (entries that miss the
-                                  wavefront's half tile are skipped)                 */
+    int64_t blend_wave_steps;  /* with FGS_INSTR_WORK: (wavefront, list entry) steps of
+                                  the blend by half tiles, which counts the work; each
+                                  evaluates one entry at the wavefront's 128 pixels
+                                  (entries that miss the wavefront's half are skipped).
+                                  Images of few tiles are otherwise blended by
+                                  quadrants of 64 pixels, the same entries           */
 } fgs_timings;
 
 /* Select instrumentation flags for later fgs_render calls and clear the sums. */

@@ -54,7 +54,7 @@ __device__ __forceinline__ void block_range(uint32_t n, uint32_t b, uint32_t nb,
 // number of keys instead of some one tile of 4096 more than others.  With tiles
 // of 4096 keys throughout, a depth pass over 10,000 keys took 12 us, now 7
 // (200,000: 14, now 8; 1M: 14.5, now 12.6); the super-tile pass over 0.23M
-// entries 30 us, now 9.3; the two over 8.6M entries 141 + 114, now 110 + 91.
+// entries 30 us, now 9.3; the two over 8.6M entries 141 + 114, now 90 + 82.
 constexpr uint32_t kItemStep = 4;
 static_assert(kSortItems % kItemStep == 0, "whole steps");
 __device__ __forceinline__ uint32_t tile_items(uint32_t n, uint32_t nb) {

@@ -11,8 +11,9 @@
 // the exclusive scan of the tiles' pair counts.  A super-tile's entries are
 // cut into chunks of kListChunk, one wavefront each, so that a dense
 // super-tile spreads over many CUs:
-//   k_list_chunks  one workgroup: chunk bases of the super-tiles (a scan of
-//                  their chunk counts) and the super-tile of every chunk;
+//   k_list_chunks  up to 16 workgroups, each scanning all super-tiles and
+//                  writing its share: chunk bases of the super-tiles and the
+//                  super-tile of every chunk;
 //   k_list_count   per chunk: the 64 tiles' hit counts (lane j: bit j), by
 //                  transposing each 64 x 64 bit block of masks across lanes;
 //   k_list_scan    one workgroup per super-tile: exclusive scan of its
@@ -22,11 +23,10 @@
 //                  of tile ids): the earlier rows' sums, then an exclusive
 //                  scan of the band's tile totals in tile id order ->
 //                  ranges[t] = [start, start + count);
-//   k_list_write   per chunk again, tile by tile over its four 64-entry
-//                  blocks (one entry per lane): the lanes whose mask has the
-//                  tile's bit write their Gaussian at the tile's running
-//                  position plus their rank among those lanes (a ballot),
-//                  one contiguous store per block.
+//   k_list_write   per chunk again: its masks transposed, lane j lists in LDS
+//                  the entries that hit tile j behind the earlier tiles', and
+//                  the list is written by all lanes, each entry's Gaussian at
+//                  its tile's running position.
 // Chunks are dealt to the XCDs in eight contiguous ranges, so that a
 // super-tile's consecutive chunks, which write the same tiles' lists, share
 // an L2.
