@@ -371,12 +371,15 @@ void SpareBlock::drop() {
     bytes_ = 0;
 }
 
-void SpareBlock::put(PreparedBuffers &pb) {
+bool SpareBlock::may_keep(const PreparedBuffers &pb) {
     size_t free_bytes = 0, total = 0;
-    const bool roomy = pb.block && pb.block_bytes <= kMax && hipMemGetInfo(&free_bytes, &total) == hipSuccess &&
-                       free_bytes >= total / 4;
+    return pb.block && pb.block_bytes <= kMax && hipMemGetInfo(&free_bytes, &total) == hipSuccess &&
+           free_bytes >= total / 4;
+}
+
+void SpareBlock::put(PreparedBuffers &pb) {
     std::lock_guard<std::mutex> lk(spare_list().mu);
-    if (roomy && pb.block_bytes >= bytes_ && hipGetDevice(&device_) == hipSuccess) {
+    if (pb.block && pb.block_bytes >= bytes_ && hipGetDevice(&device_) == hipSuccess) {
         free_p(block_);
         block_ = pb.block;
         bytes_ = pb.block_bytes;

@@ -219,7 +219,10 @@ class SpareBlock {
     SpareBlock(const SpareBlock &) = delete;
     SpareBlock &operator=(const SpareBlock &) = delete;
     void drop();                               // free it
-    void put(PreparedBuffers &pb);             // keep pb's block if it may be kept, else free it; empties pb
+    // whether a block may be kept (asks the device for its free memory, 4 us: to be
+    // called while work is still in flight)
+    static bool may_keep(const PreparedBuffers &pb);
+    void put(PreparedBuffers &pb);             // keep pb's block instead of a smaller one; empties pb
     void *get(size_t need, size_t *bytes);     // the block, if it holds need bytes and not twice as many
     size_t held() const;                       // its bytes
 

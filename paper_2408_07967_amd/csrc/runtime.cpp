@@ -698,8 +698,9 @@ fgs_status fgs_prepared_release(fgs_context *ctx, fgs_prepared *p) {
         if (ctx->prepared[i] == p) {
             ctx->prepared.erase(ctx->prepared.begin() + (long)i);
             (void)hipSetDevice(ctx->device);
+            const bool keep = SpareBlock::may_keep(p->pb);
             // frames may still read it; a failure stays with the block
-            if (hipDeviceSynchronize() == hipSuccess)
+            if (hipDeviceSynchronize() == hipSuccess && keep)
                 ctx->spare.put(p->pb);
             else
                 free_prepared(p->pb);
